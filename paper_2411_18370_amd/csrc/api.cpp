@@ -114,6 +114,19 @@ struct ft_ctx_s {
     size_t cap_stats = 0;
     float *d_bsum = nullptr;  // block sums of the split binary evaluation
     size_t cap_bsum = 0;
+    // binary banks: bounds of the bank being evaluated, and the time segments
+    // of the SFT set's summation blocks (built on the first use after a load)
+    struct BinaryBounds {
+        double f0_lo = 0.0, f0_hi = 0.0, aw_hi = 0.0, om_hi = 0.0, phase = 0.0, dt_abs = 0.0, t_ref = 0.0;
+    } bin_bounds;
+    bool seg_valid = false, seg_usable = false, seg_tab_valid = false;  // segments; their device tables (of seg_t_ref, seg_res)
+    double seg_t_ref = 0.0, seg_res = 0.0;
+    double seg_hs = 0.0, seg_dv = 0.0;
+    std::vector<uint32_t> seg_mask_h;
+    uint32_t *d_seg_mask = nullptr;
+    float *d_seg_tab = nullptr;  // par | sval
+    char *d_seg_fit = nullptr;
+    size_t cap_seg_mask = 0, cap_seg_tab = 0, cap_seg_fit = 0;
 
     // selection
     uint32_t *d_hist = nullptr, *d_state = nullptr, *d_cnt = nullptr, *d_off = nullptr,
@@ -603,6 +616,9 @@ void ft_destroy(ft_ctx c)
     release(&c->d_edges, &c->cap_edges);
     release(&c->d_stats, &c->cap_stats);
     release(&c->d_bsum, &c->cap_bsum);
+    release(&c->d_seg_mask, &c->cap_seg_mask);
+    release(&c->d_seg_tab, &c->cap_seg_tab);
+    release(&c->d_seg_fit, &c->cap_seg_fit);
     release(&c->d_hist, &c->cap_hist);
     release(&c->d_state, &c->cap_state);
     release(&c->d_cnt, &c->cap_cnt);
@@ -694,11 +710,11 @@ ft_status ft_set_sfts(ft_ctx c, int32_t n_det, const int32_t *n_sft, const doubl
         if (!is_finite(t)) return fail(c, FT_E_INVALID, "t_mid holds a non-finite value");
     hipError_t e;
     const size_t n_cells = (size_t)total * (size_t)n_bins;
-    if ((e = ensure(&c->d_power, &c->cap_power, n_cells)) != hipSuccess) return hip_fail(c, e, "alloc power");
+    if ((e = ensure(&c->d_power, &c->cap_power, n_cells + TABLE_PAD)) != hipSuccess) return hip_fail(c, e, "alloc power");
     if ((e = ensure(&c->d_tmid, &c->cap_tmid, (size_t)total)) != hipSuccess) return hip_fail(c, e, "alloc t_mid");
     if ((e = ensure(&c->d_dt, &c->cap_dt, (size_t)total)) != hipSuccess) return hip_fail(c, e, "alloc dt");
     if (weight && ((e = ensure(&c->d_weight, &c->cap_weight, (size_t)total)) != hipSuccess ||
-                   (e = ensure(&c->d_power_w, &c->cap_power_w, n_cells)) != hipSuccess))
+                   (e = ensure(&c->d_power_w, &c->cap_power_w, n_cells + TABLE_PAD)) != hipSuccess))
         return hip_fail(c, e, "alloc weight");
     e = hipMemcpyAsync(c->d_power, power, n_cells * sizeof(float), hipMemcpyDefault, c->stream);
     if (e == hipSuccess)
@@ -735,6 +751,7 @@ ft_status ft_set_sfts(ft_ctx c, int32_t n_det, const int32_t *n_sft, const doubl
     c->t_mid_h.swap(tm);
     c->have_sfts = true;
     c->have_eval = false;
+    c->seg_valid = false;
     return FT_OK;
 }
 
@@ -771,8 +788,8 @@ static ft_status ensure_nc(ft_ctx c)
     if (c->ind_valid) return FT_OK;
     const size_t n_cells = (size_t)c->n_sft * (size_t)c->n_bins;
     hipError_t e;
-    if ((e = ensure(&c->d_ind, &c->cap_ind, n_cells)) != hipSuccess ||
-        (c->has_weight && (e = ensure(&c->d_ind_w, &c->cap_ind_w, n_cells)) != hipSuccess) ||
+    if ((e = ensure(&c->d_ind, &c->cap_ind, n_cells + TABLE_PAD)) != hipSuccess ||
+        (c->has_weight && (e = ensure(&c->d_ind_w, &c->cap_ind_w, n_cells + TABLE_PAD)) != hipSuccess) ||
         (e = ensure(&c->d_mu_sigma_nc, &c->cap_mu_sigma_nc, 2)) != hipSuccess)
         return hip_fail(c, e, "alloc number-count tables");
     e = launch_nc_table(c->d_power, c->has_weight ? c->d_weight : nullptr, c->d_ind, c->d_ind_w, c->n_sft, c->n_bins,
@@ -815,6 +832,7 @@ static ft_status set_velocities_impl(ft_ctx c, const double *v, bool sync)
     if (e != hipSuccess) return hip_fail(c, e, "copy velocities");
     c->v_h.swap(vh);
     c->vmax = vmax;
+    c->seg_valid = false;
     c->have_vel = true;
     c->have_eval = false;
     return FT_OK;
@@ -878,7 +896,7 @@ ft_status ft_gen_sfts(ft_ctx c, int32_t n_det, const int32_t *n_sft, const doubl
     // SFT bookkeeping first (as ft_set_sfts), then the velocities
     hipError_t e;
     const size_t n_cells = (size_t)total * (size_t)n_bins;
-    if ((e = ensure(&c->d_power, &c->cap_power, n_cells)) != hipSuccess ||
+    if ((e = ensure(&c->d_power, &c->cap_power, n_cells + TABLE_PAD)) != hipSuccess ||
         (e = ensure(&c->d_tmid, &c->cap_tmid, (size_t)total)) != hipSuccess ||
         (e = ensure(&c->d_dt, &c->cap_dt, (size_t)total)) != hipSuccess ||
         (e = ensure(&c->d_arms, &c->cap_arms, (size_t)total * 6)) != hipSuccess ||
@@ -1155,6 +1173,7 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
         // the orbital phase stays inside the library cosine's reduction range,
         // and the track frequency stays positive: a_p Omega < 1/2
         const double dt_abs = std::max(std::fabs(dt_min), std::fabs(dt_max));
+        double om_max = 0.0, ph_max = 0.0;
         for (int64_t t = 0; t < n0; ++t) {
             const double ap = c->ap_h[t], om = c->omega_h[t], pb = c->phib_h[t];
             if (!is_finite(ap) || !is_finite(om) || !is_finite(pb) || ap < 0.0 || om < 0.0)
@@ -1164,7 +1183,10 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
             if (!(om * dt_abs + std::fabs(pb) < 1.5e6))
                 return fail(c, FT_E_UNSUPPORTED, "orbital phase beyond 1.5e6 rad (template %lld)", (long long)t);
             aw_max = std::max(aw_max, ap * om);
+            om_max = std::max(om_max, om);
+            ph_max = std::max(ph_max, om * dt_abs + std::fabs(pb));
         }
+        c->bin_bounds = {f0_min, f0_max, aw_max, om_max, ph_max, dt_abs, t_ref};
     }
     const double x_max = (f0_max + c_max) * (1.0 + c->vmax + aw_max) * c->t_sft;
     if (!(x_max < 2147483000.0)) return fail(c, FT_E_UNSUPPORTED, "track frequencies above 2^31/T_sft");
@@ -1244,11 +1266,7 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
     run.n_list = grid ? 0 : n0;
     run.t_sft = c->t_sft;
     run.vmax = c->vmax;
-    if (binary) {
-        ft_status stc = binary_cos_delta(c, run.cos_delta);
-        if (stc != FT_OK) return stc;
-        run.range_ok = bin_range_ok ? 1 : 0;
-    }
+    run.range_ok = bin_range_ok ? 1 : 0;
     // bounds used by the grid kernel
     if (grid) guard_params(c->f0_h.data(), n0, f0_max, x_max, c->vmax, c->t_sft, run.dT, run.eta);
     (void)dt_min;
@@ -1567,12 +1585,121 @@ ft_status ft_eval_templates(ft_ctx c, const ft_bank *bank, double t_ref, const f
 
 // Launch sequence of an evaluation: clear flags, map sub-bands, evaluate,
 // select, re-sum, rank (run fully prepared; n_seg_map = f0 values to map).
-// Binary banks too small to fill the GPU with one lane per template (about
-// 2^19 lanes are resident) split their SUM_BLOCK-SFT blocks over several
-// workgroup rows; the per-block sums take n_list ceil(N / SUM_BLOCK) floats of
-// context memory, at most 256 MB (else, or if that allocation fails, the bank
-// is evaluated unsplit).  Either way the statistics are the same bits.
-static hipError_t eval_binary(ft_ctx c, const EvalRun &run)
+// Time segments of the summation blocks for the bank kernel: bit j of a
+// block's mask is set where its SFT j starts a segment.  Times ascend in a
+// segment and span at most 1.2 times the median block's span (blocks across a
+// data gap or a change of detector are cut; a few SFTs missing are not).
+static ft_status bank_segments(ft_ctx c)
+{
+    if (c->seg_valid) return FT_OK;
+    const int n = c->n_sft, n_blk = (n + SUM_BLOCK - 1) / SUM_BLOCK;
+    const double *t = c->t_mid_h.data(), *v = c->v_h.data();
+    std::vector<double> spans((size_t)n_blk);
+    for (int b = 0; b < n_blk; ++b) {
+        const int k1 = std::min(n, (b + 1) * SUM_BLOCK);
+        double lo = t[b * SUM_BLOCK], hi = lo;
+        for (int k = b * SUM_BLOCK; k < k1; ++k) {
+            lo = std::min(lo, t[k]);
+            hi = std::max(hi, t[k]);
+        }
+        spans[(size_t)b] = hi - lo;
+    }
+    std::nth_element(spans.begin(), spans.begin() + n_blk / 2, spans.end());
+    const double limit = 1.2 * spans[(size_t)(n_blk / 2)];
+    c->seg_mask_h.assign((size_t)n_blk, 0u);
+    double dv2 = 0.0;
+    for (int b = 0; b < n_blk; ++b) {
+        const int k1 = std::min(n, (b + 1) * SUM_BLOCK);
+        for (int k = b * SUM_BLOCK; k < k1;) {
+            int e = k + 1;
+            while (e < k1 && t[e] >= t[e - 1] && t[e] - t[k] <= limit) ++e;
+            c->seg_mask_h[(size_t)b] |= 1u << (k % SUM_BLOCK);
+            const double *v0 = v + 3 * (size_t)((k + e - 1) >> 1);
+            for (int q = k; q < e; ++q) {
+                const double x = v[3 * (size_t)q] - v0[0], y = v[3 * (size_t)q + 1] - v0[1], z = v[3 * (size_t)q + 2] - v0[2];
+                dv2 = std::max(dv2, x * x + y * y + z * z);
+            }
+            k = e;
+        }
+    }
+    c->seg_hs = limit > 0.0 ? 0.5 * limit : 1.0;
+    c->seg_dv = std::sqrt(dv2) * (1.0 + 1e-12);
+    // blocks that are not one whole segment are summed SFT by SFT: the bank
+    // kernel is for data where they are few
+    int cut = 0;
+    for (int b = 0; b < n_blk; ++b) cut += c->seg_mask_h[(size_t)b] != 1u || n - b * SUM_BLOCK < SUM_BLOCK;
+    c->seg_usable = cut <= std::max(2, n_blk / 4);
+    hipError_t e = ensure(&c->d_seg_mask, &c->cap_seg_mask, (size_t)n_blk);
+    if (e == hipSuccess) e = ensure(&c->d_seg_tab, &c->cap_seg_tab, (size_t)n_blk * SUM_BLOCK * 5);
+    if (e == hipSuccess) e = ensure(&c->d_seg_fit, &c->cap_seg_fit, bank_fit_bytes(n_blk));
+    if (e != hipSuccess) {  // no room for the tables: the gather kernel needs none
+        (void)hipGetLastError();
+        c->seg_usable = false;
+    }
+    if (c->seg_usable) {
+        e = hipMemcpyAsync(c->d_seg_mask, c->seg_mask_h.data(), (size_t)n_blk * sizeof(uint32_t), hipMemcpyHostToDevice,
+                           c->stream);
+        if (e != hipSuccess) return hip_fail(c, e, "time segments");
+    }
+    c->seg_valid = true;
+    c->seg_tab_valid = false;
+    return FT_OK;
+}
+
+constexpr double kFitRes = 1e-5;  // largest velocity-fit residual of the bank kernel (bins)
+
+// Plan of a binary evaluation.  The bank kernel (LDS windows) takes banks with
+// per-SFT weights whose tracks are proved inside the table, whose data have few
+// cut blocks, whose whole bin range fits an LDS row, and whose block polynomials are accurate: om1 <= 0.3
+// and an estimate bound below 3e-5 bins even with the worst accepted velocity
+// fit, where at most 12% of the waves sum a block twice.  Everything else
+// (width 0 in the plan) takes the gather kernel, which needs the cosine bound.
+// At 2e6 templates x 10^4 SFTs (190 bins, 10% of the SFTs missing) the bank
+// kernel takes 7.4 ms, the gather kernel 13.3 ms.
+static ft_status plan_binary(ft_ctx c, EvalRun &run, BankPlan &pl)
+{
+    pl = BankPlan{};
+    const auto &bd = c->bin_bounds;
+    if (!run.arms && run.range_ok && c->cos_mode == 0) {
+        ft_status st = bank_segments(c);
+        if (st != FT_OK) return st;
+        const double lo = std::floor(bd.f0_lo * (1.0 - c->vmax - bd.aw_hi) * c->t_sft + 0.5) - 2.0;
+        const double hi = std::floor(bd.f0_hi * (1.0 + c->vmax + bd.aw_hi) * c->t_sft + 0.5) + 2.0;
+        const int64_t w0 = std::max((int64_t)std::max(lo, 0.0), c->first_bin);
+        const int64_t w1 = std::min((int64_t)std::min(hi, 4e9), c->first_bin + c->n_bins - 1);
+        const double f0T = bd.f0_hi * c->t_sft, om1 = bd.om_hi * c->seg_hs;
+        if (c->seg_usable && w1 >= w0 && w1 - w0 < BANK_MAX_WIDTH && om1 <= 0.3 &&
+            bank_eps(f0T, f0T * bd.aw_hi, om1, bd.phase, c->seg_dv, kFitRes / f0T) <= 3e-5) {
+            const size_t n_pad = (size_t)((c->n_sft + SUM_BLOCK - 1) / SUM_BLOCK) * SUM_BLOCK;
+            pl.mask = c->d_seg_mask;
+            pl.par = c->d_seg_tab;
+            pl.sval = c->d_seg_tab + 4 * n_pad;
+            pl.fit = c->d_seg_fit;
+            pl.hs = c->seg_hs;
+            pl.dv_max = c->seg_dv;
+            pl.dt_abs = bd.dt_abs;
+            pl.win_lo = (int32_t)w0;
+            pl.width = (int32_t)(w1 - w0 + 1);
+            pl.cols = (pl.width + 3) / 4 * 4;
+            // a power of two, so banks of one band share the tables
+            const double res = std::exp2(std::floor(std::log2(kFitRes / f0T)));
+            if (c->seg_tab_valid && c->seg_t_ref == bd.t_ref && c->seg_res == res) return FT_OK;
+            const hipError_t e = launch_bank_tables(run, pl, res, c->stream);
+            c->seg_tab_valid = e == hipSuccess;
+            c->seg_t_ref = bd.t_ref;
+            c->seg_res = res;
+            return e == hipSuccess ? FT_OK : hip_fail(c, e, "bank tables");
+        }
+    }
+    return binary_cos_delta(c, run.cos_delta);
+}
+
+// Binary banks too small to fill the GPU with one lane per template split
+// their SUM_BLOCK-SFT blocks over several workgroup rows; the per-block sums
+// take n_list ceil(N / SUM_BLOCK) floats of context memory, at most 256 MB
+// (else, or if that allocation fails, the bank is evaluated unsplit).  Either
+// way the statistics are the same bits.
+static hipError_t eval_binary(ft_ctx c, const EvalRun &run, const BankPlan &pl)
 {
     constexpr int64_t kLanes = int64_t(1) << 19;
     constexpr size_t kMaxBytes = size_t(256) << 20;
@@ -1580,13 +1707,30 @@ static hipError_t eval_binary(ft_ctx c, const EvalRun &run)
     int n_seg = 1;
     if (!run.arms && run.sum_mode == FT_SUM_BLOCKED && run.n_list > 0 && run.n_list < kLanes && n_blk > 1 &&
         (size_t)n_blk * (size_t)run.n_list * sizeof(float) <= kMaxBytes) {
-        n_seg = (int)std::min<int64_t>(n_blk, (kLanes + run.n_list - 1) / run.n_list);
+        if (pl.width > 0) {
+            // workgroups come in rounds of the resident ones; a row of the
+            // split costs its blocks plus about half a block to start
+            const int64_t wgs = (run.n_list + BANK_THREADS - 1) / BANK_THREADS;
+            const int64_t resident = pl.width <= 256 ? 512 : 256;
+            double best = 1e300;
+            for (int64_t bps = n_blk; bps >= 1; --bps) {
+                const int64_t rows = (n_blk + bps - 1) / bps;
+                const double cost = (double)((wgs * rows + resident - 1) / resident) * ((double)bps + 0.5);
+                if (cost < 0.95 * best) {
+                    best = cost;
+                    n_seg = (int)rows;
+                }
+            }
+        } else {
+            n_seg = (int)std::min<int64_t>(n_blk, (kLanes + run.n_list - 1) / run.n_list);
+        }
         if (n_seg > 1 && ensure(&c->d_bsum, &c->cap_bsum, (size_t)(n_blk * run.n_list)) != hipSuccess) {
             (void)hipGetLastError();
             n_seg = 1;
         }
     }
-    return launch_eval_binary(run, n_seg > 1 ? c->d_bsum : nullptr, n_seg, c->stream);
+    float *bsum = n_seg > 1 ? c->d_bsum : nullptr;
+    return pl.width > 0 ? launch_eval_bank(run, pl, bsum, n_seg, c->stream) : launch_eval_binary(run, bsum, n_seg, c->stream);
 }
 
 // Grid launch of `tile`; with `tail`, the f1 values past the last multiple of
@@ -1624,6 +1768,11 @@ static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile,
     ft_status st;
     const int n_seg = opts->n_sub;
     const int k = opts->k;
+    BankPlan bank;
+    if (run.ap) {
+        st = plan_binary(c, run, bank);
+        if (st != FT_OK) return st;
+    }
     // first guess of the candidate buffer: 64 per toplist slot, never more than
     // the templates themselves nor 2^26 entries (ft_sync regrows it to the
     // exact count when the threshold ties many templates)
@@ -1640,7 +1789,7 @@ static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile,
         e = launch_sky_moments(run.arms, run.weight, run.n_sft, run.sky, run.n_sky, opts->statistic, c->d_sky_norm,
                                c->d_sky_ms, c->d_err, c->stream);
     if (e == hipSuccess)
-        e = run.ap ? eval_binary(c, run)
+        e = run.ap ? eval_binary(c, run, bank)
             : !grid ? launch_eval_list(run, c->stream)
             : tile < 0 ? launch_eval_grid_direct(run, c->stream) : launch_grid(run, tile, tail, c->stream);
     if (e == hipSuccess) e = hipEventRecord(c->ev[1], c->stream);
@@ -1762,9 +1911,10 @@ static ft_status binary_random_run(ft_ctx c, const ft_binary_region *reg, uint64
     run.vmax = c->vmax;
     run.sum_mode = opts->sum_mode;
     run.precision = opts->precision;
-    st = binary_cos_delta(c, run.cos_delta);
-    if (st != FT_OK) return st;
     run.range_ok = binary_range_ok(c, reg->f0_lo, reg->f0_hi, reg->ap_hi * reg->omega_hi) ? 1 : 0;
+    const double ph = std::max(std::fabs(reg->phib_lo), std::fabs(reg->phib_hi));
+    c->bin_bounds = {reg->f0_lo, reg->f0_hi, reg->ap_hi * reg->omega_hi, reg->omega_hi,
+                     reg->omega_hi * dt_abs + ph, dt_abs, t_ref};
     return apply_stat_weights(c, opts, false, 0, run);
 }
 
@@ -1817,6 +1967,9 @@ ft_status ft_eval_binary_boxes(ft_ctx c, const ft_binary_region *reg, uint64_t s
     EvalRun run;
     st = binary_random_run(c, reg, seed, n, t_ref, opts, run, &div, c->d_box);
     if (st != FT_OK) return st;
+    BankPlan bank;
+    st = plan_binary(c, run, bank);
+    if (st != FT_OK) return st;
     c->have_eval = false;  // the bank and statistics are replaced
     const double N = (double)c->n_sft;
     const double rel_err = opts->sum_mode == FT_SUM_BLOCKED ? 40.0 * std::ldexp(1.0, -24) + 4.0 * N * std::ldexp(1.0, -53)
@@ -1829,7 +1982,7 @@ ft_status ft_eval_binary_boxes(ft_ctx c, const ft_binary_region *reg, uint64_t s
             return hip_fail(c, e, "alloc box candidates");
         BoxBufs bb{c->d_box, c->d_bmax32, c->d_bcount, c->d_bmax64, c->d_bidx, c->d_bcand, c->d_bcand_s64, c->d_bncand, cap};
         e = launch_fill_u32(c->d_err, 0u, 1, c->stream);
-        if (e == hipSuccess && attempt == 0) e = eval_binary(c, run);
+        if (e == hipSuccess && attempt == 0) e = eval_binary(c, run, bank);
         if (e == hipSuccess) e = launch_box_max(run, n, n_boxes, bb, rel_err, c->stream);
         uint32_t n_cand[2] = {0, 0};
         if (e == hipSuccess) e = hipMemcpyAsync(n_cand, c->d_bncand, sizeof n_cand, hipMemcpyDeviceToHost, c->stream);

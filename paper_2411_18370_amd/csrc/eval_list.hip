@@ -924,6 +924,13 @@ hipError_t launch_eval_list(const EvalRun &run, hipStream_t s)
     return hipGetLastError();
 }
 
+hipError_t launch_binary_block_sum(const float *bsum, int64_t n, int n_blk, float *stats, hipStream_t s)
+{
+    hipLaunchKernelGGL(binary_block_sum_kernel, dim3(grid_for(n, 256, (1u << 16))), dim3(256), 0, s, bsum, n, n_blk,
+                       stats);
+    return hipGetLastError();
+}
+
 hipError_t launch_eval_binary(const EvalRun &run, float *bsum, int n_seg, hipStream_t s)
 {
     if (run.n_list <= 0) return hipSuccess;
@@ -939,9 +946,7 @@ hipError_t launch_eval_binary(const EvalRun &run, float *bsum, int n_seg, hipStr
             hipLaunchKernelGGL((eval_binary_kernel<true, true, false, true>), g2, dim3(256), 0, s, run, bsum, bps);
         else
             hipLaunchKernelGGL((eval_binary_kernel<false, true, false, true>), g2, dim3(256), 0, s, run, bsum, bps);
-        hipLaunchKernelGGL(binary_block_sum_kernel, grid, dim3(256), 0, s, (const float *)bsum, run.n_list, n_blk,
-                           run.stats);
-        return hipGetLastError();
+        return launch_binary_block_sum(bsum, run.n_list, n_blk, run.stats, s);
     }
     float *const none = nullptr;
     if (run.cos_delta > 0.0 && run.range_ok) {

@@ -306,6 +306,44 @@ hipError_t launch_eval_list(const EvalRun &run, hipStream_t s);
 // over n_seg workgroup rows and bsum [ceil(n_sft / SUM_BLOCK)][n_list] holds the
 // per-block FP32 sums; else nullptr.
 hipError_t launch_eval_binary(const EvalRun &run, float *bsum, int n_seg, hipStream_t s);
+// The statistics of split binary evaluations: each template's block sums
+// bsum[block][template] added in block order in FP64.
+hipError_t launch_binary_block_sum(const float *bsum, int64_t n, int n_blk, float *stats, hipStream_t s);
+
+// Binary banks through LDS windows (eval_bank.hip): what the host plans.
+struct BankPlan {
+    const uint32_t *mask;  // [blocks] segment starts of each SUM_BLOCK-SFT block
+    float *par;            // [n_sft][4] per-SFT (s, v - v0)
+    float *sval;           // [blocks SUM_BLOCK] s alone
+    void *fit;             // velocity polynomials (bank_fit_bytes)
+    double hs, dv_max;     // largest half-span of a segment (s), largest |v - v0| in one
+    double dt_abs;         // largest |t - t_ref|
+    int32_t win_lo, width; // bins [win_lo, win_lo + width) hold every template's track
+    int32_t cols;          // width rounded up to a multiple of 4
+};
+constexpr int BANK_MAX_WIDTH = 512;
+// Floats allocated past a context's SFT tables: the bank kernel copies windows
+// 16 bytes at a time.
+constexpr int TABLE_PAD = 4;
+// Error bound of the bank kernel's track estimate (bins; derived in
+// eval_bank.hip): C = f0 T a_p Omega, om1 = Omega hs, phase >= |Omega dt| +
+// |phi_b|, res the velocity fit's residual.
+__host__ __device__ inline double bank_eps(double f0T, double C, double om1, double phase, double dv_max, double res)
+{
+    const double W = f0T * dv_max, o2 = om1 * om1;
+    const double X = C * om1 + 2.0 * W, Y = C * o2 * (0.5 + om1) + W;
+    const double e = 0x1p-24 * (4.0 * X + 15.0 * Y + 6.0 * W + 1.0) + f0T * res + C * (o2 * o2 * o2 / 720 * (1.0 + om1)) +
+                     C * (4e-9 + 0x1p-50 * phase) + 0x1p-48 * f0T;
+    return 1.25 * e + 1e-9;
+}
+constexpr int BANK_THREADS = 512;  // templates per workgroup of the bank kernel
+// Bytes of the velocity polynomials of n_blk blocks.
+size_t bank_fit_bytes(int n_blk);
+// Fills the plan's tables from run.dt and run.v (fits with residuals up to res_max).
+hipError_t launch_bank_tables(const EvalRun &run, const BankPlan &plan, double res_max, hipStream_t s);
+// Evaluates run (per-SFT weights, tracks proved inside the table); with bsum
+// [blocks][n_list] the blocks are split over n_seg workgroup rows.
+hipError_t launch_eval_bank(const EvalRun &run, const BankPlan &plan, float *bsum, int n_seg, hipStream_t s);
 // Largest |v_cos_f32(x) - cos 2 pi x| over every float x in [0, 1], as the bit
 // pattern of a non-negative double in *max_bits (device memory).
 hipError_t launch_hw_cos_error(unsigned long long *max_bits, hipStream_t s);
