@@ -10,10 +10,9 @@
 //    the FP64 top-K has S32 >= K32 (1 - e)/(1 + e).  Candidates are compacted
 //    per sub-band.
 // 3. Each candidate is re-summed in FP64 in SFT order with canonical bins
-//    (one wavefront per candidate: the 64 lanes form the weighted terms of
-//    256 consecutive SFTs at a time, 4 per lane, and store them to LDS; lane 0
-//    then adds them to the running sum one by one in SFT order, so the sum is
-//    the plain sequential FP64 sum).
+//    (a workgroup per candidate: three wavefronts form the weighted terms and
+//    store them to LDS; one lane of the fourth adds them to the running sum one
+//    by one in SFT order, so the sum is the plain sequential FP64 sum).
 // 4. Candidates are ranked within their sub-band by (S64 desc, index asc);
 //    ranks < K are the toplist, identical to sorting all FP64 statistics.
 #include "ft_internal.h"
@@ -352,141 +351,273 @@ __device__ __forceinline__ TemplateParams params_of(const EvalRun &r, bool grid,
     return p;
 }
 
-__device__ __forceinline__ double readlane_f64(double v, int l)
+// Table values at the canonical bins of a template at SFTs k + 64 j, j < 4 (past
+// the last SFT: the last one's) and their weights: u_k, with sky-dependent
+// weights times ab_k(n) inv, inv = 1 / sum_k' u_k' ab_k'(n).  Four at a time
+// without a branch between them, so their loads are in flight together.
+__device__ __forceinline__ void rescore_terms(const EvalRun &r, const TemplateParams &tp, int k0, bool sky, double inv,
+                                              uint32_t &bad, float (&p)[4], double (&w)[4])
 {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
-    return __hiloint2double(hi, lo);
+    double vx[4], vy[4], vz[4], dt[4];
+    int b[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int k = min(k0 + 64 * j, r.n_sft - 1);
+        const double *vk = r.v + 3 * (int64_t)k;
+        vx[j] = vk[0];
+        vy[j] = vk[1];
+        vz[j] = vk[2];
+        dt[j] = r.dt[k];
+        w[j] = 1.0;
+    }
+    if (r.weight) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = (double)r.weight[min(k0 + 64 * j, r.n_sft - 1)];
+    }
+    if (r.ap) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            b[j] = bin_binary(tp.f0, doppler_factor(vx[j], vy[j], vz[j], tp.nx, tp.ny, tp.nz), tp.aw, tp.omega, tp.phib,
+                              dt[j], r.t_sft);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            b[j] = bin_fp64(tp.f0, tp.f1 * dt[j], doppler_factor(vx[j], vy[j], vz[j], tp.nx, tp.ny, tp.nz), r.t_sft);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int k = min(k0 + 64 * j, r.n_sft - 1);
+        const int c = min(max(b[j] - r.first_bin, 0), r.n_bins - 1);
+        bad |= c != b[j] - r.first_bin ? ERR_RANGE : 0u;
+        p[j] = r.power[(int64_t)k * r.n_bins + c];
+    }
+    if (sky) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            w[j] = w[j] * (sky_ab(r.arms + 6 * (int64_t)min(k0 + 64 * j, r.n_sft - 1), tp.nx, tp.ny, tp.nz) * inv);
+    }
 }
 
-// FP64 re-summation of template t in SFT order by one wavefront: lanes form
-// the terms of 64 RS_UNROLL SFTs at a time and publish them to the wave's LDS
-// slice buf [2][64 RS_UNROLL], then lane 0 adds them one after another in SFT
-// order (the result is lane 0's).  The weight is u_k, times ab_k(n) / sum_k'
-// u_k' ab_k'(n) with sky-dependent weights.  With MOM the weight sums W1 =
-// sum w and W2 = sum w^2 come out as well.  The terms of the next chunk are
-// formed (their gathers issued) before the current chunk is added, so the
-// gathers' latency overlaps the additions.
-constexpr int RS_UNROLL = 4;
-constexpr int RS_BUF = 2 * 64 * RS_UNROLL;  // doubles of LDS per wave
+// Sequential FP64 sums over the SFTs, a group of NW waves per template: waves
+// 1 .. NW-1 of the group form the terms of a chunk of 256 (NW - 1) SFTs into one
+// of two LDS buffers while wave 0's first lane adds an earlier chunk term by
+// term in SFT order.  terms(k, p, w) gives the table values of SFTs k + 64 j,
+// j < 4 (loads in flight until the next chunk's bins are formed; anything past
+// the last SFT) and their weights; acc = sum w p, and
+// with MOM sw = sum w, sw2 = sum w^2 (the results are wave 0 lane 0's).
+// What binds it is the chain of dependent additions, 10^4 of them in 55 us with
+// the LDS reads 24 additions ahead (110 us with eight ahead: each group waited
+// for its reads); with one wave doing both, the terms' gathers and FP64 bins
+// came on top (245 us).  Called by every thread of the workgroup with the same n_sft (the
+// groups share its barriers); a group without a template is inactive.
+constexpr int SEQ_PER_WAVE = 256;
+template <int NW, bool MOM>
+struct SeqBuf {
+    static constexpr int CH = (NW - 1) * SEQ_PER_WAVE;
+    double val[2][CH];
+    double w[MOM ? 2 : 1][MOM ? CH : 1];
+};
 
-
-template <bool MOM>
-__device__ __forceinline__ double rescore_one(const EvalRun &r, bool grid, int64_t t, int lane, uint32_t &bad,
-                                              double *buf, double *w1 = nullptr, double *w2 = nullptr)
+template <int NW, bool MOM, typename F>
+__device__ __forceinline__ void seq_sums(F terms, int n_sft, SeqBuf<NW, MOM> &buf, int wave, bool active, double &acc,
+                                         double &sw, double &sw2)
 {
-    const TemplateParams tp = params_of(r, grid, t);
-    // sky-dependent weights: 1 / sum_k u_k ab_k(n) of the template's sky point
-    // (grid: per sky point, precomputed; binary banks: per template, here)
-    const bool bsky = !grid && r.arms;
-    double inv = grid && r.sky_norm ? r.sky_norm[t / ((int64_t)r.n_f0 * r.n_f1)] : 0.0;
-    if (bsky) inv = 1.0 / sky_norm_sum(r.arms, r.weight, r.n_sft, tp.nx, tp.ny, tp.nz, buf, lane);
-    // terms of SFTs k0 + 64 j + lane, j < RS_UNROLL (0 past the last SFT)
-    auto terms = [&](int k0, double (&val)[RS_UNROLL], double (&wk)[RS_UNROLL]) {
+    constexpr int CH = SeqBuf<NW, MOM>::CH;
+    const int lane = threadIdx.x & 63;
+    const int n_ch = (n_sft + CH - 1) / CH;
+    acc = sw = sw2 = 0.0;
+    if (wave == 0) __builtin_amdgcn_s_setprio(3);  // the chain goes first on its SIMD
+    float p[4] = {0.f, 0.f, 0.f, 0.f};
+    double w[4] = {0.0, 0.0, 0.0, 0.0};
+    // iteration it: the terms of chunk it are formed, those of chunk it - 1 go
+    // to LDS, chunk it - 2 is added
+    for (int it = 0; it <= n_ch + 1; ++it) {
+        if (!active) {
+        } else if (wave > 0) {
+            const int q0 = (wave - 1) * SEQ_PER_WAVE + lane;
+            float pn[4] = {0.f, 0.f, 0.f, 0.f};
+            double wn[4] = {0.0, 0.0, 0.0, 0.0};
+            if (it < n_ch) terms(it * CH + q0, pn, wn);
+            if (it > 0 && it <= n_ch) {
 #pragma unroll
-        for (int j = 0; j < RS_UNROLL; ++j) {
-            const int k = k0 + 64 * j + lane;
-            val[j] = 0.0;
-            wk[j] = 0.0;
-            if (k < r.n_sft) {
-                const double *vk = r.v + 3 * (int64_t)k;
-                const double g = doppler_factor(vk[0], vk[1], vk[2], tp.nx, tp.ny, tp.nz);
-                int b = (r.ap ? bin_binary(tp.f0, g, tp.aw, tp.omega, tp.phib, r.dt[k], r.t_sft)
-                              : bin_fp64(tp.f0, tp.f1 * r.dt[k], g, r.t_sft)) -
-                        r.first_bin;
-                if (b < 0 || b >= r.n_bins) {
-                    bad = ERR_RANGE;
-                    b = b < 0 ? 0 : r.n_bins - 1;
+                for (int j = 0; j < 4; ++j) {
+                    buf.val[(it - 1) & 1][q0 + 64 * j] = w[j] * (double)p[j];
+                    if (MOM) buf.w[(it - 1) & 1][q0 + 64 * j] = w[j];
                 }
-                double w = r.weight ? (double)r.weight[k] : 1.0;
-                if ((grid && r.sky_norm) || bsky) w = w * (sky_ab(r.arms + 6 * (int64_t)k, tp.nx, tp.ny, tp.nz) * inv);
-                val[j] = w * (double)r.power[(int64_t)k * r.n_bins + b];
-                wk[j] = w;
             }
-        }
-    };
-    double acc = 0.0, sw = 0.0, sw2 = 0.0;
-    double val[RS_UNROLL], wk[RS_UNROLL];
-    terms(0, val, wk);
-    for (int k0 = 0; k0 < r.n_sft; k0 += 64 * RS_UNROLL) {
-        double nval[RS_UNROLL], nwk[RS_UNROLL];
-        const bool more = k0 + 64 * RS_UNROLL < r.n_sft;
-        if (more) terms(k0 + 64 * RS_UNROLL, nval, nwk);
 #pragma unroll
-        for (int j = 0; j < RS_UNROLL; ++j) {
-            buf[64 * j + lane] = val[j];
-            if (MOM) buf[64 * RS_UNROLL + 64 * j + lane] = wk[j];
-        }
-        wave_lds_sync();
-        if (lane == 0) {
-            const int m_all = min(64 * RS_UNROLL, r.n_sft - k0);
+            for (int j = 0; j < 4; ++j) {
+                p[j] = pn[j];
+                w[j] = wn[j];
+            }
+        } else if (it > 1 && lane == 0) {
+            const double *x = buf.val[it & 1], *y = buf.w[MOM ? it & 1 : 0];
+            const int m = min(CH, n_sft - (it - 2) * CH);
             int q = 0;
-            for (; q + 8 <= m_all; q += 8) {
-                double x[8], y[8];
+            // four groups of eight in registers: a group is read again 24
+            // additions before its turn (an LDS read takes about 13 of them)
+            double a[4][8], b[4][8];
+            auto read = [&](int g, int at) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    x[i] = buf[q + i];
-                    if (MOM) y[i] = buf[64 * RS_UNROLL + q + i];
+                    a[g][i] = x[at + i];
+                    if (MOM) b[g][i] = y[at + i];
                 }
+            };
+            auto add = [&](int g) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    acc = acc + x[i];
+                    acc = acc + a[g][i];
                     if (MOM) {
-                        sw = sw + y[i];
-                        sw2 = sw2 + y[i] * y[i];
+                        sw = sw + b[g][i];
+                        sw2 = sw2 + b[g][i] * b[g][i];
                     }
                 }
+            };
+            if (m >= 32) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) read(g, 8 * g);
+                for (; q + 64 <= m; q += 32)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        add(g);
+                        read(g, q + 32 + 8 * g);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+#pragma unroll
+                for (int g = 0; g < 4; ++g) add(g);
+                q += 32;
             }
-            for (; q < m_all; ++q) {
-                acc = acc + buf[q];
+            for (; q < m; ++q) {
+                acc = acc + x[q];
                 if (MOM) {
-                    const double y = buf[64 * RS_UNROLL + q];
-                    sw = sw + y;
-                    sw2 = sw2 + y * y;
+                    sw = sw + y[q];
+                    sw2 = sw2 + y[q] * y[q];
                 }
             }
         }
-        wave_lds_sync();
-        if (more) {
-#pragma unroll
-            for (int j = 0; j < RS_UNROLL; ++j) {
-                val[j] = nval[j];
-                wk[j] = nwk[j];
-            }
-        }
+        __syncthreads();
     }
-    if (MOM) {
-        *w1 = sw;
-        *w2 = sw2;
+    __builtin_amdgcn_s_setprio(0);
+}
+
+// FP64 re-summation of template t in SFT order with canonical bins by one
+// workgroup (seq_sums).  With MOM the weight sums W1 = sum w and W2 = sum w^2
+// come out as well.  Four waves: three form 768 terms in about the time one
+// adds them, and a chunk's rows stay in an XCD's L2 for the other candidates
+// (eight waves: 238 against 134 us for the 1000 candidates of an all-sky band).
+constexpr int RS_WAVES = 4;
+
+template <bool MOM>
+__device__ __forceinline__ double rescore_one(const EvalRun &r, bool grid, int64_t t, uint32_t &bad,
+                                              SeqBuf<RS_WAVES, MOM> &buf, double *inv_sh, double &w1, double &w2)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const TemplateParams tp = params_of(r, grid, t);
+    // sky-dependent weights: normalised per sky point (grid, precomputed) or per
+    // template (binary banks, here)
+    const bool bsky = !grid && r.arms;
+    double inv = grid && r.sky_norm ? r.sky_norm[t / ((int64_t)r.n_f0 * r.n_f1)] : 0.0;
+    if (bsky) {
+        double c, d0, d1;
+        seq_sums<RS_WAVES, MOM>(
+            [&](int k0, float (&p)[4], double (&w)[4]) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int k = min(k0 + 64 * j, r.n_sft - 1);
+                    p[j] = 1.f;
+                    w[j] = (r.weight ? (double)r.weight[k] : 1.0) * sky_ab(r.arms + 6 * (int64_t)k, tp.nx, tp.ny, tp.nz);
+                }
+            },
+            r.n_sft, buf, wave, true, c, d0, d1);
+        if (threadIdx.x == 0) *inv_sh = 1.0 / c;
+        __syncthreads();
+        inv = *inv_sh;
+    }
+    double acc;
+    seq_sums<RS_WAVES, MOM>(
+        [&](int k, float (&p)[4], double (&w)[4]) {
+            rescore_terms(r, tp, k, (grid && r.sky_norm) || bsky, inv, bad, p, w);
+        },
+        r.n_sft, buf, wave, true, acc, w1, w2);
+    return acc;
+}
+
+// The same sum by one wavefront (per-SFT or per-sky-point weights): lanes form
+// 256 terms at a time in the wave's LDS slice and lane 0 adds them; the next
+// terms' gathers are issued before the additions.  For candidates by the
+// thousand: waves enough are in flight, and four per candidate only wait.
+constexpr int RS_UNROLL = 4;
+
+__device__ __forceinline__ double rescore_wave(const EvalRun &r, bool grid, int64_t t, int lane, uint32_t &bad,
+                                               double *buf)
+{
+    const TemplateParams tp = params_of(r, grid, t);
+    const bool sky = grid && r.sky_norm;
+    const double inv = sky ? r.sky_norm[t / ((int64_t)r.n_f0 * r.n_f1)] : 0.0;
+    float p[RS_UNROLL];
+    double w[RS_UNROLL];
+    double acc = 0.0;
+    rescore_terms(r, tp, lane, sky, inv, bad, p, w);
+    for (int k0 = 0; k0 < r.n_sft; k0 += 64 * RS_UNROLL) {
+        double val[RS_UNROLL];
+#pragma unroll
+        for (int j = 0; j < RS_UNROLL; ++j) val[j] = w[j] * (double)p[j];
+        if (k0 + 64 * RS_UNROLL < r.n_sft) rescore_terms(r, tp, k0 + 64 * RS_UNROLL + lane, sky, inv, bad, p, w);
+#pragma unroll
+        for (int j = 0; j < RS_UNROLL; ++j) buf[64 * j + lane] = val[j];
+        wave_lds_sync();
+        if (lane == 0) {
+            const int m = min(64 * RS_UNROLL, r.n_sft - k0);
+            int q = 0;
+            for (; q + 8 <= m; q += 8) {
+                double x[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[i] = buf[q + i];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc = acc + x[i];
+            }
+            for (; q < m; ++q) acc = acc + buf[q];
+        }
+        wave_lds_sync();
     }
     return acc;
 }
 
-// FP64 re-summation of the candidates, one wavefront per candidate; with
-// mom, also each candidate's sums of weights and squared weights.
-__global__ __launch_bounds__(256) void rescore_kernel(EvalRun r, bool grid, const int64_t *cand,
-                                                      const uint32_t *off, int n_seg,
-                                                      int64_t cap, double *s64, double *mom)
+__global__ __launch_bounds__(256) void rescore_many_kernel(EvalRun r, bool grid, const int64_t *cand, const uint32_t *off,
+                                                           int n_seg, int64_t cap, double *s64)
 {
-    __shared__ double rs_buf[4 * RS_BUF];
-    double *buf = rs_buf + (threadIdx.x >> 6) * RS_BUF;
-    const int lane = threadIdx.x & 63;
+    __shared__ double rs_buf[4][64 * RS_UNROLL];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t total = min((int64_t)off[n_seg], cap);
-    const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x >> 6);
     uint32_t bad = 0;
-    for (int64_t p = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); p < total;
-         p += n_waves) {
-        if (mom) {
-            double w1, w2;
-            const double acc = rescore_one<true>(r, grid, cand[p], lane, bad, buf, &w1, &w2);
-            if (lane == 0) {
-                s64[p] = acc;
+    for (int64_t p = (int64_t)blockIdx.x * 4 + wave; p < total; p += (int64_t)gridDim.x * 4) {
+        const double acc = rescore_wave(r, grid, cand[p], lane, bad, rs_buf[wave]);
+        if (lane == 0) s64[p] = acc;
+    }
+    if (bad) atomicOr(r.err, bad);
+}
+
+// FP64 re-summation of the candidates, one workgroup per candidate; with MOM,
+// also each candidate's sums of weights and squared weights.
+template <bool MOM>
+__global__ __launch_bounds__(64 * RS_WAVES) void rescore_kernel(EvalRun r, bool grid, const int64_t *cand,
+                                                                const uint32_t *off, int n_seg, int64_t cap, double *s64,
+                                                                double *mom)
+{
+    __shared__ SeqBuf<RS_WAVES, MOM> buf;
+    __shared__ double inv_sh;
+    const int64_t total = min((int64_t)off[n_seg], cap);
+    uint32_t bad = 0;
+    for (int64_t p = blockIdx.x; p < total; p += gridDim.x) {
+        double w1, w2;
+        const double acc = rescore_one<MOM>(r, grid, cand[p], bad, buf, &inv_sh, w1, w2);
+        if (threadIdx.x == 0) {
+            s64[p] = acc;
+            if (MOM) {
                 mom[2 * p] = w1;
                 mom[2 * p + 1] = w2;
             }
-        } else {
-            const double acc = rescore_one<false>(r, grid, cand[p], lane, bad, buf);
-            if (lane == 0) s64[p] = acc;
         }
     }
     if (bad) atomicOr(r.err, bad);
@@ -494,19 +625,17 @@ __global__ __launch_bounds__(256) void rescore_kernel(EvalRun r, bool grid, cons
 
 // FP64 re-summation of the templates of toplist entries top[0 .. n_out[0]):
 // out[3p .. 3p+2] = (sum, W1, W2).
-__global__ __launch_bounds__(256) void rescore_entries_kernel(EvalRun r, bool grid, const ft_candidate *top,
-                                                              const int32_t *n_out, double *out)
+__global__ __launch_bounds__(64 * RS_WAVES) void rescore_entries_kernel(EvalRun r, bool grid, const ft_candidate *top,
+                                                                        const int32_t *n_out, double *out)
 {
-    __shared__ double rs_buf[4 * RS_BUF];
-    double *buf = rs_buf + (threadIdx.x >> 6) * RS_BUF;
-    const int lane = threadIdx.x & 63;
+    __shared__ SeqBuf<RS_WAVES, true> buf;
+    __shared__ double inv_sh;
     const int64_t total = n_out[0];
-    const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x >> 6);
     uint32_t bad = 0;
-    for (int64_t p = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); p < total; p += n_waves) {
+    for (int64_t p = blockIdx.x; p < total; p += gridDim.x) {
         double w1, w2;
-        const double acc = rescore_one<true>(r, grid, top[p].index, lane, bad, buf, &w1, &w2);
-        if (lane == 0) {
+        const double acc = rescore_one<true>(r, grid, top[p].index, bad, buf, &inv_sh, w1, w2);
+        if (threadIdx.x == 0) {
             out[3 * p] = acc;
             out[3 * p + 1] = w1;
             out[3 * p + 2] = w2;
@@ -515,7 +644,8 @@ __global__ __launch_bounds__(256) void rescore_entries_kernel(EvalRun r, bool gr
     if (bad) atomicOr(r.err, bad);
 }
 
-// Rank of each candidate within its sub-band under (S64 desc, index asc).
+// Rank of each candidate within its sub-band under (S64 desc, index asc), one
+// wave per candidate: 64 rivals are compared at a time, until k are ahead.
 __global__ __launch_bounds__(256) void rank_kernel(EvalRun r, bool grid, const int64_t *cand,
                                                    const double *s64, const uint32_t *off,
                                                    int n_seg, int64_t cap, int k,
@@ -523,8 +653,8 @@ __global__ __launch_bounds__(256) void rank_kernel(EvalRun r, bool grid, const i
                                                    ft_candidate *out)
 {
     const int64_t total = min((int64_t)off[n_seg], cap);
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < total;
-         p += (int64_t)gridDim.x * blockDim.x) {
+    const int lane = threadIdx.x & 63;
+    for (int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); p < total; p += (int64_t)gridDim.x * 4) {
         int lo = 0, hi = n_seg;  // segment: off[sg] <= p < off[sg+1]
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
@@ -537,11 +667,15 @@ __global__ __launch_bounds__(256) void rank_kernel(EvalRun r, bool grid, const i
         const double sp = s64[p];
         const int64_t tp = cand[p];
         int64_t rank = 0;
-        for (int64_t q = q0; q < q1 && rank < k; ++q) {
-            const double sq = s64[q];
-            rank += (sq > sp) || (sq == sp && cand[q] < tp);
+        for (int64_t q = q0; q < q1 && rank < k; q += 64) {
+            bool ahead = false;
+            if (q + lane < q1) {
+                const double sq = s64[q + lane];
+                ahead = (sq > sp) || (sq == sp && cand[q + lane] < tp);
+            }
+            rank += __builtin_popcountll(__builtin_amdgcn_ballot_w64(ahead));
         }
-        if (rank < k) {
+        if (rank < k && lane == 0) {
             const TemplateParams par = params_of(r, grid, tp);
             ft_candidate c;
             c.index = tp;
@@ -593,10 +727,13 @@ __global__ void init_state_kernel(uint32_t *state, uint32_t *cnt, uint32_t *fill
 // ---------------------------------------------------------------------------
 // Batches: one workgroup per run does the whole exact selection of that run
 // (runs hold at most a few 1e5 templates): radix select in LDS, candidate
-// compaction, FP64 re-summation (one wavefront per candidate) and ranking.
-// SB_THREADS threads: the 16 wavefronts re-sum up to 16 candidates at once.
+// compaction, FP64 re-summation (four wavefronts per candidate) and ranking.
+// SB_THREADS threads: the re-summation takes SB_GROUPS candidates at a time, four
+// wavefronts each (three form terms, one adds them).
 // ---------------------------------------------------------------------------
 constexpr int SB_THREADS = 1024;
+constexpr int SB_GROUP_WAVES = 4;
+constexpr int SB_GROUPS = SB_THREADS / 64 / SB_GROUP_WAVES;
 
 __global__ __launch_bounds__(SB_THREADS) void select_batch_kernel(const EvalRun *runs, int k, int cap,
                                                            int64_t *cand_all, double *s64_all,
@@ -605,10 +742,11 @@ __global__ __launch_bounds__(SB_THREADS) void select_batch_kernel(const EvalRun 
 {
     __shared__ uint32_t hist[256];
     __shared__ uint32_t st_prefix, st_mask, st_krem, st_thr, st_done, n_cand;
+    __shared__ SeqBuf<SB_GROUP_WAVES, false> seq[SB_GROUPS];
     const int r = blockIdx.x;
     const EvalRun R = runs[r];
     const int64_t n_t = (int64_t)R.n_f0 * R.n_f1 * R.n_sky;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x;
     const double N = (double)R.n_sft;
     const double two_e = 2.0 * (40.0 * 0x1p-24 + 4.0 * N * 0x1p-53);
     int64_t *cand = cand_all + (int64_t)r * cap;
@@ -677,33 +815,18 @@ __global__ __launch_bounds__(SB_THREADS) void select_batch_kernel(const EvalRun 
         if (tid == 0) atomicOr(err, ERR_CAND_OVERFLOW);
         nc = cap;
     }
-    // FP64 re-summation in SFT order with canonical bins; the terms of the
-    // next 64 SFTs are formed (their loads issued) before the current 64 are
-    // added in order
+    // FP64 re-summation in SFT order with canonical bins, SB_GROUPS candidates
+    // at a time
     uint32_t bad = 0;
-    for (int p = wave; p < nc; p += SB_THREADS / 64) {
-        const TemplateParams tp = params_of(R, true, cand[p]);
-        auto term = [&](int kq) {
-            if (kq >= R.n_sft) return 0.0;
-            const double *vk = R.v + 3 * (int64_t)kq;
-            const double g = doppler_factor(vk[0], vk[1], vk[2], tp.nx, tp.ny, tp.nz);
-            int b = bin_fp64(tp.f0, tp.f1 * R.dt[kq], g, R.t_sft) - R.first_bin;
-            if (b < 0 || b >= R.n_bins) {
-                bad = ERR_RANGE;
-                b = b < 0 ? 0 : R.n_bins - 1;
-            }
-            const double w = R.weight ? (double)R.weight[kq] : 1.0;
-            return w * (double)R.power[(int64_t)kq * R.n_bins + b];
-        };
-        double acc = 0.0;
-        double val = term(lane);
-        for (int k0 = 0; k0 < R.n_sft; k0 += 64) {
-            const double nxt = term(k0 + 64 + lane);
-            const int m = min(64, R.n_sft - k0);
-            for (int l = 0; l < m; ++l) acc = acc + readlane_f64(val, l);
-            val = nxt;
-        }
-        if (lane == 0) s64[p] = acc;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), group = wave / SB_GROUP_WAVES;
+    for (int p0 = 0; p0 < nc; p0 += SB_GROUPS) {
+        const int p = p0 + group;
+        const TemplateParams tp = params_of(R, true, cand[min(p, nc - 1)]);
+        double acc, d0, d1;
+        seq_sums<SB_GROUP_WAVES, false>(
+            [&](int k_sft, float (&pw)[4], double (&w)[4]) { rescore_terms(R, tp, k_sft, false, 0.0, bad, pw, w); },
+            R.n_sft, seq[group], wave % SB_GROUP_WAVES, p < nc, acc, d0, d1);
+        if (p < nc && tid % (64 * SB_GROUP_WAVES) == 0) s64[p] = acc;
     }
     if (bad) atomicOr(err, bad);
     __syncthreads();
@@ -850,12 +973,28 @@ hipError_t launch_select(const EvalRun &r, bool grid, int n_seg, int k, double r
     return hipGetLastError();
 }
 
+// Re-summation of the candidates, about `expect` of them: a workgroup each up
+// to 4096 (50 candidates of a binary bank over 10^4 SFTs: 245 us with a wave
+// each, 62 us with a workgroup), a wave each beyond (the 10^4 of a box
+// search: 0.88 against 1.2 ms).
+static void launch_rescore(const EvalRun &r, bool grid, const int64_t *cand, const uint32_t *off, int n_seg, int64_t cap,
+                           int64_t expect, double *s64, double *mom, hipStream_t s)
+{
+    if (mom)
+        hipLaunchKernelGGL(rescore_kernel<true>, dim3(2048), dim3(64 * RS_WAVES), 0, s, r, grid, cand, off, n_seg, cap,
+                           s64, mom);
+    else if (expect <= 4096)
+        hipLaunchKernelGGL(rescore_kernel<false>, dim3(2048), dim3(64 * RS_WAVES), 0, s, r, grid, cand, off, n_seg, cap,
+                           s64, mom);
+    else
+        hipLaunchKernelGGL(rescore_many_kernel, dim3(2048), dim3(256), 0, s, r, grid, cand, off, n_seg, cap, s64);
+}
+
 hipError_t launch_rescore_rank(const EvalRun &r, bool grid, int n_seg, int k,
                                const SelectBufs &b, hipStream_t s)
 {
     double *mom = !grid && r.arms ? b.cand_mom : nullptr;  // binary banks with sky weights
-    hipLaunchKernelGGL(rescore_kernel, dim3(2048), dim3(256), 0, s, r, grid, b.cand, b.off, n_seg,
-                       b.cap, b.cand_s64, mom);
+    launch_rescore(r, grid, b.cand, b.off, n_seg, b.cap, (int64_t)n_seg * k, b.cand_s64, mom, s);
     hipLaunchKernelGGL(rank_kernel, dim3(1024), dim3(256), 0, s, r, grid, b.cand, b.cand_s64,
                        b.off, n_seg, b.cap, k, b.mu_sigma, mom, b.out);
     hipLaunchKernelGGL(n_out_kernel, dim3((unsigned)((n_seg + 255) / 256)), dim3(256), 0, s,
@@ -963,8 +1102,7 @@ hipError_t launch_box_pick(const EvalRun &r, int64_t n_boxes, const BoxBufs &b, 
                            ft_box_result *out, hipStream_t s)
 {
     const unsigned gb = (unsigned)std::min<int64_t>((n_boxes + 255) / 256, 8192);
-    hipLaunchKernelGGL(rescore_kernel, dim3(2048), dim3(256), 0, s, r, false, b.cand, b.n_cand, 1, b.cap,
-                       b.cand_s64, (double *)nullptr);
+    launch_rescore(r, false, b.cand, b.n_cand, 1, b.cap, n_boxes, b.cand_s64, nullptr, s);
     hipLaunchKernelGGL(box_pick_kernel, dim3(1024), dim3(256), 0, s, b.cand, b.cand_s64, b.n_cand, b.cap, b.box,
                        b.max64);
     hipLaunchKernelGGL(box_index_kernel, dim3(1024), dim3(256), 0, s, b.cand, b.cand_s64, b.n_cand, b.cap, b.box,
@@ -977,7 +1115,7 @@ hipError_t launch_box_pick(const EvalRun &r, int64_t n_boxes, const BoxBufs &b, 
 hipError_t launch_rescore_entries(const EvalRun &r, bool grid, const ft_candidate *top, const int32_t *n_out,
                                   double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(rescore_entries_kernel, dim3(64), dim3(256), 0, s, r, grid, top, n_out, out);
+    hipLaunchKernelGGL(rescore_entries_kernel, dim3(256), dim3(64 * RS_WAVES), 0, s, r, grid, top, n_out, out);
     return hipGetLastError();
 }
 
