@@ -1276,7 +1276,7 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
 static ft_status ensure_select(ft_ctx c, int n_seg, int k, int64_t n_seg_map, int64_t cap)
 {
     hipError_t e;
-    if ((e = ensure(&c->d_hist, &c->cap_hist, (size_t)n_seg * 256)) != hipSuccess ||
+    if ((e = ensure(&c->d_hist, &c->cap_hist, (size_t)n_seg * 1024 + SEL_TICKETS)) != hipSuccess ||
         (e = ensure(&c->d_state, &c->cap_state, (size_t)n_seg * 8)) != hipSuccess ||
         (e = ensure(&c->d_cnt, &c->cap_cnt, (size_t)n_seg)) != hipSuccess ||
         (e = ensure(&c->d_off, &c->cap_off, (size_t)n_seg + 1)) != hipSuccess ||
@@ -1294,7 +1294,8 @@ static ft_status ensure_select(ft_ctx c, int n_seg, int k, int64_t n_seg_map, in
 static SelectBufs select_bufs(ft_ctx c, int64_t cap, int stat)
 {
     SelectBufs b;
-    b.hist = c->d_hist;
+    b.ticket = c->d_hist;
+    b.hist = c->d_hist + SEL_TICKETS;
     b.state = c->d_state;
     b.cnt = c->d_cnt;
     b.off = c->d_off;
@@ -1782,8 +1783,8 @@ static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile,
     if (st != FT_OK) return st;
     if ((e = ensure(&c->d_edges, &c->cap_edges, edges.size())) != hipSuccess) return hip_fail(c, e, "alloc edges");
     e = hipMemcpyAsync(c->d_edges, edges.data(), edges.size() * sizeof(double), hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = launch_fill_u32(c->d_err, 0u, 1, c->stream);
-    if (e == hipSuccess) e = launch_subband_map(c->d_f0, n_seg_map, c->d_edges, n_seg, c->d_seg, c->stream);
+    SelectBufs sb = select_bufs(c, cap, opts->statistic);
+    if (e == hipSuccess) e = launch_select_prep(c->d_f0, n_seg_map, c->d_edges, n_seg, c->d_seg, k, sb, c->d_err, c->stream);
     if (e == hipSuccess) e = hipEventRecord(c->ev[0], c->stream);
     if (e == hipSuccess && run.sky_norm)
         e = launch_sky_moments(run.arms, run.weight, run.n_sft, run.sky, run.n_sky, opts->statistic, c->d_sky_norm,
@@ -1798,7 +1799,6 @@ static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile,
     const double rel_err = (opts->sum_mode == FT_SUM_BLOCKED ? 40.0 * std::ldexp(1.0, -24) + 4.0 * N * std::ldexp(1.0, -53)
                                                              : (N + 8.0) * std::ldexp(1.0, -24) + 4.0 * N * std::ldexp(1.0, -53)) +
                            (run.arms ? 4.0 * std::ldexp(1.0, -24) : 0.0);
-    SelectBufs sb = select_bufs(c, cap, opts->statistic);
     if (e == hipSuccess) e = launch_select(run, grid, n_seg, k, rel_err, sb, c->stream);
     if (e == hipSuccess) e = launch_rescore_rank(run, grid, n_seg, k, sb, c->stream);
     if (e == hipSuccess) e = hipEventRecord(c->ev[2], c->stream);
@@ -2027,7 +2027,7 @@ ft_status ft_sync(ft_ctx c)
         c->last_run.err = c->d_err;
         c->last_cap = cap;
         SelectBufs sb = select_bufs(c, cap, c->last_stat);
-        hipError_t e = launch_fill_u32(c->d_err, 0u, 1, c->stream);
+        hipError_t e = launch_select_prep(nullptr, 0, nullptr, c->last_nsub, nullptr, c->last_k, sb, c->d_err, c->stream);
         if (e == hipSuccess) e = launch_select(c->last_run, c->last_grid, c->last_nsub, c->last_k, c->last_rel_err, sb, c->stream);
         if (e == hipSuccess) e = launch_rescore_rank(c->last_run, c->last_grid, c->last_nsub, c->last_k, sb, c->stream);
         if (e != hipSuccess) return hip_fail(c, e, "relaunch selection");

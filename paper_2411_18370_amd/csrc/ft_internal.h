@@ -474,12 +474,16 @@ hipError_t launch_q_sample(const double *arms, const float *weight, int n_sft, d
                            const double *cos_iota, const double *psi, int64_t n, double *q, hipStream_t s);
 
 // Selection: exact toplists per segment (segment = sub-band here).
+constexpr int SEL_GROUPS = 32, SEL_LINE = 32;              // groups of workgroups, words between tickets
+constexpr int SEL_TICKET = (1 + SEL_GROUPS) * SEL_LINE;    // words of a pass
+constexpr int SEL_TICKETS = 5 * SEL_TICKET;                // four histogram passes and the count
 struct SelectBufs {
-    uint32_t *hist;       // [n_seg][256]
+    uint32_t *hist;       // [4][n_seg][256], one per radix pass
     uint32_t *state;      // [n_seg][4]: prefix, mask, k_rem, thr_key
     uint32_t *cnt;        // [n_seg]
     uint32_t *off;        // [n_seg + 1]
     uint32_t *fill;       // [n_seg]
+    uint32_t *ticket;     // [SEL_TICKETS] workgroups done with each pass and the count
     int64_t *cand;        // [cap]
     double *cand_s64;     // [cap]
     double *cand_mom;     // [cap][2] sums of each candidate's weights and squared weights
@@ -489,8 +493,10 @@ struct SelectBufs {
     const double *mu_sigma;
     int64_t cap;
 };
-hipError_t launch_subband_map(const double *f0, int64_t n, const double *edges, int n_sub,
-                              int32_t *seg, hipStream_t s);
+// Clears the error flags, maps f0[n] to sub-bands into seg (n = 0: keeps the
+// map) and sets the selection's counters; before the evaluation.
+hipError_t launch_select_prep(const double *f0, int64_t n, const double *edges, int n_seg, int32_t *seg, int k,
+                              const SelectBufs &b, uint32_t *err, hipStream_t s);
 hipError_t launch_select(const EvalRun &run, bool grid, int n_seg, int k, double rel_err,
                          const SelectBufs &b, hipStream_t s);
 hipError_t launch_rescore_rank(const EvalRun &run, bool grid, int n_seg, int k,

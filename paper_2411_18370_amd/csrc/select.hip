@@ -27,11 +27,26 @@ constexpr uint32_t NAN_KEY = 0x7f800000u;  // keys above this are NaN
 constexpr int ST = 8;                      // state words per segment
 enum { S_PREFIX = 0, S_MASK = 1, S_KREM = 2, S_DONE = 3, S_THR = 4 };
 
-__global__ void subband_map_kernel(const double *f0, int64_t n, const double *edges, int n_sub,
-                                   int32_t *seg)
+// Prepares an evaluation's selection: clears the error flags, maps the f0
+// values to sub-bands (n = 0: no mapping) and sets the selection's counters.
+__global__ __launch_bounds__(256) void select_prep_kernel(const double *f0, int64_t n, const double *edges, int n_sub,
+                                                          int32_t *seg, int k, SelectBufs b, uint32_t *err)
 {
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n;
-         q += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    if (i0 == 0) *err = 0u;
+    for (int64_t q = i0; q < SEL_TICKETS; q += step) b.ticket[q] = 0u;
+    for (int64_t q = i0; q < (int64_t)4 * n_sub * 256; q += step) b.hist[q] = 0u;
+    for (int64_t sg = i0; sg < n_sub; sg += step) {
+        uint32_t *st = b.state + sg * ST;
+        st[S_PREFIX] = 0;
+        st[S_MASK] = 0;
+        st[S_KREM] = (uint32_t)k;
+        st[S_DONE] = 0;
+        st[S_THR] = 0;
+        b.cnt[sg] = 0;
+        b.fill[sg] = 0;
+    }
+    for (int64_t q = i0; q < n; q += step) {
         const double f = f0[q];
         int lo = 0, hi = n_sub;  // find the last edge <= f
         if (!(edges[0] <= f) || !(f < edges[n_sub])) {
@@ -45,6 +60,121 @@ __global__ void subband_map_kernel(const double *f0, int64_t n, const double *ed
         }
         seg[q] = lo;
     }
+}
+
+// True in every thread of the grid's last workgroup to get here.  What the
+// workgroups hand over are device-scope atomics alone (histograms and counts),
+// read back by device-scope loads: each wave waits until its own have been
+// performed, then the ticket orders the workgroups.  A device fence would also
+// write back and drop caches, once a workgroup: measured 70 us a pass over 2048
+// of them.  Workgroups take tickets in SEL_GROUPS groups, each on a cache line
+// of its own, and the last of each group takes one of the pass: atomics on one
+// address are performed one by one (about 10 ns each).
+__device__ __forceinline__ bool last_block(uint32_t *ticket)
+{
+    __shared__ uint32_t last;
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t n = gridDim.x, g = blockIdx.x % SEL_GROUPS, members = (n - g + SEL_GROUPS - 1) / SEL_GROUPS;
+        last = 0;
+        if (__hip_atomic_fetch_add(ticket + (1 + g) * SEL_LINE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == members - 1)
+            last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                   min(n, (uint32_t)SEL_GROUPS) - 1;
+    }
+    __syncthreads();
+    return last;
+}
+
+// One wave chooses the digit holding the k_rem-th largest key of a segment from
+// its histogram h(d): lane l sums digits 255 - 4 l .. 252 - 4 l, a scan over the
+// lanes finds the four that hold it.  Updates the segment's state (every lane
+// calls it; the state is read before and written by lane 0).
+template <typename H>
+__device__ __forceinline__ void choose_digit(H h, uint32_t *st, int shift, double two_e)
+{
+    const int lane = threadIdx.x & 63;
+    const uint32_t done = st[S_DONE], k_rem = st[S_KREM], prefix = st[S_PREFIX], mask = st[S_MASK];
+    if (done) return;
+    uint32_t v[4], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[i] = h(255 - 4 * lane - i);
+        sum += v[i];
+    }
+    uint32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    const uint64_t reach = __builtin_amdgcn_ballot_w64(incl >= k_rem);
+    if (reach == 0) {  // fewer than K members: all of them are candidates
+        if (lane == 0) {
+            st[S_DONE] = 1;
+            st[S_THR] = 0;
+        }
+        return;
+    }
+    if (lane != __builtin_ctzll(reach)) return;
+    uint32_t cum = incl - sum;
+    int found = 255 - 4 * lane;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        if (cum + v[i] >= k_rem) break;
+        cum += v[i];
+        --found;
+    }
+    const uint32_t key = prefix | (uint32_t)found << shift;
+    st[S_PREFIX] = key;
+    st[S_MASK] = mask | 255u << shift;
+    st[S_KREM] = k_rem - cum;
+    if (shift == 0) {
+        const double kth = (double)__uint_as_float(key);
+        const double thr = kth * (1.0 - two_e) / (1.0 + two_e);
+        float tf = (float)thr;
+        if ((double)tf > thr) tf = nextafterf(tf, 0.f);
+        if (!(tf > 0.f)) tf = 0.f;
+        st[S_THR] = __float_as_uint(tf);
+        st[S_DONE] = 1;
+    }
+}
+
+// End of a histogram pass: the last workgroup chooses every segment's digit.
+__device__ __forceinline__ void hist_done(uint32_t *state, const uint32_t *hist, int n_seg, int shift, double two_e,
+                                          uint32_t *ticket)
+{
+    if (!last_block(ticket)) return;
+    for (int sg = threadIdx.x >> 6; sg < n_seg; sg += blockDim.x >> 6) {
+        const uint32_t *h = hist + (int64_t)sg * 256;
+        choose_digit([&](int d) { return __hip_atomic_load(h + d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+                     state + (int64_t)sg * ST, shift, two_e);
+    }
+}
+
+// End of the count: the last workgroup forms the segments' offsets in the
+// candidate list and the toplist lengths.
+__device__ __forceinline__ void count_done(const SelectBufs &b, int n_seg, int k, uint32_t *ticket, uint32_t *err)
+{
+    __shared__ uint64_t part[256];
+    if (!last_block(ticket)) return;
+    const int tid = threadIdx.x, per = (n_seg + 255) / 256;
+    const int s0 = min(tid * per, n_seg), s1 = min(s0 + per, n_seg);
+    auto cnt = [&](int sg) { return __hip_atomic_load(b.cnt + sg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    uint64_t own = 0;
+    for (int sg = s0; sg < s1; ++sg) own += cnt(sg);
+    part[tid] = own;
+    __syncthreads();
+    uint64_t acc = 0;
+    for (int q = 0; q < tid; ++q) acc += part[q];
+    if (tid == 0) b.off[0] = 0;
+    for (int sg = s0; sg < s1; ++sg) {
+        const uint32_t c = cnt(sg);
+        acc += c;
+        b.off[sg + 1] = (uint32_t)(acc < 0xffffffffull ? acc : 0xffffffffull);
+        b.n_out[sg] = (int32_t)min(c, (uint32_t)k);
+    }
+    if (tid == 255 && acc > (uint64_t)b.cap) atomicOr(err, ERR_CAND_OVERFLOW);
 }
 
 // Iterate the templates of a bank as rows: GRID rows are (s, j) pairs of
@@ -62,8 +192,8 @@ __device__ __forceinline__ int seg_at(const int32_t *seg_of, const Rows &rw, int
 
 template <bool LDS>
 __global__ __launch_bounds__(256) void hist_kernel(const float *stats, const int32_t *seg_of,
-                                                   Rows rw, const uint32_t *state,
-                                                   uint32_t *hist, int n_seg, int shift)
+                                                   Rows rw, uint32_t *state, uint32_t *hist, int n_seg,
+                                                   int shift, double two_e, uint32_t *ticket)
 {
     extern __shared__ uint32_t hsh[];
     if (LDS) {
@@ -90,6 +220,7 @@ __global__ __launch_bounds__(256) void hist_kernel(const float *stats, const int
         for (int q = threadIdx.x; q < n_seg * 256; q += blockDim.x)
             if (hsh[q]) atomicAdd(&hist[q], hsh[q]);
     }
+    hist_done(state, hist, n_seg, shift, two_e, ticket);
 }
 
 // Grid banks: a row is one (sky, f1) pair of n_f0 templates and the sub-band
@@ -121,7 +252,8 @@ __device__ __forceinline__ GridCols<COLS> grid_cols(const int32_t *seg_of, const
 // the wave's count.
 template <int COLS>
 __global__ __launch_bounds__(256) void hist_grid_kernel(const float *stats, const int32_t *seg_of, Rows rw,
-                                                        const uint32_t *state, uint32_t *hist, int n_seg, int shift)
+                                                        uint32_t *state, uint32_t *hist, int n_seg, int shift,
+                                                        double two_e, uint32_t *ticket)
 {
     extern __shared__ uint32_t hsh[];
     for (int q = threadIdx.x; q < n_seg * 256; q += blockDim.x) hsh[q] = 0;
@@ -160,13 +292,15 @@ __global__ __launch_bounds__(256) void hist_grid_kernel(const float *stats, cons
     __syncthreads();
     for (int q = threadIdx.x; q < n_seg * 256; q += blockDim.x)
         if (hsh[q]) atomicAdd(&hist[q], hsh[q]);
+    hist_done(state, hist, n_seg, shift, two_e, ticket);
 }
 
 // Candidates per sub-band over grid rows: counts kept per column in
 // registers, added once per thread.
 template <int COLS>
 __global__ __launch_bounds__(256) void count_grid_kernel(const float *stats, const int32_t *seg_of, Rows rw,
-                                                         const uint32_t *state, uint32_t *cnt, int n_seg)
+                                                         const uint32_t *state, SelectBufs b, int n_seg, int k,
+                                                         uint32_t *err)
 {
     extern __shared__ uint32_t csh[];
     for (int q = threadIdx.x; q < n_seg; q += blockDim.x) csh[q] = 0;
@@ -192,7 +326,8 @@ __global__ __launch_bounds__(256) void count_grid_kernel(const float *stats, con
         if (g.on[i] && n[i]) atomicAdd(&csh[g.sg[i]], n[i]);
     __syncthreads();
     for (int q = threadIdx.x; q < n_seg; q += blockDim.x)
-        if (csh[q]) atomicAdd(&cnt[q], csh[q]);
+        if (csh[q]) atomicAdd(&b.cnt[q], csh[q]);
+    count_done(b, n_seg, k, b.ticket + 4 * SEL_TICKET, err);
 }
 
 // Compaction of the candidates over grid rows.
@@ -220,53 +355,13 @@ __global__ __launch_bounds__(256) void scatter_grid_kernel(const float *stats, c
     }
 }
 
-// One thread per segment: choose the digit holding the k_rem-th largest key.
-__global__ void scan_kernel(uint32_t *state, const uint32_t *hist, int n_seg, int shift,
-                            double two_e)
-{
-    const int sg = blockIdx.x * blockDim.x + threadIdx.x;
-    if (sg >= n_seg) return;
-    uint32_t *st = state + (int64_t)sg * ST;
-    if (st[S_DONE]) return;
-    const uint32_t *h = hist + (int64_t)sg * 256;
-    uint32_t k_rem = st[S_KREM], cum = 0;
-    int found = -1;
-    for (int d = 255; d >= 0; --d) {
-        if (cum + h[d] >= k_rem) {
-            found = d;
-            break;
-        }
-        cum += h[d];
-    }
-    if (found < 0) {  // fewer than K members: all of them are candidates
-        st[S_DONE] = 1;
-        st[S_THR] = 0;
-        return;
-    }
-    st[S_PREFIX] |= (uint32_t)found << shift;
-    st[S_MASK] |= 255u << shift;
-    st[S_KREM] = k_rem - cum;
-    if (shift == 0) {
-        const double kth = (double)__uint_as_float(st[S_PREFIX]);
-        const double thr = kth * (1.0 - two_e) / (1.0 + two_e);
-        float tf = (float)thr;
-        if ((double)tf > thr) tf = nextafterf(tf, 0.f);
-        if (!(tf > 0.f)) tf = 0.f;
-        st[S_THR] = __float_as_uint(tf);
-        st[S_DONE] = 1;
-    }
-}
-
-template <bool LDS>
 __global__ __launch_bounds__(256) void count_kernel(const float *stats, const int32_t *seg_of,
-                                                    Rows rw, const uint32_t *state,
-                                                    uint32_t *cnt, int n_seg)
+                                                    Rows rw, const uint32_t *state, SelectBufs b, int n_seg,
+                                                    int k, uint32_t *err)
 {
     extern __shared__ uint32_t csh[];
-    if (LDS) {
-        for (int q = threadIdx.x; q < n_seg; q += blockDim.x) csh[q] = 0;
-        __syncthreads();
-    }
+    for (int q = threadIdx.x; q < n_seg; q += blockDim.x) csh[q] = 0;
+    __syncthreads();
     for (int64_t row = blockIdx.x; row < rw.n_rows; row += gridDim.x) {
         for (int64_t c = threadIdx.x; c < rw.row_len; c += blockDim.x) {
             const int64_t t = row * rw.row_len + c;
@@ -275,28 +370,13 @@ __global__ __launch_bounds__(256) void count_kernel(const float *stats, const in
             if (sg < 0) continue;
             const uint32_t key = __float_as_uint(stats[t]);
             if (key > NAN_KEY || key < state[(int64_t)sg * ST + S_THR]) continue;
-            if (LDS) atomicAdd(&csh[sg], 1u);
-            else atomicAdd(&cnt[sg], 1u);
+            atomicAdd(&csh[sg], 1u);
         }
     }
-    if (LDS) {
-        __syncthreads();
-        for (int q = threadIdx.x; q < n_seg; q += blockDim.x)
-            if (csh[q]) atomicAdd(&cnt[q], csh[q]);
-    }
-}
-
-__global__ void offsets_kernel(const uint32_t *cnt, uint32_t *off, int n_seg, int64_t cap,
-                               uint32_t *err)
-{
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    uint64_t acc = 0;
-    off[0] = 0;
-    for (int s = 0; s < n_seg; ++s) {
-        acc += cnt[s];
-        off[s + 1] = (uint32_t)(acc < 0xffffffffull ? acc : 0xffffffffull);
-    }
-    if (acc > (uint64_t)cap) atomicOr(err, ERR_CAND_OVERFLOW);
+    __syncthreads();
+    for (int q = threadIdx.x; q < n_seg; q += blockDim.x)
+        if (csh[q]) atomicAdd(&b.cnt[q], csh[q]);
+    count_done(b, n_seg, k, b.ticket + 4 * SEL_TICKET, err);
 }
 
 __global__ __launch_bounds__(256) void scatter_kernel(const float *stats, const int32_t *seg_of,
@@ -703,25 +783,84 @@ __global__ __launch_bounds__(256) void rank_kernel(EvalRun r, bool grid, const i
     }
 }
 
-__global__ void n_out_kernel(const uint32_t *cnt, int n_seg, int k, int32_t *n_out)
-{
-    const int sg = blockIdx.x * blockDim.x + threadIdx.x;
-    if (sg < n_seg) n_out[sg] = (int32_t)min(cnt[sg], (uint32_t)k);
-}
+// The whole selection of a small bank (at most SMALL_KEYS x 1024 templates, 32
+// sub-bands) by one workgroup, the keys in registers: radix passes and counts
+// in LDS, then the compaction.  One launch of 18 us in place of six with little
+// work each (10800 templates, one sub-band: 120 us with the passes' launches,
+// fills and scans).  Above these limits the keys leave the registers.
+constexpr int SMALL_KEYS = 16, SMALL_SEG = 32;
 
-__global__ void init_state_kernel(uint32_t *state, uint32_t *cnt, uint32_t *fill, int n_seg,
-                                  int k)
+__global__ __launch_bounds__(1024) void select_small_kernel(const float *stats, const int32_t *seg_of, Rows rw, SelectBufs b,
+                                                            int n_seg, int k, double two_e, uint32_t *err)
 {
-    const int sg = blockIdx.x * blockDim.x + threadIdx.x;
-    if (sg >= n_seg) return;
-    uint32_t *st = state + (int64_t)sg * ST;
-    st[S_PREFIX] = 0;
-    st[S_MASK] = 0;
-    st[S_KREM] = (uint32_t)k;
-    st[S_DONE] = 0;
-    st[S_THR] = 0;
-    cnt[sg] = 0;
-    fill[sg] = 0;
+    extern __shared__ uint32_t hsh[];  // [n_seg][256]
+    __shared__ uint32_t state[SMALL_SEG * ST], cnt[SMALL_SEG], off[SMALL_SEG + 1], fill[SMALL_SEG];
+    const int tid = threadIdx.x, lane = tid & 63;
+    uint32_t key[SMALL_KEYS];
+    int sg[SMALL_KEYS];
+#pragma unroll
+    for (int i = 0; i < SMALL_KEYS; ++i) {
+        const int t = tid + 1024 * i;
+        sg[i] = -1;
+        key[i] = 0;
+        if (t < rw.n_total) {
+            sg[i] = seg_of[rw.grid ? t % (int)rw.row_len : t];
+            key[i] = __float_as_uint(stats[t]);
+            if (key[i] > NAN_KEY) sg[i] = -1;
+        }
+    }
+    if (tid < n_seg) {
+        uint32_t *st = state + tid * ST;
+        st[S_PREFIX] = st[S_MASK] = st[S_DONE] = st[S_THR] = 0;
+        st[S_KREM] = (uint32_t)k;
+        cnt[tid] = fill[tid] = 0;
+    }
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        for (int q = tid; q < n_seg * 256; q += 1024) hsh[q] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < SMALL_KEYS; ++i) {
+            int idx = -1;
+            if (sg[i] >= 0) {
+                const uint32_t *st = state + sg[i] * ST;
+                if (!st[S_DONE] && (key[i] & st[S_MASK]) == st[S_PREFIX]) idx = sg[i] * 256 + (int)((key[i] >> shift) & 255u);
+            }
+            const uint64_t valid = __builtin_amdgcn_ballot_w64(idx >= 0);
+            if (valid == 0) continue;
+            const int first = __builtin_ctzll(valid);
+            const int lead = __builtin_amdgcn_readlane(idx, first);
+            if (__builtin_amdgcn_ballot_w64(idx == lead) == valid) {
+                if (lane == first) atomicAdd(&hsh[lead], (uint32_t)__builtin_popcountll(valid));
+            } else if (idx >= 0) {
+                atomicAdd(&hsh[idx], 1u);
+            }
+        }
+        __syncthreads();
+        for (int q = tid >> 6; q < n_seg; q += 16) choose_digit([&](int d) { return hsh[q * 256 + d]; }, state + q * ST, shift, two_e);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < SMALL_KEYS; ++i)
+        if (sg[i] >= 0 && key[i] >= state[sg[i] * ST + S_THR]) atomicAdd(&cnt[sg[i]], 1u);
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t acc = 0;
+        off[0] = b.off[0] = 0;
+        for (int q = 0; q < n_seg; ++q) {
+            acc += cnt[q];
+            off[q + 1] = b.off[q + 1] = acc;
+            b.cnt[q] = cnt[q];
+            b.n_out[q] = (int32_t)min(cnt[q], (uint32_t)k);
+        }
+        if ((int64_t)acc > b.cap) atomicOr(err, ERR_CAND_OVERFLOW);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < SMALL_KEYS; ++i)
+        if (sg[i] >= 0 && key[i] >= state[sg[i] * ST + S_THR]) {
+            const int64_t pos = (int64_t)off[sg[i]] + atomicAdd(&fill[sg[i]], 1u);
+            if (pos < b.cap) b.cand[pos] = tid + 1024 * i;
+        }
 }
 
 // ---------------------------------------------------------------------------
@@ -874,14 +1013,24 @@ Rows rows_of(const EvalRun &r, bool grid)
         rw.n_rows = (int64_t)r.n_sky * r.n_f1;
         rw.n_total = rw.n_rows * rw.row_len;
     } else {
-        rw.row_len = 4096;
+        // rows of 256 templates and up, so that a bank of 1e5 has some 400
+        rw.row_len = 256 * std::min<int64_t>(std::max<int64_t>(r.n_list / (256 * 1024), 1), 16);
         rw.n_total = r.n_list;
         rw.n_rows = (r.n_list + rw.row_len - 1) / rw.row_len;
     }
     return rw;
 }
 
-unsigned blocks_for(int64_t n_rows) { return (unsigned)std::min<int64_t>(std::max<int64_t>(n_rows, 1), 8192); }
+// Workgroups of a pass: each adds its histogram to the sub-bands' with atomics
+// that are performed one by one, so the fewer the better while the keys fit the
+// caches (grid of 1.6e6: selection 92 us with 512, 118 us with 2048; list of
+// 2e6: 173 us and 151 us); larger banks are read from memory and need them all
+// (4e7: 826 us and 421 us).
+unsigned blocks_for(const Rows &rw)
+{
+    const int64_t most = rw.n_total <= (1 << 21) ? 512 : 2048;
+    return (unsigned)std::min(std::max<int64_t>(rw.n_rows, 1), most);
+}
 
 }  // namespace
 
@@ -904,12 +1053,13 @@ hipError_t launch_labels(const double *max_z, int n_runs, double tau, uint8_t *l
     return hipGetLastError();
 }
 
-hipError_t launch_subband_map(const double *f0, int64_t n, const double *edges, int n_sub,
-                              int32_t *seg, hipStream_t s)
+static bool small_select(const Rows &rw, int n_seg) { return rw.n_total <= 1024 * SMALL_KEYS && n_seg <= SMALL_SEG; }
+
+hipError_t launch_select_prep(const double *f0, int64_t n, const double *edges, int n_seg, int32_t *seg, int k,
+                              const SelectBufs &b, uint32_t *err, hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    const unsigned g = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
-    hipLaunchKernelGGL(subband_map_kernel, dim3(g), dim3(256), 0, s, f0, n, edges, n_sub, seg);
+    const unsigned g = (unsigned)std::min<int64_t>((std::max<int64_t>(n, (int64_t)n_seg * 256) + 255) / 256, 4096);
+    hipLaunchKernelGGL(select_prep_kernel, dim3(g), dim3(256), 0, s, f0, n, edges, n_seg, seg, k, b, err);
     return hipGetLastError();
 }
 
@@ -917,50 +1067,43 @@ hipError_t launch_select(const EvalRun &r, bool grid, int n_seg, int k, double r
                          const SelectBufs &b, hipStream_t s)
 {
     const Rows rw = rows_of(r, grid);
-    const unsigned sg_blocks = (unsigned)((n_seg + 255) / 256);
-    hipLaunchKernelGGL(init_state_kernel, dim3(sg_blocks), dim3(256), 0, s, b.state, b.cnt,
-                       b.fill, n_seg, k);
+    const double two_e = 2.0 * rel_err;
+    if (small_select(rw, n_seg)) {
+        hipLaunchKernelGGL(select_small_kernel, dim3(1), dim3(1024), (size_t)n_seg * 256 * sizeof(uint32_t), s, r.stats,
+                           b.seg_of_f0, rw, b, n_seg, k, two_e, r.err);
+        return hipGetLastError();
+    }
     const bool lds_hist = n_seg * 256 <= 8192;
-    const unsigned nb = blocks_for(rw.n_rows);
+    const unsigned nb = blocks_for(rw);
     // grid rows of at most 2048 templates: column-owning kernels
     const int cols = !grid || !lds_hist ? 0 : rw.row_len <= 1024 ? 4 : rw.row_len <= 2048 ? 8 : 0;
     for (int pass = 0; pass < 4; ++pass) {
         const int shift = 24 - 8 * pass;
-        hipError_t e = launch_fill_u32(b.hist, 0u, (int64_t)n_seg * 256, s);
-        if (e != hipSuccess) return e;
+        uint32_t *hist = b.hist + (int64_t)pass * n_seg * 256, *ticket = b.ticket + pass * SEL_TICKET;
         const size_t hl = (size_t)n_seg * 256 * sizeof(uint32_t);
         if (cols == 4)
             hipLaunchKernelGGL(hist_grid_kernel<4>, dim3(nb), dim3(256), hl, s, r.stats, b.seg_of_f0, rw, b.state,
-                               b.hist, n_seg, shift);
+                               hist, n_seg, shift, two_e, ticket);
         else if (cols == 8)
             hipLaunchKernelGGL(hist_grid_kernel<8>, dim3(nb), dim3(256), hl, s, r.stats, b.seg_of_f0, rw, b.state,
-                               b.hist, n_seg, shift);
+                               hist, n_seg, shift, two_e, ticket);
         else if (lds_hist)
-            hipLaunchKernelGGL(hist_kernel<true>, dim3(nb), dim3(256),
-                               (size_t)n_seg * 256 * sizeof(uint32_t), s, r.stats, b.seg_of_f0,
-                               rw, b.state, b.hist, n_seg, shift);
+            hipLaunchKernelGGL(hist_kernel<true>, dim3(nb), dim3(256), hl, s, r.stats, b.seg_of_f0, rw, b.state, hist,
+                               n_seg, shift, two_e, ticket);
         else
-            hipLaunchKernelGGL(hist_kernel<false>, dim3(nb), dim3(256), 0, s, r.stats,
-                               b.seg_of_f0, rw, b.state, b.hist, n_seg, shift);
-        hipLaunchKernelGGL(scan_kernel, dim3(sg_blocks), dim3(256), 0, s, b.state, b.hist, n_seg,
-                           shift, 2.0 * rel_err);
+            hipLaunchKernelGGL(hist_kernel<false>, dim3(nb), dim3(256), 0, s, r.stats, b.seg_of_f0, rw, b.state, hist,
+                               n_seg, shift, two_e, ticket);
     }
-    const bool lds_cnt = n_seg <= 8192;
+    const size_t cl = (size_t)n_seg * sizeof(uint32_t);
     if (cols == 4)
-        hipLaunchKernelGGL(count_grid_kernel<4>, dim3(nb), dim3(256), (size_t)n_seg * sizeof(uint32_t), s, r.stats,
-                           b.seg_of_f0, rw, b.state, b.cnt, n_seg);
+        hipLaunchKernelGGL(count_grid_kernel<4>, dim3(nb), dim3(256), cl, s, r.stats, b.seg_of_f0, rw, b.state, b, n_seg,
+                           k, r.err);
     else if (cols == 8)
-        hipLaunchKernelGGL(count_grid_kernel<8>, dim3(nb), dim3(256), (size_t)n_seg * sizeof(uint32_t), s, r.stats,
-                           b.seg_of_f0, rw, b.state, b.cnt, n_seg);
-    else if (lds_cnt)
-        hipLaunchKernelGGL(count_kernel<true>, dim3(nb), dim3(256),
-                           (size_t)n_seg * sizeof(uint32_t), s, r.stats, b.seg_of_f0, rw,
-                           b.state, b.cnt, n_seg);
+        hipLaunchKernelGGL(count_grid_kernel<8>, dim3(nb), dim3(256), cl, s, r.stats, b.seg_of_f0, rw, b.state, b, n_seg,
+                           k, r.err);
     else
-        hipLaunchKernelGGL(count_kernel<false>, dim3(nb), dim3(256), 0, s, r.stats, b.seg_of_f0,
-                           rw, b.state, b.cnt, n_seg);
-    hipLaunchKernelGGL(offsets_kernel, dim3(1), dim3(64), 0, s, b.cnt, b.off, n_seg, b.cap,
-                       r.err);
+        hipLaunchKernelGGL(count_kernel, dim3(nb), dim3(256), cl, s, r.stats, b.seg_of_f0, rw, b.state, b, n_seg, k,
+                           r.err);
     if (cols == 4)
         hipLaunchKernelGGL(scatter_grid_kernel<4>, dim3(nb), dim3(256), 0, s, r.stats, b.seg_of_f0, rw, b.state,
                            b.off, b.fill, b.cand, b.cap);
@@ -997,8 +1140,6 @@ hipError_t launch_rescore_rank(const EvalRun &r, bool grid, int n_seg, int k,
     launch_rescore(r, grid, b.cand, b.off, n_seg, b.cap, (int64_t)n_seg * k, b.cand_s64, mom, s);
     hipLaunchKernelGGL(rank_kernel, dim3(1024), dim3(256), 0, s, r, grid, b.cand, b.cand_s64,
                        b.off, n_seg, b.cap, k, b.mu_sigma, mom, b.out);
-    hipLaunchKernelGGL(n_out_kernel, dim3((unsigned)((n_seg + 255) / 256)), dim3(256), 0, s,
-                       b.cnt, n_seg, k, b.n_out);
     return hipGetLastError();
 }
 

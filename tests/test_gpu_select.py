@@ -1,0 +1,62 @@
+"""Toplist selection on both sides of the single-workgroup limits (16384 templates, 32
+sub-bands) and of the histogram's LDS limit, grid and list banks: toplists shorter than,
+equal to and longer than a sub-band's members, many ties, sub-bands without members."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2411_18370_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _ctx(ft, w):
+    import torch
+    c = ft.Context(0, torch.cuda.current_stream().cuda_stream)
+    c.set_sfts(w.n_sft_per_det, w.t_mid, w.t_sft, w.first_bin, w.power, None)
+    c.set_velocities(w.v)
+    return c
+
+
+def _edges(w, n_sub):
+    # the lowest tenth of the band lies outside every sub-band, the last one is above it
+    lo, hi = w.f0[0], max(w.f0[-1], w.f0[0] + 1e-3)
+    e = np.linspace(lo + 0.1 * (hi - lo) * (len(w.f0) > 1), np.nextafter(hi, np.inf), n_sub)
+    return np.concatenate([e, [e[-1] + 1.0]])
+
+
+def _check(c, s64, f0, edges, k):
+    n_sub = len(edges) - 1
+    want = oracle.toplist(s64, oracle.subband(f0, edges), n_sub, k)
+    for s in range(n_sub):
+        top = c.toplist(s, k)
+        assert [t.index for t in top] == list(want[s])
+        assert all(t.s64 == s64[t.index] for t in top)
+
+
+@pytest.mark.parametrize("n_sub,k", [(1, 1), (31, 7), (32, 700), (33, 7), (100, 3)])
+@pytest.mark.parametrize("n", [1, 63, 1025, 16383, 16384, 16385, 40000])
+def test_select_list(ft, n, n_sub, k):
+    w = synth.tiny_bank(40, 1, 1, 40)
+    w.power[:] = np.random.default_rng(2).integers(0, 3, w.power.shape)  # sums tie often
+    rng = np.random.default_rng(n)
+    f0, f1, sky = rng.uniform(w.f0[0], w.f0[-1], n), rng.uniform(-3e-10, 2e-10, n), synth.isotropic_sky(n, rng)
+    s64, bad = oracle.eval_list(w.t_mid, w.t_ref, w.t_sft, w.first_bin, w.power, None, w.v, f0, f1, sky)
+    assert bad == -1
+    edges = _edges(w, n_sub)
+    with _ctx(ft, w) as c:
+        c.eval_templates(f0, f1, sky, w.t_ref, k, edges, kind=ft.FT_BANK_LIST)
+        _check(c, s64, f0, edges, k)
+
+
+@pytest.mark.parametrize("n_sub,k", [(2, 5), (32, 40), (33, 40)])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (128, 2, 64), (127, 3, 43), (129, 2, 64), (1100, 1, 16)])
+def test_select_grid(ft, shape, n_sub, k):
+    w = synth.tiny_bank(shape[0], shape[1], shape[2], 64)
+    s64, bad = oracle.eval_grid(w.t_mid, w.t_ref, w.t_sft, w.first_bin, w.power, None, w.v, w.f0, w.f1, w.sky)
+    assert bad == -1
+    edges = _edges(w, n_sub)
+    f0 = np.tile(w.f0, shape[1] * shape[2])  # templates run f0 fastest
+    with _ctx(ft, w) as c:
+        c.eval_templates(w.f0, w.f1, w.sky, w.t_ref, k, edges)
+        _check(c, s64, f0, edges, k)
