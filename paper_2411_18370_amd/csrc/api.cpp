@@ -3117,7 +3117,8 @@ ft_status ft_mlp_create(ft_ctx c, const float *params, uint64_t seed, const floa
     }
     const int mb = (max_batch + 63) / 64 * 64;
     p->m.max_batch = mb;
-    const size_t act = (size_t)mb * MLP_H;
+    p->m.ld = (int64_t)mb + 128;
+    const size_t act = (size_t)p->m.ld * MLP_H;
     MlpBufs &m = p->m;
     hipError_t e = hipSuccess;
     float **f32s[] = {&m.theta, &m.m, &m.v, &m.grad};
@@ -3127,19 +3128,17 @@ ft_status ft_mlp_create(ft_ctx c, const float *params, uint64_t seed, const floa
     if (e == hipSuccess) e = mlp_alloc(p, &m.w3b, (size_t)MLP_H * MLP_H);
     if (e == hipSuccess) e = mlp_alloc(p, &m.w2t, (size_t)MLP_H * MLP_H);
     if (e == hipSuccess) e = mlp_alloc(p, &m.w3t, (size_t)MLP_H * MLP_H);
-    float **acts[] = {&m.z1, &m.z2, &m.z3, &m.dz1, &m.dz2, &m.dz3};
+    float **acts[] = {&m.dz1, &m.dz2, &m.dz3};
     for (float **q : acts)
         if (e == hipSuccess) e = mlp_alloc(p, q, act);
-    __bf16 **bacts[] = {&m.a1, &m.a2, &m.a3, &m.dz1b, &m.dz2b, &m.dz3b};
+    __bf16 **bacts[] = {&m.a1, &m.a2, &m.a3, &m.dz2b, &m.dz3b};
     for (__bf16 **q : bacts)
         if (e == hipSuccess) e = mlp_alloc(p, q, act);
-    if (e == hipSuccess) e = mlp_alloc(p, &m.x, (size_t)mb * 6);
-    if (e == hipSuccess) e = mlp_alloc(p, &m.logit, (size_t)mb);
+    if (e == hipSuccess) e = mlp_alloc(p, &m.x, (size_t)m.ld * 6);
     if (e == hipSuccess) e = mlp_alloc(p, &m.dlogit, (size_t)mb);
     if (e == hipSuccess) e = mlp_alloc(p, &m.loss, (size_t)1);
     if (e == hipSuccess) e = mlp_alloc(p, &m.lossv, (size_t)mb);
-    if (e == hipSuccess) e = mlp_alloc(p, &m.part, (size_t)(mb / MLP_RED_ROWS + 1) * MLP_RED_VEC);
-    if (e == hipSuccess) e = mlp_alloc(p, &m.wpart, (size_t)2 * MLP_MAX_SLICES * MLP_H * MLP_H);
+    if (e == hipSuccess) e = mlp_alloc(p, &m.bad, (size_t)2);
     if (e != hipSuccess) {
         mlp_free(p);
         delete p;
@@ -3210,20 +3209,19 @@ static ft_status mlp_upload(ft_mlp p, const float *raw, const float *y, int64_t 
     if (e == hipSuccess) e = hipMemcpyAsync(p->d_raw, raw, (size_t)n * 6 * 4, hipMemcpyDefault, c->stream);
     if (e == hipSuccess && y) e = hipMemcpyAsync(p->d_y, y, (size_t)n * 4, hipMemcpyDefault, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "upload MLP data");
-    // validate on the host (amp > 0 for the log feature, finite values, labels in [0, 1])
-    std::vector<float> h;
-    if (fetch(h, raw, (size_t)n * 6) != hipSuccess) return fail(c, FT_E_INVALID, "cannot read inputs");
-    for (int64_t i = 0; i < n; ++i) {
-        if (!(h[(size_t)i * 6] > 0.0f)) return fail(c, FT_E_INVALID, "input %lld: amplitude must be > 0", (long long)i);
-        for (int j = 0; j < 6; ++j)
-            if (!is_finite(h[(size_t)i * 6 + j])) return fail(c, FT_E_INVALID, "inputs must be finite");
+    // amp > 0 for the log feature, finite values, labels in [0, 1]; nothing is
+    // changed or written for the caller before this is known
+    uint64_t bad[2];
+    e = launch_fill_u32((uint32_t *)p->m.bad, 0xffffffffu, 4, c->stream);
+    if (e == hipSuccess) e = mlp_check(p->d_raw, y ? p->d_y : nullptr, n, p->m.bad, c->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(bad, p->m.bad, sizeof bad, hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "check MLP data");
+    if (bad[0] != ~0ull) {
+        if (bad[0] & 1) return fail(c, FT_E_INVALID, "inputs must be finite");
+        return fail(c, FT_E_INVALID, "input %lld: amplitude must be > 0", (long long)(bad[0] >> 1));
     }
-    if (y) {
-        std::vector<float> hy;
-        if (fetch(hy, y, (size_t)n) != hipSuccess) return fail(c, FT_E_INVALID, "cannot read labels");
-        for (float v : hy)
-            if (!(v >= 0.0f && v <= 1.0f)) return fail(c, FT_E_INVALID, "labels must lie in [0, 1]");
-    }
+    if (bad[1] == 0) return fail(c, FT_E_INVALID, "labels must lie in [0, 1]");
     return FT_OK;
 }
 
@@ -3236,14 +3234,11 @@ ft_status ft_mlp_predict(ft_mlp p, const float *raw, int64_t n, float *prob)
     ft_status st = mlp_upload(p, raw, nullptr, n);
     if (st != FT_OK) return st;
     hipError_t e = ensure(&p->d_prob, &p->cap_prob, (size_t)n);
-    for (int64_t b0 = 0; b0 < n && e == hipSuccess; b0 += p->m.max_batch) {
-        const int bsz = (int)std::min<int64_t>(p->m.max_batch, n - b0);
-        MlpConst cst = p->cst;
-        cst.base = b0;
-        cst.n_total = n;
-        cst.perm_a = 0;
-        e = mlp_forward(p->m, p->d_raw, nullptr, cst, bsz, p->d_prob + b0, c->stream);
-    }
+    MlpConst cst = p->cst;
+    cst.base = 0;
+    cst.n_total = n;
+    cst.perm_a = 0;
+    if (e == hipSuccess) e = mlp_predict(p->m, p->d_raw, cst, (int)n, p->d_prob, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(prob, p->d_prob, (size_t)n * 4, hipMemcpyDefault, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "predict");
@@ -3264,8 +3259,7 @@ ft_status ft_mlp_loss_grad(ft_mlp p, const float *raw, const float *y, int32_t n
     cst.n_total = n;
     cst.perm_a = 0;
     hipError_t e = launch_fill_u32((uint32_t *)p->m.loss, 0u, 1, c->stream);
-    if (e == hipSuccess) e = mlp_forward(p->m, p->d_raw, p->d_y, cst, n, nullptr, c->stream);
-    if (e == hipSuccess) e = mlp_backward(p->m, n, nullptr, c->stream);
+    if (e == hipSuccess) e = mlp_step(p->m, p->d_raw, p->d_y, cst, n, nullptr, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(loss, p->m.loss, 4, hipMemcpyDefault, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(grad, p->m.grad, (size_t)MLP_N_PARAMS * 4, hipMemcpyDefault, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -3300,9 +3294,8 @@ ft_status ft_mlp_train(ft_mlp p, const float *raw, const float *y, int64_t n, in
             cst.n_total = n;
             cst.perm_a = n > 1 ? a : 0;
             cst.perm_c = b;
-            e = mlp_forward(p->m, p->d_raw, p->d_y, cst, bsz, nullptr, c->stream);
             const MlpAdamStep adam{lr, ++p->step};
-            if (e == hipSuccess) e = mlp_backward(p->m, bsz, &adam, c->stream);
+            e = mlp_step(p->m, p->d_raw, p->d_y, cst, bsz, &adam, c->stream);
             ++n_batches;
         }
         if (epoch_loss && e == hipSuccess) {
