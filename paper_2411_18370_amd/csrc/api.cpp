@@ -3293,7 +3293,8 @@ ft_status ft_mlp_train(ft_mlp p, const float *raw, const float *y, int64_t n, in
             cst.base = b0;
             cst.n_total = n;
             cst.perm_a = n > 1 ? a : 0;
-            cst.perm_c = b;
+            cst.start = (a * (uint64_t)b0 + b) % (uint64_t)n;
+            cst.inv_total = 1.0 / (double)n;
             const MlpAdamStep adam{lr, ++p->step};
             e = mlp_step(p->m, p->d_raw, p->d_y, cst, bsz, &adam, c->stream);
             ++n_batches;

@@ -518,7 +518,9 @@ struct MlpConst {
     float shift[6], scale[6];  // feature standardisation
     int64_t base;              // first sample of the batch (in permuted order)
     int64_t n_total;           // samples in the data set
-    uint64_t perm_a, perm_c;   // sample = (perm_a * i + perm_c) mod n_total (perm_a = 0: i)
+    uint64_t perm_a;           // sample = (perm_a * (i - base) + start) mod n_total (perm_a = 0: i)
+    uint64_t start;            // sample of i = base
+    double inv_total;          // 1 / n_total
 };
 
 // Gradient reductions: column sums (every entry that is not a 256 x 256 weight)
@@ -531,14 +533,14 @@ struct MlpBufs {
     float *theta, *m, *v, *grad;
     __bf16 *w2b, *w3b;  // BF16 copies of W2, W3 in the MFMA operand's order
     __bf16 *w2t, *w3t;  // and of their transposes
-    // the current batch, a row of ld entries per feature or unit
+    // the current batch, ld entries per feature or unit
     float *x, *dz1, *dz2, *dz3;
     __bf16 *a1, *a2, *a3, *dz2b, *dz3b;
     float *dlogit, *lossv;  // [max_batch]
     float *loss;            // sum of the batches' mean losses
     uint64_t *bad;          // [2] of mlp_check
     int max_batch;          // multiple of 64
-    int64_t ld;             // max_batch + 128: the rows' starts spread over the memory channels
+    int64_t ld;             // max_batch + 128: arrays start on different memory channels
 };
 struct MlpAdamStep {
     float lr;
