@@ -335,22 +335,68 @@ double model_cost(int id, double n_f0, double n_f1)
     return f0w * f1w * ops;
 }
 
-int choose_tile(int64_t n_f0, int64_t n_f1, bool uniform)
+// Measured time of a round of workgroups of a tile, per SFT: first + (q - 1)
+// more nanoseconds with q workgroups on every CU, up to `most` of them (more
+// wait for the next round).  From grids of 0.25 to 12 workgroups per CU, 3000
+// SFTs at 100 Hz; windows at 400 Hz or of 800 SFTs change it by a few percent.
+struct TileTime {
+    int id;
+    double first, more;
+    int most;
+};
+const TileTime kTileTime[] = {
+    {17, 446, 64, 4}, {22, 397, 54, 4}, {28, 342, 45, 4}, {29, 286, 42, 4},  // L5, J 4 3 2 1, K8 O4
+    {23, 346, 48, 5}, {30, 320, 46, 5}, {31, 267, 44, 5}, {32, 238, 42, 5},  // L3, J 4 3 2 1, K8 O5
+    {20, 430, 62, 4}, {7, 372, 49, 3},  {2, 290, 41, 3},  {15, 273, 34, 3},  // L3 J6, L3 J6, L3 J4, L3 J3
+    {0, 174, 17, 6},  {14, 244, 50, 6}, {1, 266, 60, 6},                     // L1, J 1 3 4
+};
+
+// What a grid launch of tile t is expected to take (ns) with rows of bps
+// summation blocks (bps = n_blk: not split): rounds of workgroups, each row
+// with the start of its pipeline (6 SFTs); a split adds its block sums, written
+// and read, and their launch.
+double grid_cost(const TileTime &t, int most, int64_t n0, int64_t n1, int64_t ns, int64_t n_sft, int64_t bps)
 {
-    if (!uniform || n_f0 < 96) return n_f1 >= 4 ? 1 : 0;
-    // fewest wasted lanes x operations; on ties the first listed (SFT stages
-    // of 8 before 16: more workgroups fit in LDS)
-    const int cands[] = {8, 3, 2, 4, 5, 7, 6};
-    double best = 1e30;
-    int best_id = 8;
-    for (int id : cands) {
-        const double cost = model_cost(id, (double)n_f0, (double)n_f1);
-        if (cost < best - 1e-9) {
-            best = cost;
-            best_id = id;
+    const TileCfg &cfg = tile_cfg(t.id);
+    const int64_t n_blk = (n_sft + SUM_BLOCK - 1) / SUM_BLOCK, rows = (n_blk + bps - 1) / bps;
+    const int64_t wgs = (n0 + 64 * cfg.L - 1) / (64 * cfg.L) * ((n1 + cfg.JT - 1) / cfg.JT) * ((ns + cfg.NW - 1) / cfg.NW) * rows;
+    const int64_t q = (wgs + 255) / 256;
+    const double full = 0.95 * (t.first + t.more * (most - 1));
+    const double round = q <= most ? t.first + t.more * (double)(q - 1)
+                                   : full * (double)(q / most) + (q % most ? t.first + t.more * (double)(q % most - 1) : 0.0);
+    const double sfts = (double)std::min<int64_t>(n_sft, bps * SUM_BLOCK) + 6.0;
+    const double sums = rows > 1 ? (double)(n0 * n1 * ns) * (double)n_blk * 1e-3 + 6e3 : 0.0;
+    return round * sfts + sums;
+}
+
+// The block sums of a split grid take n_templates ceil(N / SUM_BLOCK) floats of
+// context memory, at most 1 GiB (larger grids fill the GPU unsplit).
+constexpr double kGridSplitBytes = (double)(1ull << 30);
+
+const TileTime *tile_time(int id)
+{
+    for (const TileTime &t : kTileTime)
+        if (t.id == id) return &t;
+    return nullptr;
+}
+
+// Summation blocks per row of the split of least cost, n_blk where not
+// splitting is best; cost is set to it.  Splitting at 64 workgroups and 3000
+// SFTs: 1402 us unsplit, 165 us in rows of one block (L5 J4).
+int64_t grid_split(const TileTime &t, int most, bool may_split, int64_t n0, int64_t n1, int64_t ns, int64_t n_sft, double &cost)
+{
+    const int64_t n_blk = (n_sft + SUM_BLOCK - 1) / SUM_BLOCK;
+    int64_t best = std::max<int64_t>(n_blk, 1);
+    cost = grid_cost(t, most, n0, n1, ns, n_sft, best);
+    if (!may_split || (double)(n0 * n1 * ns) * (double)n_blk * 4.0 > kGridSplitBytes) return best;
+    for (int64_t bps = n_blk - 1; bps >= 1 && (n_blk + bps - 1) / bps <= 32768; --bps) {
+        const double c = grid_cost(t, most, n0, n1, ns, n_sft, bps);
+        if (c < 0.95 * cost) {
+            cost = c;
+            best = bps;
         }
     }
-    return best_id;
+    return best;
 }
 
 // Tiles the autotuner times: eligible (run-length tiles need the guard), cost
@@ -1318,6 +1364,80 @@ static std::vector<int64_t> plain_tune_key(ft_ctx c, int64_t n0, int64_t n1, int
     return {0, n0, n1, (int64_t)c->n_sft, (int64_t)floor_log2(ns), (int64_t)dop, uniform ? 1 : 0};
 }
 
+// A grid evaluation: the tile (its window; tile -1: direct kernel), the tile of
+// the last f1 values (tile -1: none) and the summation blocks per row of a split
+// (0: none).  Every choice gives the same bits.
+struct GridPlan {
+    WindowPlan main, tail;
+    int64_t bps = 0;
+    double cost = 1e300;
+};
+
+// Plans a grid with `tile`: when JT does not divide n_f1, the last n_f1 % JT
+// values go to the tile of the same shape with that JT (no idle f1 slots).
+static GridPlan plan_grid_tile(ft_ctx c, const EvalRun &run, int tile, double dt_absmax, bool may_split)
+{
+    const int64_t n0 = run.n_f0, n1 = run.n_f1, ns = run.n_sky;
+    const bool sky = run.sky_norm != nullptr;
+    GridPlan p;
+    const auto window = [&](const double *f1, int64_t n, int t) {
+        return plan_window(c->f0_h.data(), n0, f1, n, c->sky_tile_h.data(), ns, dt_absmax, c->vmax, c->t_sft, t);
+    };
+    p.main = window(c->f1_h.data(), n1, tile);
+    if (p.main.tile < 0) return p;
+    const int jt = tile_cfg(tile).JT, rem = (int)(n1 % jt);
+    const int comp = rem && n1 > jt ? tile_companion(tile, rem) : -1;
+    if (comp >= 0 && (!sky || tile_has_sky_weights(comp))) p.tail = window(c->f1_h.data() + (n1 - rem), rem, comp);
+    const TileTime *t = tile_time(tile);
+    if (!t) return p;
+    // workgroups of the tile that a CU's 160 KB hold
+    const auto fits = [](const TileTime &tt, const WindowPlan &w) {
+        const size_t lds = tile_static_lds(tt.id) + (size_t)2 * tile_cfg(tt.id).KS * w.wtp * sizeof(float);
+        return (int)std::max<size_t>(1, std::min<size_t>((size_t)tt.most, (size_t)160 * 1024 / lds));
+    };
+    const TileTime *tc = p.tail.tile >= 0 ? tile_time(p.tail.tile) : nullptr;
+    const int64_t n_main = p.tail.tile >= 0 ? n1 - rem : n1;
+    may_split = may_split && tile_has_split(tile, sky) && (p.tail.tile < 0 || (tc && tile_has_split(p.tail.tile, sky)));
+    p.bps = grid_split(*t, fits(*t, p.main), may_split, n0, n_main, ns, run.n_sft, p.cost);
+    const int64_t n_blk = (run.n_sft + SUM_BLOCK - 1) / SUM_BLOCK;
+    if (tc) p.cost += grid_cost(*tc, fits(*tc, p.tail), n0, rem, ns, run.n_sft, std::max<int64_t>(p.bps, 1));
+    if (p.bps >= n_blk || (double)(n0 * n1 * ns) * (double)n_blk * 4.0 > kGridSplitBytes) p.bps = 0;
+    return p;
+}
+
+// The library's choice: the tile and split of least expected time whose window
+// fits in LDS.  Run-length tiles need the guard (uniform f0).  Sky-dependent
+// weights take the run of 5 f0 with as many f1 as the bank has, up to 4 (a
+// split fills the GPU; idle f1 slots cost as much as used ones: 437 x 3 x 1201
+// templates, 3000 SFTs: 2.84 ms in J4 unsplit, 1.0 ms in J3 split).
+static GridPlan choose_grid(ft_ctx c, const EvalRun &run, double dt_absmax, bool uniform, bool may_split)
+{
+    const bool sky = run.sky_norm != nullptr;
+    std::vector<std::pair<double, int>> cands;
+    for (const TileTime &t : kTileTime) {
+        const int jt = tile_cfg(t.id).JT;
+        const bool run_tile = tile_cfg(t.id).L > 1;
+        if (run_tile && !uniform) continue;
+        if (sky && (!tile_has_sky_weights(t.id) || (uniform && (!run_tile || jt != std::min(run.n_f1, 4))))) continue;
+        const int64_t n1 = run.n_f1, rem = n1 > jt ? n1 % jt : 0;
+        const int comp = rem ? tile_companion(t.id, (int)rem) : -1;
+        const TileTime *tc = comp >= 0 ? tile_time(comp) : nullptr;
+        double cost;
+        const int64_t bps = grid_split(t, t.most, may_split && tile_has_split(t.id, sky), run.n_f0, tc ? n1 - rem : n1,
+                                       run.n_sky, run.n_sft, cost);
+        if (tc) cost += grid_cost(*tc, tc->most, run.n_f0, rem, run.n_sky, run.n_sft, bps);
+        cands.push_back({cost, t.id});
+    }
+    std::sort(cands.begin(), cands.end());
+    GridPlan best;
+    for (const auto &cd : cands) {
+        if (cd.first >= best.cost) break;  // a window only ever adds to it
+        const GridPlan p = plan_grid_tile(c, run, cd.second, dt_absmax, may_split);
+        if (p.main.tile >= 0 && p.cost < best.cost) best = p;
+    }
+    return best;
+}
+
 static hipError_t launch_grid(const EvalRun &run, int tile, const WindowPlan *tail, hipStream_t s);
 
 // Times the candidate tiles on a sample of the Doppler-ordered sky (blocks
@@ -1504,10 +1624,8 @@ static ft_status apply_stat_weights(ft_ctx c, const ft_eval_opts *opts, bool gri
     return FT_OK;
 }
 
-// Tiles with a sky-weighted form: the run tile for uniform f0 grids and the
-// single-f0 tile otherwise.
-constexpr int kSkyTileRun = 17;  // L5_J4_W4_K8_O4
-constexpr int kSkyTileOne = 1;   // L1_J4_W4_K16
+// The tile for f0 grids that are not uniform where a run-length one was asked for.
+constexpr int kSkyTileOne = 1;  // L1_J4_W4_K16
 
 ft_status ft_eval_templates(ft_ctx c, const ft_bank *bank, double t_ref, const ft_eval_opts *opts,
                             float *stats)
@@ -1531,22 +1649,19 @@ ft_status ft_eval_templates(ft_ctx c, const ft_bank *bank, double t_ref, const f
 
     // tile choice and LDS window for the grid kernel
     int tile = -1;
-    WindowPlan tail;  // the tile of the last f1 values (tile -1: none)
+    GridPlan gp;
     if (grid) {
         const int64_t n0 = bank->n_f0, n1 = bank->n_f1, ns = bank->n_sky;
-        const bool uniform = run.eta < 1e-4;
+        const bool uniform = run.eta < 1e-4, may_split = run.sum_mode == FT_SUM_BLOCKED;
         double dt_absmax = 0.0;
         for (double t : c->t_mid_h) dt_absmax = std::max(dt_absmax, std::fabs(t - t_ref));
-        if (sky) {
-            if (opts->tile > 0 && !tile_has_sky_weights(opts->tile - 1))
+        if (opts->tile > 0) {
+            if (sky && !tile_has_sky_weights(opts->tile - 1))
                 return fail(c, FT_E_INVALID, "tile %d has no form with sky-dependent weights", opts->tile);
-            tile = opts->tile > 0 ? opts->tile - 1 : uniform ? kSkyTileRun : kSkyTileOne;
-        } else if (opts->tile > 0) {
             tile = opts->tile - 1;
-        } else {
+        } else if (!sky) {
             const std::vector<int64_t> key = plain_tune_key(c, n0, n1, ns, uniform);
             const auto it = c->tune_cache.find(key);
-            tile = -1;
             if (it != c->tune_cache.end()) {
                 tile = it->second;
             } else if (opts->tile == FT_TILE_TUNE) {
@@ -1554,12 +1669,12 @@ ft_status ft_eval_templates(ft_ctx c, const ft_bank *bank, double t_ref, const f
                 if (st != FT_OK) return st;
                 if (tile >= 0) c->tune_cache[key] = tile;
             }
-            if (tile < 0) tile = choose_tile(n0, n1, uniform);
         }
-        if (tile_cfg(tile).L > 1 && !uniform) tile = kSkyTileOne;
-        const WindowPlan wp = plan_window(c->f0_h.data(), n0, c->f1_h.data(), n1, c->sky_tile_h.data(), ns,
-                                          dt_absmax, c->vmax, c->t_sft, tile);
-        tile = wp.tile;  // -1: the window does not fit in LDS, use the direct kernel
+        if (tile >= 0 && tile_cfg(tile).L > 1 && !uniform) tile = kSkyTileOne;
+        gp = tile >= 0 ? plan_grid_tile(c, run, tile, dt_absmax, may_split)
+                       : choose_grid(c, run, dt_absmax, uniform, may_split);
+        const WindowPlan &wp = gp.main;
+        tile = wp.tile;  // -1: no window fits in LDS, use the direct kernel
         run.wt = wp.wt;
         run.wtp = wp.wtp;
         run.tiles_f0 = wp.tiles_f0;
@@ -1567,21 +1682,20 @@ ft_status ft_eval_templates(ft_ctx c, const ft_bank *bank, double t_ref, const f
         run.tiles_sky = wp.tiles_sky;
         if ((int64_t)run.tiles_f0 * run.tiles_f1 * run.tiles_sky >= 0x7fffffffLL)
             return fail(c, FT_E_UNSUPPORTED, "too many tiles");
-        // When JT does not divide n_f1, the last rem f1 values go to the tile of
-        // the same shape with JT = rem (no idle f1 slots); every tile shape gives
-        // the same bits.
-        if (tile >= 0) {
-            const int jt = tile_cfg(tile).JT;
-            const int rem = (int)(n1 % jt);
-            const int comp = rem && n1 > jt ? tile_companion(tile, rem) : -1;
-            if (comp >= 0 && (!run.sky_norm || tile_has_sky_weights(comp)))
-                tail = plan_window(c->f0_h.data(), n0, c->f1_h.data() + (n1 - rem), rem, c->sky_tile_h.data(), ns,
-                                   dt_absmax, c->vmax, c->t_sft, comp);
+        if (tile >= 0 && gp.bps > 0) {
+            const size_t n_blk = (size_t)((run.n_sft + SUM_BLOCK - 1) / SUM_BLOCK);
+            if (ensure(&c->d_bsum, &c->cap_bsum, n_blk * (size_t)n_t) == hipSuccess) {
+                run.seg_blocks = (int32_t)gp.bps;
+                run.bsum = c->d_bsum;
+                run.bsum_n = n_t;
+            } else {
+                (void)hipGetLastError();  // no room: not split
+            }
         }
     }
 
     return launch_eval_select(c, run, grid, tile, n_t, grid ? bank->n_f0 : n_t, opts, edges, stats,
-                              tail.tile >= 0 ? &tail : nullptr);
+                              gp.tail.tile >= 0 ? &gp.tail : nullptr);
 }
 
 // Launch sequence of an evaluation: clear flags, map sub-bands, evaluate,
@@ -1734,12 +1848,22 @@ static hipError_t eval_binary(ft_ctx c, const EvalRun &run, const BankPlan &pl)
     return pl.width > 0 ? launch_eval_bank(run, pl, bsum, n_seg, c->stream) : launch_eval_binary(run, bsum, n_seg, c->stream);
 }
 
+// The statistics of a split grid from its block sums.
+static hipError_t grid_block_sum(const EvalRun &run, hipStream_t s)
+{
+    if (run.seg_blocks == 0) return hipSuccess;
+    return launch_binary_block_sum(run.bsum, run.bsum_n, (run.n_sft + SUM_BLOCK - 1) / SUM_BLOCK, run.stats, s);
+}
+
 // Grid launch of `tile`; with `tail`, the f1 values past the last multiple of
 // JT go to the tail's tile (a view of the same bank: f1 and stats shifted, the
 // output rows keeping the whole bank's f1 count).
 static hipError_t launch_grid(const EvalRun &run, int tile, const WindowPlan *tail, hipStream_t s)
 {
-    if (!tail) return launch_eval_grid(run, tile_cfg(tile), s);
+    if (!tail) {
+        const hipError_t e = launch_eval_grid(run, tile_cfg(tile), s);
+        return e == hipSuccess ? grid_block_sum(run, s) : e;
+    }
     const TileCfg &cfg = tile_cfg(tile), &tcfg = tile_cfg(tail->tile);
     const int n_main = run.n_f1 - tcfg.JT;
     EvalRun a = run;
@@ -1751,6 +1875,7 @@ static hipError_t launch_grid(const EvalRun &run, int tile, const WindowPlan *ta
     b.n_f1 = tcfg.JT;
     b.n_f1_stride = run.n_f1;
     b.stats = run.stats + (int64_t)n_main * run.n_f0;
+    if (b.bsum) b.bsum += (int64_t)n_main * run.n_f0;
     b.wt = tail->wt;
     b.wtp = tail->wtp;
     b.tiles_f0 = tail->tiles_f0;
@@ -1758,7 +1883,7 @@ static hipError_t launch_grid(const EvalRun &run, int tile, const WindowPlan *ta
     b.tiles_sky = tail->tiles_sky;
     hipError_t e = launch_eval_grid(a, cfg, s);
     if (e == hipSuccess) e = launch_eval_grid(b, tcfg, s);
-    return e;
+    return e == hipSuccess ? grid_block_sum(run, s) : e;
 }
 
 static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile, int64_t n_t, int64_t n_seg_map,
@@ -3210,7 +3335,7 @@ static ft_status mlp_upload(ft_mlp p, const float *raw, const float *y, int64_t 
     if (e == hipSuccess && y) e = hipMemcpyAsync(p->d_y, y, (size_t)n * 4, hipMemcpyDefault, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "upload MLP data");
     // amp > 0 for the log feature, finite values, labels in [0, 1]; nothing is
-    // changed or written for the caller before this is known
+    // changed or written for the caller before this is known.
     uint64_t bad[2];
     e = launch_fill_u32((uint32_t *)p->m.bad, 0xffffffffu, 4, c->stream);
     if (e == hipSuccess) e = mlp_check(p->d_raw, y ? p->d_y : nullptr, n, p->m.bad, c->stream);

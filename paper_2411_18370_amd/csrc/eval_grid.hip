@@ -496,10 +496,31 @@ __device__ __forceinline__ void accumulate_pipelined(const EvalRun &r, const Sta
     }
 }
 
-template <int L, int JT, int NW, int KS, bool PIPE, bool SKYW>
+// w(t, jl, l) for every template of the lane: t its position (original sky order).
+template <int L, int JT, typename W>
+__device__ __forceinline__ void write_tile(const EvalRun &r, const TileGeom &tg, int wave, int i0, W w)
+{
+    const int s = tg.s_base + wave;
+    if (s > tg.s_last) return;
+    const int64_t s_orig = r.sky_perm ? r.sky_perm[s] : s;
+#pragma unroll
+    for (int jl = 0; jl < JT; ++jl) {
+        const int j = tg.j_base + jl;
+        if (j > tg.j_last) continue;
+        const int64_t row = (s_orig * (r.n_f1_stride ? r.n_f1_stride : r.n_f1) + j) * r.n_f0;
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            const int i = i0 + l;
+            if (i <= tg.i_last) w(row + i, jl, l);
+        }
+    }
+}
+
+template <int L, int JT, int NW, int KS, bool PIPE, bool SKYW, bool SPLIT = false>
 __device__ __forceinline__ void eval_tile(const EvalRun &r, int64_t b, float *win,
                                           Shared<L, JT, NW, KS> &sh)
 {
+    static_assert(!(PIPE && SPLIT), "the pipelined form flushes its blocks itself");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nthreads = 64 * NW;
@@ -641,7 +662,16 @@ __device__ __forceinline__ void eval_tile(const EvalRun &r, int64_t b, float *wi
             }
         }
         // blocks of SUM_BLOCK SFTs end with a stage (KS divides SUM_BLOCK)
-        if (!(L > 1 && PIPE) && r.sum_mode == FT_SUM_BLOCKED && ((k0 + ks) & (SUM_BLOCK - 1)) == 0) {
+        if (SPLIT) {
+            if (((k0 + ks) & (SUM_BLOCK - 1)) == 0 || p + 1 == n_stage) {
+                float *out = r.bsum + (int64_t)(k0 / SUM_BLOCK) * r.bsum_n;
+                write_tile<L, JT>(r, tg, wave, i0, [&](int64_t t, int jl, int l) { out[t] = acc[jl][l]; });
+#pragma unroll
+                for (int j = 0; j < JT; ++j)
+#pragma unroll
+                    for (int l = 0; l < L; ++l) acc[j][l] = 0.f;
+            }
+        } else if (!(L > 1 && PIPE) && r.sum_mode == FT_SUM_BLOCKED && ((k0 + ks) & (SUM_BLOCK - 1)) == 0) {
 #pragma unroll
             for (int j = 0; j < JT; ++j)
 #pragma unroll
@@ -654,21 +684,9 @@ __device__ __forceinline__ void eval_tile(const EvalRun &r, int64_t b, float *wi
         __syncthreads();
     }
 
-    // --- epilogue: write the statistic (original sky order) ----------------
-    const int s = tg.s_base + wave;
-    if (s > tg.s_last) return;
-    const int64_t s_orig = r.sky_perm ? r.sky_perm[s] : s;
-#pragma unroll
-    for (int jl = 0; jl < JT; ++jl) {
-        const int j = tg.j_base + jl;
-        if (j > tg.j_last) continue;
-        const int64_t row = (s_orig * (r.n_f1_stride ? r.n_f1_stride : r.n_f1) + j) * r.n_f0;
-#pragma unroll
-        for (int l = 0; l < L; ++l) {
-            const int i = i0 + l;
-            if (i <= tg.i_last) r.stats[row + i] = (float)(tot[jl][l] + (double)acc[jl][l]);
-        }
-    }
+    if (!SPLIT)
+        write_tile<L, JT>(r, tg, wave, i0,
+                          [&](int64_t t, int jl, int l) { r.stats[t] = (float)(tot[jl][l] + (double)acc[jl][l]); });
 }
 
 // Grid-stride over tiles.  Blocks are dispatched round-robin over the 8 XCDs
@@ -679,16 +697,30 @@ __device__ __forceinline__ void eval_tile(const EvalRun &r, int64_t b, float *wi
 // launch-bounds argument: a register budget of 512 / OCC VGPRs per lane; with
 // four-wave workgroups that is OCC workgroups per CU); 0 leaves the
 // allocation free.
-template <int L, int JT, int NW, int KS, int OCC, bool PIPE, bool SKYW>
+//
+// SPLIT: workgroup row y takes the summation blocks [y seg_blocks, (y + 1)
+// seg_blocks) -- a view of the run with its SFTs shifted -- and leaves FP32
+// block sums, which binary_block_sum_kernel then adds in block order in FP64:
+// the same operations in the same order as unsplit.
+template <int L, int JT, int NW, int KS, int OCC, bool PIPE, bool SKYW, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, OCC > 0 ? OCC : 1) void eval_grid_kernel(EvalRun r)
 {
     extern __shared__ float win[];  // [2][KS][wtp]
     __shared__ Shared<L, JT, NW, KS> sh;
+    if (SPLIT) {
+        const int b0 = (int)blockIdx.y * r.seg_blocks, k0 = b0 * SUM_BLOCK;
+        r.power_w += (int64_t)k0 * r.n_bins;
+        r.v += 3 * (int64_t)k0;
+        r.dt += k0;
+        if (SKYW) r.arms += 6 * (int64_t)k0;
+        r.bsum += b0 * r.bsum_n;
+        r.n_sft = min(r.n_sft - k0, r.seg_blocks * SUM_BLOCK);
+    }
     const int64_t nt = (int64_t)r.tiles_f0 * r.tiles_f1 * r.tiles_sky;
     const int64_t full = nt - (nt & 7);
     for (int64_t b0 = blockIdx.x; b0 < nt; b0 += gridDim.x) {
         const int64_t b = b0 < full ? (b0 & 7) * (full >> 3) + (b0 >> 3) : b0;
-        eval_tile<L, JT, NW, KS, PIPE, SKYW>(r, b, win, sh);
+        eval_tile<L, JT, NW, KS, PIPE, SKYW, SPLIT>(r, b, win, sh);
     }
 }
 
@@ -727,18 +759,19 @@ hipError_t launch_batch_t(const EvalRun *runs, const int2 *items, int n_items, i
     return hipGetLastError();
 }
 
-template <int L, int JT, int NW, int KS, int OCC, bool PIPE, bool SKYW = false>
+template <int L, int JT, int NW, int KS, int OCC, bool PIPE, bool SKYW = false, bool SPLIT = false>
 hipError_t launch_t(const EvalRun &r, hipStream_t s)
 {
     const int64_t nt = (int64_t)r.tiles_f0 * r.tiles_f1 * r.tiles_sky;
     if (nt <= 0) return hipSuccess;
     const size_t lds = (size_t)2 * KS * r.wtp * sizeof(float);
     // at most 2^22 blocks (work-items stay below 2^32); a multiple of 8 keeps
-    // every block's tiles on one XCD
-    int64_t grid = nt < (1 << 22) ? nt : (1 << 22);
-    if (grid > 8) grid &= ~(int64_t)7;
-    hipLaunchKernelGGL((eval_grid_kernel<L, JT, NW, KS, OCC, PIPE, SKYW>), dim3((unsigned)grid), dim3(64 * NW),
-                       lds, s, r);
+    // every block's tiles on one XCD (rounded up: a block with two tiles would
+    // take twice the time of a small grid's others)
+    const int64_t grid = nt < (1 << 22) ? (nt + 7) / 8 * 8 : (1 << 22);
+    const int n_blk = (r.n_sft + SUM_BLOCK - 1) / SUM_BLOCK;
+    const dim3 g((unsigned)grid, SPLIT ? (unsigned)((n_blk + r.seg_blocks - 1) / r.seg_blocks) : 1u);
+    hipLaunchKernelGGL((eval_grid_kernel<L, JT, NW, KS, OCC, PIPE, SKYW, SPLIT>), g, dim3(64 * NW), lds, s, r);
     return hipGetLastError();
 }
 
@@ -820,6 +853,7 @@ struct TileEntry {
     size_t static_lds;
     ProbeLauncher probe_fn;
     Launcher sky_fn;  // sky-dependent weights, or nullptr (no such form of the tile)
+    Launcher split_fn = nullptr, sky_split_fn = nullptr;  // split over SFT blocks, likewise
 };
 
 #define FT_TILE_X(id, L, JT, NW, KS, SKY)                                                          \
@@ -831,6 +865,13 @@ struct TileEntry {
      &launch_batch_t<L, JT, NW, KS, OCC, false>, sizeof(Shared<L, JT, NW, KS>),                     \
      &launch_probe_t<L, JT, NW, KS, OCC>, SKY}
 #define FT_TILE_O(id, L, JT, NW, KS, OCC) FT_TILE_OX(id, L, JT, NW, KS, OCC, nullptr)
+// with the split forms; SKY: 1 with the forms for sky-dependent weights
+#define FT_TILE_S(id, L, JT, NW, KS, OCC, NAME, SKY)                                                    \
+    {{id, NAME, L, JT, NW, KS}, &launch_t<L, JT, NW, KS, OCC, false>,                                   \
+     &launch_batch_t<L, JT, NW, KS, OCC, false>, sizeof(Shared<L, JT, NW, KS>),                     \
+     &launch_probe_t<L, JT, NW, KS, OCC>, SKY ? &launch_t<L, JT, NW, KS, OCC, false, SKY != 0> : nullptr, \
+     &launch_t<L, JT, NW, KS, OCC, false, false, true>,                                                 \
+     SKY ? &launch_t<L, JT, NW, KS, OCC, false, SKY != 0, true> : nullptr}
 #define FT_TILE_PX(id, L, JT, NW, KS, OCC, SKY)                                                     \
     {{id, "L" #L "_J" #JT "_W" #NW "_K" #KS "_O" #OCC "_P", L, JT, NW, KS}, &launch_t<L, JT, NW, KS, OCC, true>, \
      &launch_batch_t<L, JT, NW, KS, OCC, true>, sizeof(Shared<L, JT, NW, KS>),                     \
@@ -838,8 +879,8 @@ struct TileEntry {
 #define FT_TILE_P(id, L, JT, NW, KS, OCC) FT_TILE_PX(id, L, JT, NW, KS, OCC, nullptr)
 
 const TileEntry kTiles[] = {
-    FT_TILE(0, 1, 1, 4, 16),
-    FT_TILE_X(1, 1, 4, 4, 16, (&launch_t<1, 4, 4, 16, 0, false, true>)),
+    FT_TILE_S(0, 1, 1, 4, 16, 0, "L1_J1_W4_K16", 0),
+    FT_TILE_S(1, 1, 4, 4, 16, 0, "L1_J4_W4_K16", 1),
     FT_TILE(2, 3, 4, 4, 16),
     FT_TILE(3, 5, 4, 4, 16),
     FT_TILE(4, 5, 3, 4, 16),
@@ -855,17 +896,22 @@ const TileEntry kTiles[] = {
     FT_TILE(14, 1, 3, 4, 16),
     FT_TILE(15, 3, 3, 4, 16),
     FT_TILE(16, 5, 3, 4, 8),
-    FT_TILE_OX(17, 5, 4, 4, 8, 4, (&launch_t<5, 4, 4, 8, 4, false, true>)),
+    FT_TILE_S(17, 5, 4, 4, 8, 4, "L5_J4_W4_K8_O4", 1),
     FT_TILE_O(18, 5, 4, 4, 8, 5),
     FT_TILE(19, 3, 6, 4, 8),
     FT_TILE_O(20, 3, 6, 4, 8, 4),
     FT_TILE_O(21, 3, 6, 4, 8, 5),
-    FT_TILE_OX(22, 5, 3, 4, 8, 4, (&launch_t<5, 3, 4, 8, 4, false, true>)),
-    FT_TILE_O(23, 3, 4, 4, 8, 5),
+    FT_TILE_S(22, 5, 3, 4, 8, 4, "L5_J3_W4_K8_O4", 1),
+    FT_TILE_S(23, 3, 4, 4, 8, 5, "L3_J4_W4_K8_O5", 0),
     FT_TILE_PX(24, 5, 4, 4, 8, 4, (&launch_t<5, 4, 4, 8, 4, true, true>)),
     FT_TILE_P(25, 5, 3, 4, 8, 4),
     FT_TILE_P(26, 3, 4, 4, 8, 4),
     FT_TILE_P(27, 5, 4, 4, 8, 3),
+    FT_TILE_S(28, 5, 2, 4, 8, 4, "L5_J2_W4_K8_O4", 1),
+    FT_TILE_S(29, 5, 1, 4, 8, 4, "L5_J1_W4_K8_O4", 1),
+    FT_TILE_S(30, 3, 3, 4, 8, 5, "L3_J3_W4_K8_O5", 0),
+    FT_TILE_S(31, 3, 2, 4, 8, 5, "L3_J2_W4_K8_O5", 0),
+    FT_TILE_S(32, 3, 1, 4, 8, 5, "L3_J1_W4_K8_O5", 0),
 };
 
 }  // namespace
@@ -877,6 +923,11 @@ const TileCfg &tile_cfg(int id) { return kTiles[id].cfg; }
 size_t tile_static_lds(int id) { return kTiles[id].static_lds; }
 
 bool tile_has_sky_weights(int id) { return kTiles[id].sky_fn != nullptr; }
+
+bool tile_has_split(int id, bool sky_weights)
+{
+    return (sky_weights ? kTiles[id].sky_split_fn : kTiles[id].split_fn) != nullptr;
+}
 
 int tile_companion(int id, int jt)
 {
@@ -893,8 +944,9 @@ int tile_companion(int id, int jt)
 
 hipError_t launch_eval_grid(const EvalRun &run, const TileCfg &cfg, hipStream_t s)
 {
-    if (run.sky_norm) return kTiles[cfg.id].sky_fn ? kTiles[cfg.id].sky_fn(run, s) : hipErrorInvalidValue;
-    return kTiles[cfg.id].fn(run, s);
+    const TileEntry &t = kTiles[cfg.id];
+    const Launcher fn = run.seg_blocks > 0 ? (run.sky_norm ? t.sky_split_fn : t.split_fn) : run.sky_norm ? t.sky_fn : t.fn;
+    return fn ? fn(run, s) : hipErrorInvalidValue;
 }
 
 hipError_t launch_eval_batch(const EvalRun *runs, const int2 *items, int n_items, int max_wtp,

@@ -264,6 +264,11 @@ struct EvalRun {
                           // values [j0, j0 + n_f1) has f1 and stats shifted by j0 (rows) already
     int32_t sum_mode;
     int32_t precision;
+    // grid split over SFT blocks: seg_blocks > 0 summation blocks a workgroup row,
+    // block sums to bsum[block][n_t] (blocked sums only)
+    int32_t seg_blocks = 0;
+    float *bsum = nullptr;
+    int64_t bsum_n = 0;
 };
 
 // Tile configurations of the grid kernel.
@@ -279,6 +284,7 @@ int tile_count();
 const TileCfg &tile_cfg(int id);
 size_t tile_static_lds(int id);
 bool tile_has_sky_weights(int id);  // the tile has a form with sky-dependent weights
+bool tile_has_split(int id, bool sky_weights);  // and one split over SFT blocks
 // The tile of the same L, NW, KS and register budget with JT = jt, or -1.
 int tile_companion(int id, int jt);
 
