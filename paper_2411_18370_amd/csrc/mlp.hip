@@ -104,10 +104,10 @@ constexpr int row_threads(int r) { return 64 * r; }
 //
 // Without TRAIN a workgroup keeps both matrices and walks over tiles: nothing
 // but features is read, and the bound is the VALU's erf (two branches each, so a
-// lane's run one after the other and take waves to overlap; 200,000 rows:
-// PREDICT_FIG).  A training step's workgroups are bound by the
+// lane's run one after the other and take waves to overlap; 200,000 rows: 233 us,
+// 1200 us as four launches per 8192 rows).  A training step's workgroups are bound by the
 // latency of five layers in turn, the first behind the weights' way from L2
-// (2048 rows: STEP_FIG).
+// (2048 rows: 17 us, 59 us as seven launches).
 template <int R, bool TRAIN>
 __global__ __launch_bounds__(row_threads(R)) void mlp_rows_kernel(const float *raw, const float *labels, MlpBufs m, MlpConst c,
                                                        int bsz, int n_tiles, float inv_n, float *prob)
@@ -381,7 +381,8 @@ __device__ __forceinline__ float adam_step(const MlpBufs &m, const AdamArgs &ad,
 //               added in order, then the chunks in order
 //   320         the batch's mean loss
 // All of them run at once; the time is that of the batch's 11 MB coming
-// from memory and the last sums (2048 rows: UPD_FIG).  The tiles
+// from memory and the last sums (2048 rows: 9.5 us, 26 us as
+// four launches).  The tiles
 // of an XCD (workgroups b, b + 8, ...) are a 4 x 4 square of one matrix, whose
 // operand rows its L2 holds.
 constexpr int UPD_W = 128, UPD_C = 192;

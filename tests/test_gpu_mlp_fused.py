@@ -1,6 +1,7 @@
 """The surrogate's fused kernels at the edges of their tiles: 16- and 32-row query tiles,
 walks of more than 256 workgroups, batches around the 64-row padding and the slice rule,
-and the device's check of inputs and labels."""
+and the check of inputs and labels on the
+host (short calls) and the device."""
 import numpy as np
 import pytest
 
@@ -50,14 +51,15 @@ def test_gradient_tiles(ft, n):
     _check_grad(g, g64)
 
 
+@pytest.mark.parametrize("n", [1000, 5000])
 @pytest.mark.parametrize("row,col,value,text", [
     (700, 0, 0.0, "input 700: amplitude must be > 0"), (700, 0, np.nan, "input 700: amplitude must be > 0"),
     (3, 0, np.inf, "inputs must be finite"), (999, 5, -np.inf, "inputs must be finite"),
     (0, 3, np.nan, "inputs must be finite")])
-def test_check_reports_the_first_bad_input(ft, row, col, value, text):
+def test_check_reports_the_first_bad_input(ft, n, row, col, value, text):
     rng = np.random.default_rng(5)
-    raw = _raw(rng, 1000).astype(np.float32)
-    y = np.zeros(1000, np.float32)
+    raw = _raw(rng, n).astype(np.float32)
+    y = np.zeros(n, np.float32)
     with _ctx(ft) as c:
         net = ft.Mlp(c, SHIFT, SCALE, max_batch=1024, seed=1)
         before = net.params()
