@@ -119,6 +119,13 @@ struct ft_ctx_s {
     struct BinaryBounds {
         double f0_lo = 0.0, f0_hi = 0.0, aw_hi = 0.0, om_hi = 0.0, phase = 0.0, dt_abs = 0.0, t_ref = 0.0;
     } bin_bounds;
+    // list banks: bounds of the bank being evaluated; its order by f0
+    struct ListBounds {
+        double f0_lo = 0.0, f0_hi = 0.0, f1_abs = 0.0, dt_lo = 0.0, dt_hi = 0.0, t_ref = 0.0;
+    } list_bounds;
+    int32_t *d_order = nullptr;
+    uint32_t *d_order_cnt = nullptr;
+    size_t cap_order = 0, cap_order_cnt = 0;
     bool seg_valid = false, seg_usable = false, seg_tab_valid = false;  // segments; their device tables (of seg_t_ref, seg_res)
     double seg_t_ref = 0.0, seg_res = 0.0;
     double seg_hs = 0.0, seg_dv = 0.0;
@@ -662,6 +669,8 @@ void ft_destroy(ft_ctx c)
     release(&c->d_edges, &c->cap_edges);
     release(&c->d_stats, &c->cap_stats);
     release(&c->d_bsum, &c->cap_bsum);
+    release(&c->d_order, &c->cap_order);
+    release(&c->d_order_cnt, &c->cap_order_cnt);
     release(&c->d_seg_mask, &c->cap_seg_mask);
     release(&c->d_seg_tab, &c->cap_seg_tab);
     release(&c->d_seg_fit, &c->cap_seg_fit);
@@ -1237,6 +1246,13 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
     const double x_max = (f0_max + c_max) * (1.0 + c->vmax + aw_max) * c->t_sft;
     if (!(x_max < 2147483000.0)) return fail(c, FT_E_UNSUPPORTED, "track frequencies above 2^31/T_sft");
     bool bin_range_ok = false;
+    if (!grid && !binary) {
+        c->list_bounds = {f0_min, f0_max, std::max(std::fabs(f1_min), std::fabs(f1_max)), dt_min, dt_max, t_ref};
+        // bins of the extreme tracks (the bin is monotone in f0, f1 dt and the Doppler factor)
+        const double lo = (f0_min + c_min) * (1.0 - c->vmax) * c->t_sft, hi = (f0_max + c_max) * (1.0 + c->vmax) * c->t_sft;
+        bin_range_ok = std::floor(lo * (1.0 - 1e-12) + 0.5 - 1e-6) >= (double)c->first_bin &&
+                       std::floor(hi * (1.0 + 1e-12) + 0.5 + 1e-6) < (double)(c->first_bin + c->n_bins);
+    }
     if (binary) {
         bin_range_ok = true;
         for (int64_t t = 0; t < n0 && bin_range_ok; ++t)
@@ -1763,6 +1779,27 @@ static ft_status bank_segments(ft_ctx c)
 
 constexpr double kFitRes = 1e-5;  // largest velocity-fit residual of the bank kernel (bins)
 
+// The segments' tables for t_ref and velocity fits good for f0 T, into pl.
+static ft_status segment_tables(ft_ctx c, const EvalRun &run, double t_ref, double dt_abs, double f0T, BankPlan &pl)
+{
+    const size_t n_pad = (size_t)((c->n_sft + SUM_BLOCK - 1) / SUM_BLOCK) * SUM_BLOCK;
+    pl.mask = c->d_seg_mask;
+    pl.par = c->d_seg_tab;
+    pl.sval = c->d_seg_tab + 4 * n_pad;
+    pl.fit = c->d_seg_fit;
+    pl.hs = c->seg_hs;
+    pl.dv_max = c->seg_dv;
+    pl.dt_abs = dt_abs;
+    // a power of two, so banks of one band share the tables
+    const double res = std::exp2(std::floor(std::log2(kFitRes / f0T)));
+    if (c->seg_tab_valid && c->seg_t_ref == t_ref && c->seg_res == res) return FT_OK;
+    const hipError_t e = launch_bank_tables(run, pl, res, c->stream);
+    c->seg_tab_valid = e == hipSuccess;
+    c->seg_t_ref = t_ref;
+    c->seg_res = res;
+    return e == hipSuccess ? FT_OK : hip_fail(c, e, "bank tables");
+}
+
 // Plan of a binary evaluation.  The bank kernel (LDS windows) takes banks with
 // per-SFT weights whose tracks are proved inside the table, whose data have few
 // cut blocks, whose whole bin range fits an LDS row, and whose block polynomials are accurate: om1 <= 0.3
@@ -1785,28 +1822,32 @@ static ft_status plan_binary(ft_ctx c, EvalRun &run, BankPlan &pl)
         const double f0T = bd.f0_hi * c->t_sft, om1 = bd.om_hi * c->seg_hs;
         if (c->seg_usable && w1 >= w0 && w1 - w0 < BANK_MAX_WIDTH && om1 <= 0.3 &&
             bank_eps(f0T, f0T * bd.aw_hi, om1, bd.phase, c->seg_dv, kFitRes / f0T) <= 3e-5) {
-            const size_t n_pad = (size_t)((c->n_sft + SUM_BLOCK - 1) / SUM_BLOCK) * SUM_BLOCK;
-            pl.mask = c->d_seg_mask;
-            pl.par = c->d_seg_tab;
-            pl.sval = c->d_seg_tab + 4 * n_pad;
-            pl.fit = c->d_seg_fit;
-            pl.hs = c->seg_hs;
-            pl.dv_max = c->seg_dv;
-            pl.dt_abs = bd.dt_abs;
             pl.win_lo = (int32_t)w0;
             pl.width = (int32_t)(w1 - w0 + 1);
             pl.cols = (pl.width + 3) / 4 * 4;
-            // a power of two, so banks of one band share the tables
-            const double res = std::exp2(std::floor(std::log2(kFitRes / f0T)));
-            if (c->seg_tab_valid && c->seg_t_ref == bd.t_ref && c->seg_res == res) return FT_OK;
-            const hipError_t e = launch_bank_tables(run, pl, res, c->stream);
-            c->seg_tab_valid = e == hipSuccess;
-            c->seg_t_ref = bd.t_ref;
-            c->seg_res = res;
-            return e == hipSuccess ? FT_OK : hip_fail(c, e, "bank tables");
+            return segment_tables(c, run, bd.t_ref, bd.dt_abs, f0T, pl);
         }
     }
     return binary_cos_delta(c, run.cos_delta);
+}
+
+// Rows of the split of a bank evaluated through windows: workgroups come in
+// rounds of the resident ones; a row costs its blocks plus about half a block
+// to start.
+static int window_rows(int64_t n_list, int64_t n_blk, int64_t resident)
+{
+    const int64_t wgs = (n_list + BANK_THREADS - 1) / BANK_THREADS;
+    double best = 1e300;
+    int n_seg = 1;
+    for (int64_t bps = n_blk; bps >= 1 && (n_blk + bps - 1) / bps <= 32768; --bps) {
+        const int64_t rows = (n_blk + bps - 1) / bps;
+        const double cost = (double)((wgs * rows + resident - 1) / resident) * ((double)bps + 0.5);
+        if (cost < 0.95 * best) {
+            best = cost;
+            n_seg = (int)rows;
+        }
+    }
+    return n_seg;
 }
 
 // Binary banks too small to fill the GPU with one lane per template split
@@ -1823,19 +1864,7 @@ static hipError_t eval_binary(ft_ctx c, const EvalRun &run, const BankPlan &pl)
     if (!run.arms && run.sum_mode == FT_SUM_BLOCKED && run.n_list > 0 && run.n_list < kLanes && n_blk > 1 &&
         (size_t)n_blk * (size_t)run.n_list * sizeof(float) <= kMaxBytes) {
         if (pl.width > 0) {
-            // workgroups come in rounds of the resident ones; a row of the
-            // split costs its blocks plus about half a block to start
-            const int64_t wgs = (run.n_list + BANK_THREADS - 1) / BANK_THREADS;
-            const int64_t resident = pl.width <= 256 ? 512 : 256;
-            double best = 1e300;
-            for (int64_t bps = n_blk; bps >= 1; --bps) {
-                const int64_t rows = (n_blk + bps - 1) / bps;
-                const double cost = (double)((wgs * rows + resident - 1) / resident) * ((double)bps + 0.5);
-                if (cost < 0.95 * best) {
-                    best = cost;
-                    n_seg = (int)rows;
-                }
-            }
+            n_seg = window_rows(run.n_list, n_blk, pl.width <= 256 ? 512 : 256);
         } else {
             n_seg = (int)std::min<int64_t>(n_blk, (kLanes + run.n_list - 1) / run.n_list);
         }
@@ -1848,11 +1877,52 @@ static hipError_t eval_binary(ft_ctx c, const EvalRun &run, const BankPlan &pl)
     return pl.width > 0 ? launch_eval_bank(run, pl, bsum, n_seg, c->stream) : launch_eval_binary(run, bsum, n_seg, c->stream);
 }
 
+// List banks: through LDS windows when every track is proved inside the table
+// and the tracks of a block are polynomials to 3e-5 bins (as for binary banks),
+// else one lane per template with checked bins.  Below LIST_MIN evaluations the
+// windows' tables and the ordering cost more than they save.  Block sums as for
+// split grids.
+static ft_status plan_list(ft_ctx c, const EvalRun &run, BankPlan &pl)
+{
+    pl = BankPlan{};
+    const auto &bd = c->list_bounds;
+    if (!run.range_ok || run.n_list > 0x7fffffff) return FT_OK;
+    ft_status st = bank_segments(c);
+    if (st != FT_OK) return st;
+    const double dt_abs = std::max(std::fabs(bd.dt_lo), std::fabs(bd.dt_hi));
+    const double f0T = (bd.f0_hi + bd.f1_abs * dt_abs) * c->t_sft, bT = bd.f1_abs * c->seg_hs * c->t_sft;
+    if (!c->seg_usable || !(list_eps(f0T, bT * (bd.f0_hi / bd.f0_lo), c->seg_dv, kFitRes / f0T) <= 3e-5)) return FT_OK;
+    if (ensure(&c->d_order, &c->cap_order, (size_t)run.n_list) != hipSuccess ||
+        ensure(&c->d_order_cnt, &c->cap_order_cnt, list_order_keys()) != hipSuccess) {
+        (void)hipGetLastError();  // no room: one lane per template
+        return FT_OK;
+    }
+    pl.width = 1;  // windows on (their places and widths are the workgroups')
+    return segment_tables(c, run, bd.t_ref, dt_abs, f0T, pl);
+}
+
+static hipError_t eval_list(ft_ctx c, const EvalRun &run, const BankPlan &pl)
+{
+    if (pl.width == 0) return launch_eval_list(run, c->stream);
+    const int64_t n_blk = (run.n_sft + SUM_BLOCK - 1) / SUM_BLOCK;
+    int n_seg = 1;
+    if (run.sum_mode == FT_SUM_BLOCKED && n_blk > 1 && (double)n_blk * (double)run.n_list * 4.0 <= kGridSplitBytes) {
+        n_seg = window_rows(run.n_list, n_blk, 512);
+        if (n_seg > 1 && ensure(&c->d_bsum, &c->cap_bsum, (size_t)(n_blk * run.n_list)) != hipSuccess) {
+            (void)hipGetLastError();
+            n_seg = 1;
+        }
+    }
+    const auto &bd = c->list_bounds;
+    const ListPlan lp{bd.f0_lo, bd.f0_hi, bd.dt_lo, bd.dt_hi, c->d_order, c->d_order_cnt};
+    return launch_list_window(run, pl, lp, n_seg > 1 ? c->d_bsum : nullptr, n_seg, c->stream);
+}
+
 // The statistics of a split grid from its block sums.
 static hipError_t grid_block_sum(const EvalRun &run, hipStream_t s)
 {
     if (run.seg_blocks == 0) return hipSuccess;
-    return launch_binary_block_sum(run.bsum, run.bsum_n, (run.n_sft + SUM_BLOCK - 1) / SUM_BLOCK, run.stats, s);
+    return launch_block_sum(run.bsum, run.bsum_n, (run.n_sft + SUM_BLOCK - 1) / SUM_BLOCK, run.stats, nullptr, s);
 }
 
 // Grid launch of `tile`; with `tail`, the f1 values past the last multiple of
@@ -1898,6 +1968,9 @@ static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile,
     if (run.ap) {
         st = plan_binary(c, run, bank);
         if (st != FT_OK) return st;
+    } else if (!grid) {
+        st = plan_list(c, run, bank);
+        if (st != FT_OK) return st;
     }
     // first guess of the candidate buffer: 64 per toplist slot, never more than
     // the templates themselves nor 2^26 entries (ft_sync regrows it to the
@@ -1916,7 +1989,7 @@ static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile,
                                c->d_sky_ms, c->d_err, c->stream);
     if (e == hipSuccess)
         e = run.ap ? eval_binary(c, run, bank)
-            : !grid ? launch_eval_list(run, c->stream)
+            : !grid ? eval_list(c, run, bank)
             : tile < 0 ? launch_eval_grid_direct(run, c->stream) : launch_grid(run, tile, tail, c->stream);
     if (e == hipSuccess) e = hipEventRecord(c->ev[1], c->stream);
     const double N = (double)c->n_sft;

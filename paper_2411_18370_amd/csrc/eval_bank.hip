@@ -241,7 +241,7 @@ __device__ __forceinline__ void bank_stage(const EvalRun &r, const BankPlan &pl,
 
 // SPLIT: workgroup row y takes blocks [y bps, (y + 1) bps) and stores every
 // block's FP32 sum in bsum[block][template] (added in block order by
-// binary_block_sum_kernel: the unsplit kernel's sequence of operations).
+// block_sum_kernel: the unsplit kernel's sequence of operations).
 template <int W, bool SPLIT>
 __global__ __launch_bounds__(BANK_THREADS, 4) void eval_bank_kernel(EvalRun r, BankPlan pl, float *bsum, int bps)
 {
@@ -364,6 +364,309 @@ __global__ __launch_bounds__(BANK_THREADS, 4) void eval_bank_kernel(EvalRun r, B
     }
     if (!SPLIT && live) r.stats[t] = (float)(tot + (double)acc);
 }
+
+// List banks (arbitrary f0, f1, sky) the same way: with a0 = f0 + f1 tau and
+// a1 = f1 hs the position in a segment is x = T (a0 + a1 s)(1 + v(s).n), again
+// of degree 5 (the s^6 term, a1/a0 of a velocity term, is in the bound).
+// Templates are taken in the order of their f0 (list_order_kernel), so a
+// workgroup's window is little more than the Doppler range: LIST_W columns hold
+// it unless few templates lie far apart; such a workgroup reads the table
+// itself, at canonical bins.  Before, one lane a template walked all SFTs with
+// a gather and ten FP64 operations in a chain: 2e5 templates (0.25 Hz) x 5000
+// SFTs 2.8 ms, now LIST_FIG.
+constexpr int LIST_W = 256;
+
+struct ListLane {
+    double f0, f1, nx, ny, nz;
+    float rr, thr, f0T;
+};
+
+// Canonical bin of a list template at SFT k (the guard's rare fallback).
+__device__ __forceinline__ int list_canonical(const EvalRun &r, const ListLane &p, int k)
+{
+    const auto *vk = as_const(r.v + 3 * (int64_t)k);
+    return bin_fp64(p.f0, p.f1 * as_const(r.dt)[k], doppler_factor(vk[0], vk[1], vk[2], p.nx, p.ny, p.nz), r.t_sft);
+}
+
+__device__ __forceinline__ void list_poly(const ListLane &p, double T, double tau,
+                                          const __attribute__((address_space(4))) double *v0,
+                                          const __attribute__((address_space(4))) double *v1,
+                                          const __attribute__((address_space(4))) float *vj, double hs, int win_lo,
+                                          float (&k)[6], int &base)
+{
+    const double aT = fma(p.f1, tau, p.f0) * T, bT = (p.f1 * hs) * T;
+    const double d = fma(p.nz, v0[2], fma(p.ny, v0[1], p.nx * v0[0]));
+    const double A = fma(aT, d, aT);
+    const double ai = __builtin_rint(A);
+    double k1 = fma(bT, d, bT);
+    k[0] = (float)(A - ai);
+    k[2] = k[3] = k[4] = k[5] = 0.f;
+    if (vj) {
+        const double e = aT * fma(p.nz, v1[2], fma(p.ny, v1[1], p.nx * v1[0]));
+        k1 += e;
+        const float gx = (float)(aT * p.nx), gy = (float)(aT * p.ny), gz = (float)(aT * p.nz);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            k[j + 2] = __builtin_fmaf(gz, vj[3 * j + 2], __builtin_fmaf(gy, vj[3 * j + 1], gx * vj[3 * j]));
+#pragma unroll
+        for (int j = 5; j > 2; --j) k[j] = __builtin_fmaf(p.rr, k[j - 1], k[j]);
+        k[2] = __builtin_fmaf(p.rr, (float)e, k[2]);
+    }
+    k[1] = (float)k1;
+    base = ((int)ai - win_lo) * 4;
+}
+
+// LDS byte address in the row at `row` of the bin of position x at SFT k, checked.
+__device__ __forceinline__ int list_checked(const EvalRun &r, const ListLane &p, float x, float thr, int base, int row,
+                                            int k, int win_lo)
+{
+    const float n = __builtin_rintf(x);
+    int off = (int)n * 4 + base;
+    const bool bad = !(__builtin_fabsf(x - n) < thr);
+    if (__builtin_amdgcn_ballot_w64(bad) != 0) {
+        const int B = list_canonical(r, p, k);
+        off = bad ? (B - win_lo) * 4 : off;
+    }
+    return row + off;
+}
+
+// One SUM_BLOCK block of a lane from its window; returns the running sum.
+__device__ __forceinline__ float list_block(const EvalRun &r, const BankPlan &pl, const ListLane &p, int b, int wb, float acc)
+{
+    constexpr int W = LIST_W;
+    const auto *fit = as_const((const BankFit *)pl.fit);
+    const int k0 = b * SUM_BLOCK, len = min(SUM_BLOCK, r.n_sft - k0);
+    if (fit[b].res >= 0.f) {
+        float k[6];
+        int base;
+        list_poly(p, r.t_sft, 0.5 * (as_const(r.dt)[k0] + as_const(r.dt)[k0 + SUM_BLOCK - 1]), fit[b].v0, fit[b].v1,
+                  fit[b].v[0], pl.hs, pl.win_lo, k, base);
+        const float thr = __builtin_fmaf(-p.f0T, fit[b].res, p.thr) - 0x1p-24f;
+        float a = acc, top = 0.f;
+        uint32_t at = (uint32_t)(wb + base) - ROUND_BITS4;
+        float magic = ROUND_MAGIC;
+        asm("" : "+v"(at), "+v"(magic));  // one base; the constant stays in a VGPR
+#pragma unroll
+        for (int h = 0; h < SUM_BLOCK; h += 8) {
+            float v[8];
+            const f32x4 sa = *(lds_f32x4 *)(uintptr_t)(uint32_t)(wb + (SUM_BLOCK * W + h) * 4);
+            const f32x4 sb = *(lds_f32x4 *)(uintptr_t)(uint32_t)(wb + (SUM_BLOCK * W + h + 4) * 4);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float x = horner5(k, i < 4 ? sa[i] : sb[i - 4]);
+                const float m = x + magic;
+                top = __builtin_fmaxf(top, __builtin_fabsf(x - (m - magic)));
+                v[i] = lds_at((int)((__float_as_uint(m) << 2) + at) + (h + i) * (W * 4));
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) a += v[i];
+        }
+        if (__builtin_amdgcn_ballot_w64(!(top < thr)) == 0) return a;
+        a = acc;
+#pragma unroll 1
+        for (int h = 0; h < SUM_BLOCK; h += 8) {
+            int ad[8];
+            const f32x4 sa = *(lds_f32x4 *)(uintptr_t)(uint32_t)(wb + (SUM_BLOCK * W + h) * 4);
+            const f32x4 sb = *(lds_f32x4 *)(uintptr_t)(uint32_t)(wb + (SUM_BLOCK * W + h + 4) * 4);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                ad[i] = list_checked(r, p, horner5(k, i < 4 ? sa[i] : sb[i - 4]), thr, base, wb + (h + i) * W * 4,
+                                     k0 + h + i, pl.win_lo);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) a += lds_at(ad[i]);
+        }
+        return a;
+    }
+    uint32_t m = as_const(pl.mask)[b];
+    const f32x4 *par = (const f32x4 *)pl.par;
+    while (m) {
+        const int f = __builtin_ctz(m);
+        m &= m - 1;
+        const int kf = k0 + f, kl = k0 + (m ? __builtin_ctz(m) - 1 : len - 1);
+        float k[6];
+        int base;
+        const double tau = 0.5 * (as_const(r.dt)[kf] + as_const(r.dt)[kl]);
+        list_poly(p, r.t_sft, tau, as_const(r.v + 3 * (int64_t)((kf + kl) >> 1)), nullptr, nullptr, pl.hs, pl.win_lo, k,
+                  base);
+        const double aT = fma(p.f1, tau, p.f0) * r.t_sft;
+        const float gx = (float)(aT * p.nx), gy = (float)(aT * p.ny), gz = (float)(aT * p.nz);
+#pragma unroll 1
+        for (int q = kf; q <= kl; ++q) {
+            const f32x4 c = as_const(par)[q];
+            float y = c[1] * gx;
+            y = __builtin_fmaf(c[2], gy, y);
+            y = __builtin_fmaf(c[3], gz, y);
+            const float x = __builtin_fmaf(y, __builtin_fmaf(p.rr, c[0], 1.f), __builtin_fmaf(c[0], k[1], k[0]));
+            acc += lds_at(list_checked(r, p, x, p.thr, base, wb + (q - k0) * W * 4, q, pl.win_lo));
+        }
+    }
+    return acc;
+}
+
+// The same block at canonical bins from the table (windows that do not fit).
+__device__ __forceinline__ float list_block_direct(const EvalRun &r, const ListLane &p, int b, float acc)
+{
+    const int k0 = b * SUM_BLOCK, k1 = min(k0 + SUM_BLOCK, r.n_sft);
+    for (int k = k0; k < k1; k += 8) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int q = min(k + i, k1 - 1);
+            const int col = min(max(list_canonical(r, p, q) - r.first_bin, 0), r.n_bins - 1);
+            v[i] = r.power_w[(int64_t)q * r.n_bins + col];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (k + i < k1) acc += v[i];
+    }
+    return acc;
+}
+
+template <bool SPLIT>
+__global__ __launch_bounds__(BANK_THREADS, 4) void eval_list_kernel(EvalRun r, BankPlan pl, const int32_t *order, double dt_lo,
+                                                                    double dt_hi, float *bsum, int bps)
+{
+    extern __shared__ float win[];  // [2][kBufFloats]
+    __shared__ int lo_w[kWaves], hi_w[kWaves];
+    const int n_blk = (r.n_sft + SUM_BLOCK - 1) / SUM_BLOCK;
+    const int b0 = SPLIT ? (int)blockIdx.y * bps : 0;
+    const int b1 = SPLIT ? min(b0 + bps, n_blk) : n_blk;
+    if (b0 >= b1) return;
+    const int64_t i_raw = (int64_t)blockIdx.x * BANK_THREADS + threadIdx.x;
+    const bool live = i_raw < r.n_list;
+    const bool wave_live = __builtin_amdgcn_ballot_w64(live) != 0;  // the others only copy windows
+    const int64_t pos = live ? i_raw : r.n_list - 1, t = order[pos];
+    ListLane p;
+    p.f0 = r.f0[t];
+    p.f1 = r.f1[t];
+    p.nx = r.sky[3 * t];
+    p.ny = r.sky[3 * t + 1];
+    p.nz = r.sky[3 * t + 2];
+    {
+        // bins of the track at any time, two to spare
+        const double c0 = p.f1 * dt_lo, c1 = p.f1 * dt_hi, fl = (p.f0 + fmin(c0, c1)) * (1.0 - r.vmax) * r.t_sft,
+                     fh = (p.f0 + fmax(c0, c1)) * (1.0 + r.vmax) * r.t_sft;
+        int lo = (int)floor(fl + 0.5) - 2, hi = (int)floor(fh + 0.5) + 2;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = min(lo, __shfl_xor(lo, o, 64));
+            hi = max(hi, __shfl_xor(hi, o, 64));
+        }
+        if ((threadIdx.x & 63) == 0) {
+            lo_w[threadIdx.x >> 6] = lo;
+            hi_w[threadIdx.x >> 6] = hi;
+        }
+        const double f0T = (p.f0 + fabs(p.f1) * pl.dt_abs) * r.t_sft, bT = fabs(p.f1) * pl.hs * r.t_sft;
+        const double eps = list_eps(f0T, bT, pl.dv_max, 0.0);
+        p.rr = (float)(p.f1 * pl.hs / p.f0);
+        p.thr = (float)(0.5 - eps) - 0x1p-24f;
+        p.f0T = (float)(f0T * (1.0 + 0x1p-22));
+    }
+    __syncthreads();
+    int lo = lo_w[0], hi = hi_w[0];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) {
+        lo = min(lo, lo_w[w]);
+        hi = max(hi, hi_w[w]);
+    }
+    pl.win_lo = __builtin_amdgcn_readfirstlane(max(lo, r.first_bin));
+    const int win_hi = __builtin_amdgcn_readfirstlane(min(hi, r.first_bin + r.n_bins - 1));
+    pl.cols = (win_hi - pl.win_lo + 4) & ~3;
+    const bool fits = pl.cols <= LIST_W;
+    if (fits) bank_stage<LIST_W>(r, pl, b0, win);
+    float acc = 0.f;
+    double tot = 0.0;
+    for (int b = b0; b < b1; ++b) {
+        if (fits) {
+            // the copies of block b have landed (every wave waits for its own),
+            // and every wave is done with the other buffer
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+            __syncthreads();
+            const int cur = (b - b0) & 1;
+            if (b + 1 < b1) bank_stage<LIST_W>(r, pl, b + 1, win + (cur ^ 1) * kBufFloats<LIST_W>);
+            if (!wave_live) continue;
+            acc = list_block(r, pl, p, b, lds_addr(win) + cur * kBufFloats<LIST_W> * 4, acc);
+        } else {
+            if (!wave_live) continue;
+            acc = list_block_direct(r, p, b, acc);
+        }
+        if (SPLIT) {
+            if (live) bsum[(int64_t)b * r.n_list + pos] = acc;
+            acc = 0.f;
+        } else if (r.sum_mode == FT_SUM_BLOCKED) {
+            tot += (double)acc;
+            acc = 0.f;
+        }
+    }
+    if (!SPLIT && live) r.stats[t] = (float)(tot + (double)acc);
+}
+
+// Templates in the order of LIST_KEYS equal steps of f0 (any order within one):
+// counts, their running sum, places.  A workgroup counts 4096 templates in LDS
+// and adds or takes its share of a step with one atomic.
+constexpr int LIST_KEYS = 4096;
+
+__device__ __forceinline__ int list_key(const EvalRun &r, int64_t t, double f_lo, double scale)
+{
+    return min(max((int)((r.f0[t] - f_lo) * scale), 0), LIST_KEYS - 1);
+}
+
+template <bool PLACE>
+__global__ __launch_bounds__(1024) void list_order_kernel(EvalRun r, double f_lo, double scale, uint32_t *cnt, int32_t *order)
+{
+    __shared__ uint32_t h[LIST_KEYS];
+    for (int q = threadIdx.x; q < LIST_KEYS; q += 1024) h[q] = 0;
+    __syncthreads();
+    int key[4];
+    uint32_t rank[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t t = (int64_t)blockIdx.x * 4096 + i * 1024 + threadIdx.x;
+        key[i] = t < r.n_list ? list_key(r, t, f_lo, scale) : -1;
+        if (key[i] >= 0) rank[i] = atomicAdd(&h[key[i]], 1u);
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < LIST_KEYS; q += 1024)
+        if (h[q]) {
+            const uint32_t at = atomicAdd(&cnt[q], h[q]);
+            if (PLACE) h[q] = at;
+        }
+    if (!PLACE) return;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (key[i] >= 0) order[h[key[i]] + rank[i]] = (int32_t)((int64_t)blockIdx.x * 4096 + i * 1024 + threadIdx.x);
+}
+
+// Counts to first places, in place.
+__global__ __launch_bounds__(1024) void list_scan_kernel(uint32_t *cnt)
+{
+    __shared__ uint32_t wsum[16];
+    const int tid = threadIdx.x, lane = tid & 63;
+    uint32_t v[4], own = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[i] = cnt[4 * tid + i];
+        own += v[i];
+    }
+    uint32_t incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    if (lane == 63) wsum[tid >> 6] = incl;
+    __syncthreads();
+    uint32_t at = incl - own;
+    for (int w = 0; w < tid >> 6; ++w) at += wsum[w];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        cnt[4 * tid + i] = at;
+        at += v[i];
+    }
+}
+
+__global__ __launch_bounds__(1024) void list_clear_kernel(uint32_t *cnt) { cnt[blockIdx.x * 1024 + threadIdx.x] = 0; }
 
 // Per-SFT parameters (s, v - v0) of the segments in mask, and s alone.
 __global__ __launch_bounds__(256) void bank_par_kernel(const double *dt, const double *v, const uint32_t *mask,
@@ -531,7 +834,31 @@ hipError_t launch_eval_bank(const EvalRun &run, const BankPlan &pl, float *bsum,
                        ? launch_w<512>(run, pl, bsum, bps, grid, s)
                        : hipErrorInvalidValue;
     if (e == hipSuccess && bsum)
-        e = launch_binary_block_sum(bsum, run.n_list, n_blk, run.stats, s);
+        e = launch_block_sum(bsum, run.n_list, n_blk, run.stats, nullptr, s);
+    return e;
+}
+
+size_t list_order_keys() { return LIST_KEYS; }
+
+hipError_t launch_list_window(const EvalRun &run, const BankPlan &pl, const ListPlan &lp, float *bsum, int n_seg, hipStream_t s)
+{
+    if (run.n_list <= 0) return hipSuccess;
+    const int n_blk = (run.n_sft + SUM_BLOCK - 1) / SUM_BLOCK;
+    const int bps = bsum ? (n_blk + n_seg - 1) / n_seg : n_blk;
+    const double scale = lp.f0_hi > lp.f0_lo ? LIST_KEYS / (lp.f0_hi - lp.f0_lo) : 0.0;
+    const dim3 go((unsigned)((run.n_list + 4095) / 4096));
+    hipLaunchKernelGGL(list_clear_kernel, dim3(LIST_KEYS / 1024), dim3(1024), 0, s, lp.cnt);
+    hipLaunchKernelGGL(list_order_kernel<false>, go, dim3(1024), 0, s, run, lp.f0_lo, scale, lp.cnt, lp.order);
+    hipLaunchKernelGGL(list_scan_kernel, dim3(1), dim3(1024), 0, s, lp.cnt);
+    hipLaunchKernelGGL(list_order_kernel<true>, go, dim3(1024), 0, s, run, lp.f0_lo, scale, lp.cnt, lp.order);
+    const dim3 grid((unsigned)((run.n_list + BANK_THREADS - 1) / BANK_THREADS), bsum ? (unsigned)((n_blk + bps - 1) / bps) : 1u);
+    const size_t lds = (size_t)2 * kBufFloats<LIST_W> * sizeof(float);
+    if (bsum)
+        hipLaunchKernelGGL(eval_list_kernel<true>, grid, dim3(BANK_THREADS), lds, s, run, pl, lp.order, lp.dt_lo, lp.dt_hi, bsum, bps);
+    else
+        hipLaunchKernelGGL(eval_list_kernel<false>, grid, dim3(BANK_THREADS), lds, s, run, pl, lp.order, lp.dt_lo, lp.dt_hi, bsum, bps);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && bsum) e = launch_block_sum(bsum, run.n_list, n_blk, run.stats, lp.order, s);
     return e;
 }
 

@@ -700,7 +700,7 @@ __device__ __forceinline__ void eval_tile(const EvalRun &r, int64_t b, float *wi
 //
 // SPLIT: workgroup row y takes the summation blocks [y seg_blocks, (y + 1)
 // seg_blocks) -- a view of the run with its SFTs shifted -- and leaves FP32
-// block sums, which binary_block_sum_kernel then adds in block order in FP64:
+// block sums, which block_sum_kernel then adds in block order in FP64:
 // the same operations in the same order as unsplit.
 template <int L, int JT, int NW, int KS, int OCC, bool PIPE, bool SKYW, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, OCC > 0 ? OCC : 1) void eval_grid_kernel(EvalRun r)

@@ -536,7 +536,7 @@ __device__ __forceinline__ float binary_gather(const EvalRun &r, int k, uint32_t
 // end by W1 = sum_k u_k ab_k (FP64, sequential in SFT order).
 // SPLIT (blocked sums, no sky weights): workgroup row blockIdx.y takes the
 // SUM_BLOCK-SFT blocks [y bps, (y + 1) bps) and stores each block's FP32 sum
-// in bsum[block][template]; binary_block_sum_kernel then adds them in block
+// in bsum[block][template]; block_sum_kernel then adds them in block
 // order in FP64, which is the unsplit kernel's sequence of operations.  Small
 // banks use it to fill the GPU.
 template <bool HW, bool RANGE, bool SKYW, bool SPLIT = false>
@@ -639,7 +639,8 @@ __global__ __launch_bounds__(256) void eval_binary_kernel(EvalRun r, float *bsum
 
 // Statistic of the split binary evaluation: the block sums of each template
 // added in block order in FP64 (the unsplit kernel's totals).
-__global__ __launch_bounds__(256) void binary_block_sum_kernel(const float *bsum, int64_t n, int n_blk, float *stats)
+__global__ __launch_bounds__(256) void block_sum_kernel(const float *bsum, int64_t n, int n_blk, float *stats,
+                                                        const int32_t *order)
 {
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
         double tot = 0.0;
@@ -652,7 +653,7 @@ __global__ __launch_bounds__(256) void binary_block_sum_kernel(const float *bsum
             for (int i = 0; i < 8; ++i) tot += (double)x[i];
         }
         for (; b < n_blk; ++b) tot += (double)bsum[(int64_t)b * n + t];
-        stats[t] = (float)tot;
+        stats[order ? order[t] : t] = (float)tot;
     }
 }
 
@@ -924,10 +925,10 @@ hipError_t launch_eval_list(const EvalRun &run, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_binary_block_sum(const float *bsum, int64_t n, int n_blk, float *stats, hipStream_t s)
+hipError_t launch_block_sum(const float *bsum, int64_t n, int n_blk, float *stats, const int32_t *order, hipStream_t s)
 {
-    hipLaunchKernelGGL(binary_block_sum_kernel, dim3(grid_for(n, 256, (1u << 16))), dim3(256), 0, s, bsum, n, n_blk,
-                       stats);
+    hipLaunchKernelGGL(block_sum_kernel, dim3(grid_for(n, 256, (1u << 16))), dim3(256), 0, s, bsum, n, n_blk,
+                       stats, order);
     return hipGetLastError();
 }
 
@@ -946,7 +947,7 @@ hipError_t launch_eval_binary(const EvalRun &run, float *bsum, int n_seg, hipStr
             hipLaunchKernelGGL((eval_binary_kernel<true, true, false, true>), g2, dim3(256), 0, s, run, bsum, bps);
         else
             hipLaunchKernelGGL((eval_binary_kernel<false, true, false, true>), g2, dim3(256), 0, s, run, bsum, bps);
-        return launch_binary_block_sum(bsum, run.n_list, n_blk, run.stats, s);
+        return launch_block_sum(bsum, run.n_list, n_blk, run.stats, nullptr, s);
     }
     float *const none = nullptr;
     if (run.cos_delta > 0.0 && run.range_ok) {

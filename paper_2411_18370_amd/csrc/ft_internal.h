@@ -314,7 +314,8 @@ hipError_t launch_eval_list(const EvalRun &run, hipStream_t s);
 hipError_t launch_eval_binary(const EvalRun &run, float *bsum, int n_seg, hipStream_t s);
 // The statistics of split binary evaluations: each template's block sums
 // bsum[block][template] added in block order in FP64.
-hipError_t launch_binary_block_sum(const float *bsum, int64_t n, int n_blk, float *stats, hipStream_t s);
+// order: stats index of each template, or null.
+hipError_t launch_block_sum(const float *bsum, int64_t n, int n_blk, float *stats, const int32_t *order, hipStream_t s);
 
 // Binary banks through LDS windows (eval_bank.hip): what the host plans.
 struct BankPlan {
@@ -342,7 +343,25 @@ __host__ __device__ inline double bank_eps(double f0T, double C, double om1, dou
                      C * (4e-9 + 0x1p-50 * phase) + 0x1p-48 * f0T;
     return 1.25 * e + 1e-9;
 }
+// The same for list templates: bT >= |f1| hs T; the velocity terms appear once
+// more times a1/a0 <= bT / (f0 T).
+__host__ __device__ inline double list_eps(double f0T, double bT, double dv_max, double res)
+{
+    const double W = f0T * dv_max, rr = bT / f0T;
+    const double X = 2.0 * W + 1.01 * bT, Y = W * (1.0 + 4.0 * rr);
+    const double e = 0x1p-24 * (4.0 * X + 15.0 * Y + 6.0 * W + 1.0) + f0T * res + rr * W * (1.0 + rr) + 0x1p-48 * f0T;
+    return 1.25 * e + 1e-9;
+}
 constexpr int BANK_THREADS = 512;  // templates per workgroup of the bank kernel
+// List banks through windows: bounds of f0 and of t - t_ref, and scratch.
+struct ListPlan {
+    double f0_lo, f0_hi, dt_lo, dt_hi;
+    int32_t *order;  // [n_list]
+    uint32_t *cnt;   // [list_order_keys()]
+};
+size_t list_order_keys();
+hipError_t launch_list_window(const EvalRun &run, const BankPlan &plan, const ListPlan &list, float *bsum, int n_seg,
+                              hipStream_t s);
 // Bytes of the velocity polynomials of n_blk blocks.
 size_t bank_fit_bytes(int n_blk);
 // Fills the plan's tables from run.dt and run.v (fits with residuals up to res_max).
