@@ -365,20 +365,33 @@ __global__ __launch_bounds__(BANK_THREADS, 4) void eval_bank_kernel(EvalRun r, B
     if (!SPLIT && live) r.stats[t] = (float)(tot + (double)acc);
 }
 
-// List banks (arbitrary f0, f1, sky) the same way: with a0 = f0 + f1 tau and
-// a1 = f1 hs the position in a segment is x = T (a0 + a1 s)(1 + v(s).n), again
-// of degree 5 (the s^6 term, a1/a0 of a velocity term, is in the bound).
+// List banks (arbitrary f0, f1, sky) the same way: with a0 = f0 + f1 tau, a1 =
+// f1 hs and the segment's v0 the position at an SFT is
+//   x = T a0 (1 + v0.n) + T a1 (1 + v0.n) s + T a0 (v - v0).n,
+// four FMAs from the SFT's (s, v - v0), which stream into LDS beside the window
+// (a1/a0 of the last term is in the bound, list_eps: k_0 and the sums 3 u, their
+// terms' roundings 6 u T a1 and 10 u W).  No fit is needed, so blocks may span
+// most of a day (32 SFTs of 1800 s; a polynomial there would take degree 9).
+//
 // Templates are taken in the order of their f0 (list_order_kernel), so a
 // workgroup's window is little more than the Doppler range: LIST_W columns hold
 // it unless few templates lie far apart; such a workgroup reads the table
 // itself, at canonical bins.  Before, one lane a template walked all SFTs with
 // a gather and ten FP64 operations in a chain: 2e5 templates (0.25 Hz) x 5000
-// SFTs 2.8 ms, now LIST_FIG.
+// SFTs 2.85 ms, now 0.45 ms (2.2e12 evaluations/s, bound as above).
 constexpr int LIST_W = 256;
+constexpr int kListFloats = kBufFloats<LIST_W> + 4 * SUM_BLOCK;  // the window, s, (s, v - v0)
 
 struct ListLane {
     double f0, f1, nx, ny, nz;
-    float rr, thr, f0T;
+    float thr;
+};
+
+// A template in a segment: k_0 less its nearest integer (whose LDS offset is
+// base), k_1, and T a0 n.
+struct ListSeg {
+    float k0, k1, gx, gy, gz;
+    int base;
 };
 
 // Canonical bin of a list template at SFT k (the guard's rare fallback).
@@ -388,41 +401,32 @@ __device__ __forceinline__ int list_canonical(const EvalRun &r, const ListLane &
     return bin_fp64(p.f0, p.f1 * as_const(r.dt)[k], doppler_factor(vk[0], vk[1], vk[2], p.nx, p.ny, p.nz), r.t_sft);
 }
 
-__device__ __forceinline__ void list_poly(const ListLane &p, double T, double tau,
-                                          const __attribute__((address_space(4))) double *v0,
-                                          const __attribute__((address_space(4))) double *v1,
-                                          const __attribute__((address_space(4))) float *vj, double hs, int win_lo,
-                                          float (&k)[6], int &base)
+// Segment of SFTs [kf, kl].
+__device__ __forceinline__ ListSeg list_seg(const EvalRun &r, const ListLane &p, int kf, int kl, double hs, int win_lo)
 {
-    const double aT = fma(p.f1, tau, p.f0) * T, bT = (p.f1 * hs) * T;
+    const double tau = 0.5 * (as_const(r.dt)[kf] + as_const(r.dt)[kl]);
+    const auto *v0 = as_const(r.v + 3 * (int64_t)((kf + kl) >> 1));
+    const double aT = fma(p.f1, tau, p.f0) * r.t_sft, bT = (p.f1 * hs) * r.t_sft;
     const double d = fma(p.nz, v0[2], fma(p.ny, v0[1], p.nx * v0[0]));
-    const double A = fma(aT, d, aT);
-    const double ai = __builtin_rint(A);
-    double k1 = fma(bT, d, bT);
-    k[0] = (float)(A - ai);
-    k[2] = k[3] = k[4] = k[5] = 0.f;
-    if (vj) {
-        const double e = aT * fma(p.nz, v1[2], fma(p.ny, v1[1], p.nx * v1[0]));
-        k1 += e;
-        const float gx = (float)(aT * p.nx), gy = (float)(aT * p.ny), gz = (float)(aT * p.nz);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            k[j + 2] = __builtin_fmaf(gz, vj[3 * j + 2], __builtin_fmaf(gy, vj[3 * j + 1], gx * vj[3 * j]));
-#pragma unroll
-        for (int j = 5; j > 2; --j) k[j] = __builtin_fmaf(p.rr, k[j - 1], k[j]);
-        k[2] = __builtin_fmaf(p.rr, (float)e, k[2]);
-    }
-    k[1] = (float)k1;
-    base = ((int)ai - win_lo) * 4;
+    const double A = fma(aT, d, aT), ai = __builtin_rint(A);
+    return {(float)(A - ai),   (float)fma(bT, d, bT), (float)(aT * p.nx),
+            (float)(aT * p.ny), (float)(aT * p.nz),    ((int)ai - win_lo) * 4};
+}
+
+__device__ __forceinline__ float list_pos(const ListSeg &g, const f32x4 c)
+{
+    float x = __builtin_fmaf(c[0], g.k1, g.k0);
+    x = __builtin_fmaf(c[1], g.gx, x);
+    x = __builtin_fmaf(c[2], g.gy, x);
+    return __builtin_fmaf(c[3], g.gz, x);
 }
 
 // LDS byte address in the row at `row` of the bin of position x at SFT k, checked.
-__device__ __forceinline__ int list_checked(const EvalRun &r, const ListLane &p, float x, float thr, int base, int row,
-                                            int k, int win_lo)
+__device__ __forceinline__ int list_checked(const EvalRun &r, const ListLane &p, float x, int base, int row, int k, int win_lo)
 {
     const float n = __builtin_rintf(x);
     int off = (int)n * 4 + base;
-    const bool bad = !(__builtin_fabsf(x - n) < thr);
+    const bool bad = !(__builtin_fabsf(x - n) < p.thr);
     if (__builtin_amdgcn_ballot_w64(bad) != 0) {
         const int B = list_canonical(r, p, k);
         off = bad ? (B - win_lo) * 4 : off;
@@ -430,77 +434,58 @@ __device__ __forceinline__ int list_checked(const EvalRun &r, const ListLane &p,
     return row + off;
 }
 
-// One SUM_BLOCK block of a lane from its window; returns the running sum.
+// One SUM_BLOCK block of a lane from its window at LDS address wb; returns the
+// running sum.
 __device__ __forceinline__ float list_block(const EvalRun &r, const BankPlan &pl, const ListLane &p, int b, int wb, float acc)
 {
     constexpr int W = LIST_W;
-    const auto *fit = as_const((const BankFit *)pl.fit);
     const int k0 = b * SUM_BLOCK, len = min(SUM_BLOCK, r.n_sft - k0);
-    if (fit[b].res >= 0.f) {
-        float k[6];
-        int base;
-        list_poly(p, r.t_sft, 0.5 * (as_const(r.dt)[k0] + as_const(r.dt)[k0 + SUM_BLOCK - 1]), fit[b].v0, fit[b].v1,
-                  fit[b].v[0], pl.hs, pl.win_lo, k, base);
-        const float thr = __builtin_fmaf(-p.f0T, fit[b].res, p.thr) - 0x1p-24f;
+    const int par = wb + (kBufFloats<W>) * 4;
+    uint32_t m = as_const(pl.mask)[b];
+    if (m == 1u && len == SUM_BLOCK) {
+        const ListSeg g = list_seg(r, p, k0, k0 + SUM_BLOCK - 1, pl.hs, pl.win_lo);
         float a = acc, top = 0.f;
-        uint32_t at = (uint32_t)(wb + base) - ROUND_BITS4;
+        uint32_t at = (uint32_t)(wb + g.base) - ROUND_BITS4;
         float magic = ROUND_MAGIC;
         asm("" : "+v"(at), "+v"(magic));  // one base; the constant stays in a VGPR
 #pragma unroll
         for (int h = 0; h < SUM_BLOCK; h += 8) {
             float v[8];
-            const f32x4 sa = *(lds_f32x4 *)(uintptr_t)(uint32_t)(wb + (SUM_BLOCK * W + h) * 4);
-            const f32x4 sb = *(lds_f32x4 *)(uintptr_t)(uint32_t)(wb + (SUM_BLOCK * W + h + 4) * 4);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const float x = horner5(k, i < 4 ? sa[i] : sb[i - 4]);
-                const float m = x + magic;
-                top = __builtin_fmaxf(top, __builtin_fabsf(x - (m - magic)));
-                v[i] = lds_at((int)((__float_as_uint(m) << 2) + at) + (h + i) * (W * 4));
+                const float x = list_pos(g, *(lds_f32x4 *)(uintptr_t)(uint32_t)(par + (h + i) * 16));
+                const float n = x + magic;
+                top = __builtin_fmaxf(top, __builtin_fabsf(x - (n - magic)));
+                v[i] = lds_at((int)((__float_as_uint(n) << 2) + at) + (h + i) * (W * 4));
             }
 #pragma unroll
             for (int i = 0; i < 8; ++i) a += v[i];
         }
-        if (__builtin_amdgcn_ballot_w64(!(top < thr)) == 0) return a;
-        a = acc;
-#pragma unroll 1
-        for (int h = 0; h < SUM_BLOCK; h += 8) {
-            int ad[8];
-            const f32x4 sa = *(lds_f32x4 *)(uintptr_t)(uint32_t)(wb + (SUM_BLOCK * W + h) * 4);
-            const f32x4 sb = *(lds_f32x4 *)(uintptr_t)(uint32_t)(wb + (SUM_BLOCK * W + h + 4) * 4);
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                ad[i] = list_checked(r, p, horner5(k, i < 4 ? sa[i] : sb[i - 4]), thr, base, wb + (h + i) * W * 4,
-                                     k0 + h + i, pl.win_lo);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) a += lds_at(ad[i]);
-        }
-        return a;
+        if (__builtin_amdgcn_ballot_w64(!(top < p.thr)) == 0) return a;
     }
-    uint32_t m = as_const(pl.mask)[b];
-    const f32x4 *par = (const f32x4 *)pl.par;
+    // segments shorter than a block, and blocks with a bin to check, SFT by SFT
     while (m) {
         const int f = __builtin_ctz(m);
         m &= m - 1;
         const int kf = k0 + f, kl = k0 + (m ? __builtin_ctz(m) - 1 : len - 1);
-        float k[6];
-        int base;
-        const double tau = 0.5 * (as_const(r.dt)[kf] + as_const(r.dt)[kl]);
-        list_poly(p, r.t_sft, tau, as_const(r.v + 3 * (int64_t)((kf + kl) >> 1)), nullptr, nullptr, pl.hs, pl.win_lo, k,
-                  base);
-        const double aT = fma(p.f1, tau, p.f0) * r.t_sft;
-        const float gx = (float)(aT * p.nx), gy = (float)(aT * p.ny), gz = (float)(aT * p.nz);
+        const ListSeg g = list_seg(r, p, kf, kl, pl.hs, pl.win_lo);
 #pragma unroll 1
         for (int q = kf; q <= kl; ++q) {
-            const f32x4 c = as_const(par)[q];
-            float y = c[1] * gx;
-            y = __builtin_fmaf(c[2], gy, y);
-            y = __builtin_fmaf(c[3], gz, y);
-            const float x = __builtin_fmaf(y, __builtin_fmaf(p.rr, c[0], 1.f), __builtin_fmaf(c[0], k[1], k[0]));
-            acc += lds_at(list_checked(r, p, x, p.thr, base, wb + (q - k0) * W * 4, q, pl.win_lo));
+            const f32x4 c = *(lds_f32x4 *)(uintptr_t)(uint32_t)(par + (q - k0) * 16);
+            acc += lds_at(list_checked(r, p, list_pos(g, c), g.base, wb + (q - k0) * W * 4, q, pl.win_lo));
         }
     }
     return acc;
+}
+
+// Window of block b and its SFTs' (s, v - v0).
+__device__ __forceinline__ void list_stage(const EvalRun &r, const BankPlan &pl, int b, float *buf)
+{
+    bank_stage<LIST_W>(r, pl, b, buf);
+    const uint32_t tid = threadIdx.x;
+    if (tid >= 64 && tid < 64 + SUM_BLOCK)  // the table is padded to whole blocks
+        __builtin_amdgcn_global_load_lds((const char *)(pl.par + (int64_t)b * SUM_BLOCK * 4) + (tid - 64) * 16u,
+                                         buf + kBufFloats<LIST_W>, 16, 0, 0);
 }
 
 // The same block at canonical bins from the table (windows that do not fit).
@@ -526,7 +511,7 @@ template <bool SPLIT>
 __global__ __launch_bounds__(BANK_THREADS, 4) void eval_list_kernel(EvalRun r, BankPlan pl, const int32_t *order, double dt_lo,
                                                                     double dt_hi, float *bsum, int bps)
 {
-    extern __shared__ float win[];  // [2][kBufFloats]
+    extern __shared__ float win[];  // [2][kListFloats]
     __shared__ int lo_w[kWaves], hi_w[kWaves];
     const int n_blk = (r.n_sft + SUM_BLOCK - 1) / SUM_BLOCK;
     const int b0 = SPLIT ? (int)blockIdx.y * bps : 0;
@@ -557,10 +542,7 @@ __global__ __launch_bounds__(BANK_THREADS, 4) void eval_list_kernel(EvalRun r, B
             hi_w[threadIdx.x >> 6] = hi;
         }
         const double f0T = (p.f0 + fabs(p.f1) * pl.dt_abs) * r.t_sft, bT = fabs(p.f1) * pl.hs * r.t_sft;
-        const double eps = list_eps(f0T, bT, pl.dv_max, 0.0);
-        p.rr = (float)(p.f1 * pl.hs / p.f0);
-        p.thr = (float)(0.5 - eps) - 0x1p-24f;
-        p.f0T = (float)(f0T * (1.0 + 0x1p-22));
+        p.thr = (float)(0.5 - list_eps(f0T, bT, pl.dv_max)) - 0x1p-24f;
     }
     __syncthreads();
     int lo = lo_w[0], hi = hi_w[0];
@@ -573,7 +555,7 @@ __global__ __launch_bounds__(BANK_THREADS, 4) void eval_list_kernel(EvalRun r, B
     const int win_hi = __builtin_amdgcn_readfirstlane(min(hi, r.first_bin + r.n_bins - 1));
     pl.cols = (win_hi - pl.win_lo + 4) & ~3;
     const bool fits = pl.cols <= LIST_W;
-    if (fits) bank_stage<LIST_W>(r, pl, b0, win);
+    if (fits) list_stage(r, pl, b0, win);
     float acc = 0.f;
     double tot = 0.0;
     for (int b = b0; b < b1; ++b) {
@@ -583,9 +565,9 @@ __global__ __launch_bounds__(BANK_THREADS, 4) void eval_list_kernel(EvalRun r, B
             __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
             __syncthreads();
             const int cur = (b - b0) & 1;
-            if (b + 1 < b1) bank_stage<LIST_W>(r, pl, b + 1, win + (cur ^ 1) * kBufFloats<LIST_W>);
+            if (b + 1 < b1) list_stage(r, pl, b + 1, win + (cur ^ 1) * kListFloats);
             if (!wave_live) continue;
-            acc = list_block(r, pl, p, b, lds_addr(win) + cur * kBufFloats<LIST_W> * 4, acc);
+            acc = list_block(r, pl, p, b, lds_addr(win) + cur * kListFloats * 4, acc);
         } else {
             if (!wave_live) continue;
             acc = list_block_direct(r, p, b, acc);
@@ -852,7 +834,7 @@ hipError_t launch_list_window(const EvalRun &run, const BankPlan &pl, const List
     hipLaunchKernelGGL(list_scan_kernel, dim3(1), dim3(1024), 0, s, lp.cnt);
     hipLaunchKernelGGL(list_order_kernel<true>, go, dim3(1024), 0, s, run, lp.f0_lo, scale, lp.cnt, lp.order);
     const dim3 grid((unsigned)((run.n_list + BANK_THREADS - 1) / BANK_THREADS), bsum ? (unsigned)((n_blk + bps - 1) / bps) : 1u);
-    const size_t lds = (size_t)2 * kBufFloats<LIST_W> * sizeof(float);
+    const size_t lds = (size_t)2 * kListFloats * sizeof(float);
     if (bsum)
         hipLaunchKernelGGL(eval_list_kernel<true>, grid, dim3(BANK_THREADS), lds, s, run, pl, lp.order, lp.dt_lo, lp.dt_hi, bsum, bps);
     else

@@ -343,14 +343,11 @@ __host__ __device__ inline double bank_eps(double f0T, double C, double om1, dou
                      C * (4e-9 + 0x1p-50 * phase) + 0x1p-48 * f0T;
     return 1.25 * e + 1e-9;
 }
-// The same for list templates: bT >= |f1| hs T; the velocity terms appear once
-// more times a1/a0 <= bT / (f0 T).
-__host__ __device__ inline double list_eps(double f0T, double bT, double dv_max, double res)
+// The same for list templates (no fit): bT >= |f1| hs T.
+__host__ __device__ inline double list_eps(double f0T, double bT, double dv_max)
 {
-    const double W = f0T * dv_max, rr = bT / f0T;
-    const double X = 2.0 * W + 1.01 * bT, Y = W * (1.0 + 4.0 * rr);
-    const double e = 0x1p-24 * (4.0 * X + 15.0 * Y + 6.0 * W + 1.0) + f0T * res + rr * W * (1.0 + rr) + 0x1p-48 * f0T;
-    return 1.25 * e + 1e-9;
+    const double W = f0T * dv_max;
+    return 1.25 * (0x1p-24 * (6.0 * bT + 10.0 * W + 3.0) + W * (bT / f0T) + 0x1p-48 * f0T) + 1e-9;
 }
 constexpr int BANK_THREADS = 512;  // templates per workgroup of the bank kernel
 // List banks through windows: bounds of f0 and of t - t_ref, and scratch.
