@@ -2559,11 +2559,13 @@ struct BatchPlan {
     std::vector<int64_t> dt_prefix, stats_prefix, gen_prefix_sft, gen_prefix_elem, sky_prefix;
     std::vector<int32_t> sft_begin, perm;
     std::vector<double> tref, sky_tile;
-    std::vector<std::vector<int2>> items;  // per tile id; index tile_count(): direct items
+    std::vector<std::vector<int2>> items;  // per tile id; then the small-bank and the local-bank kernel's
     std::vector<char> uniform;             // per run: the run-length guard applies
     std::vector<double> dt_absmax, vmax;   // per run: window inputs
     std::vector<int> group_wtp;            // per tile id: widest LDS row of its runs
     int small_chunk = 8;                   // f0 values per item of the small-bank kernel (5 or 8)
+    int local_chunk = 8;                   // and of the local-bank kernel
+    std::vector<char> local;               // per run without a tile: the local-bank kernel takes it
 };
 
 // Tile-dependent fields of batch run r for `tile` (0-based, -1: direct).
@@ -2594,24 +2596,48 @@ int64_t run_items(const BatchPlan &pl, int r)
 {
     const EvalRun &E = pl.runs[r];
     if (pl.tile[r] >= 0) return (int64_t)E.tiles_f0 * E.tiles_f1 * E.tiles_sky;
+    if (pl.local[r])
+        return (int64_t)((E.n_f0 + pl.local_chunk - 1) / pl.local_chunk) * (((int64_t)E.n_f1 * E.n_sky + LOCAL_JS - 1) / LOCAL_JS);
     return (int64_t)((E.n_f0 + pl.small_chunk - 1) / pl.small_chunk) * (((int64_t)E.n_f1 * E.n_sky + 63) / 64);
 }
 
-// f0 chunk of the small-bank kernel for the batch's small runs: the one with
-// fewer modelled lane operations, counting per item and SFT a fixed part
-// (Doppler factor, f1 dt, loads: about 1.5 bins' worth) plus one bin, gather
-// and add per f0 slot.  Label campaigns (5 f0 values per run) take 5; a batch
-// of 16- or 24-value runs takes 8.
-int choose_small_chunk(const BatchPlan &pl)
+// Whether batch run r (without a tile) suits the local-bank kernel: a uniform
+// f0 grid of one bin, and bins of all its tracks at any time within LOCAL_W
+// (f0 chunk, spindown, patch of sky; 12 columns for the movement within a block
+// and the margins).  Others would take the canonical bins block by block, which
+// is slower than the small-bank kernel.
+bool local_bank(const BatchPlan &pl, int r, const ft_run &R, const double *f0h, const double *f1h, const double *skyh,
+                double t_sft)
+{
+    const EvalRun &E = pl.runs[r];
+    if (!pl.uniform[r] || (R.n_f0 > 1 && std::fabs(E.dT - 1.0) > 0.01)) return false;
+    const double *f1 = f1h + R.f1_begin, *n = skyh + 3 * (size_t)R.sky_begin;
+    const double f1_span = *std::max_element(f1, f1 + R.n_f1) - *std::min_element(f1, f1 + R.n_f1);
+    double rad = 0.0;
+    for (int s = 1; s < R.n_sky; ++s) {
+        const double x = n[3 * s] - n[0], y = n[3 * s + 1] - n[1], z = n[3 * s + 2] - n[2];
+        rad = std::max(rad, std::sqrt(x * x + y * y + z * z));
+    }
+    const double f_hi = f0h[R.f0_begin + R.n_f0 - 1];
+    return 8.0 + f1_span * pl.dt_absmax[r] * t_sft + f_hi * pl.vmax[r] * 2.0 * rad * t_sft + 12.0 <= (double)LOCAL_W;
+}
+
+// f0 chunk of the small-bank (local: of the local-bank) kernel for its runs of
+// the batch: the one with fewer modelled lane operations, counting per item and
+// SFT a fixed part (positions, loads) plus one part per f0 slot.  Label
+// campaigns (5 f0 values per run) take 5; a batch of 16- or 24-value runs takes
+// 8.
+int choose_small_chunk(const BatchPlan &pl, bool local)
 {
     double cost[2] = {0.0, 0.0};
     const int chunks[2] = {5, 8};
     for (size_t r = 0; r < pl.runs.size(); ++r) {
-        if (pl.tile[r] >= 0) continue;
+        if (pl.tile[r] >= 0 || (pl.local[r] != 0) != local) continue;
         const EvalRun &E = pl.runs[r];
-        const double js = (double)(((int64_t)E.n_f1 * E.n_sky + 63) / 64) * (double)E.n_sft;
+        const int lanes = local ? LOCAL_JS : 64;
+        const double js = (double)(((int64_t)E.n_f1 * E.n_sky + lanes - 1) / lanes) * (double)E.n_sft;
         for (int q = 0; q < 2; ++q)
-            cost[q] += (double)((E.n_f0 + chunks[q] - 1) / chunks[q]) * js * (1.5 + chunks[q]);
+            cost[q] += (double)((E.n_f0 + chunks[q] - 1) / chunks[q]) * js * ((local ? 5.0 : 1.5) + chunks[q]);
     }
     return cost[0] < cost[1] ? 5 : 8;
 }
@@ -2639,7 +2665,7 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
     auto &b = c->bb;
     const int n_runs = (int)pl.runs.size();
     hipError_t e = launch_fill_u32(c->d_err, 0u, 1, st);
-    if (e == hipSuccess) e = launch_fill_u32(b.counters, 0u, tile_count() + 1, st);
+    if (e == hipSuccess) e = launch_fill_u32(b.counters, 0u, tile_count() + 2, st);
     if (e == hipSuccess)
         e = launch_batch_dt(b.tmid, b.sft_begin, b.tref, b.dt_prefix, n_runs, pl.dt_prefix[n_runs], b.dt, st);
     if (e == hipSuccess && generate)
@@ -2651,13 +2677,13 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
     // before the selection (a captured graph gets parallel branches), so one
     // launch's last workgroups overlap the next launch
     struct Launch {
-        int id;  // tile, or tile_count() for the small-bank kernel
+        int id;  // tile, tile_count() for the small-bank kernel, the next for the local-bank kernel
         int64_t off;
         int n;
     };
     std::vector<Launch> ls;
     int64_t item_off = 0;
-    for (int id = 0; id <= tile_count(); ++id) {
+    for (int id = 0; id <= tile_count() + 1; ++id) {
         const int n_items = (int)pl.items[id].size();
         if (n_items > 0) ls.push_back({id, item_off, n_items});
         item_off += n_items;
@@ -2675,6 +2701,9 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
         if (L.id < tile_count())
             e = launch_eval_batch(b.runs, b.items + L.off, L.n, pl.group_wtp[L.id], b.counters + L.id,
                                   std::min(L.n, 2048), tile_cfg(L.id), s);
+        else if (L.id == tile_count() + 1)
+            e = launch_eval_batch_local(b.runs, b.items + L.off, L.n, pl.local_chunk, b.counters + L.id,
+                                        std::min(L.n, 1024), s);
         else
             e = launch_eval_batch_small(b.runs, b.items + L.off, L.n, pl.small_chunk, b.counters + tile_count(),
                                         std::min(L.n, 8192), s);
@@ -2869,7 +2898,7 @@ ft_status ft_eval_batch(ft_ctx c, const ft_batch *bt, int32_t use_graph)
     BatchPlan pl;
     pl.runs.resize(n_runs);
     pl.tile.resize(n_runs);
-    pl.items.assign(tile_count() + 1, {});
+    pl.items.assign(tile_count() + 2, {});
     pl.dt_prefix.assign(n_runs + 1, 0);
     pl.stats_prefix.assign(n_runs + 1, 0);
     pl.gen_prefix_sft.assign(n_runs + 1, 0);
@@ -2878,6 +2907,7 @@ ft_status ft_eval_batch(ft_ctx c, const ft_batch *bt, int32_t use_graph)
     pl.sft_begin.resize(n_runs);
     pl.tref.resize(n_runs);
     pl.uniform.assign(n_runs, 0);
+    pl.local.assign(n_runs, 0);
     pl.dt_absmax.assign(n_runs, 0.0);
     pl.vmax.assign(n_runs, 0.0);
     for (int r = 0; r < n_runs; ++r) {
@@ -3004,7 +3034,7 @@ ft_status ft_eval_batch(ft_ctx c, const ft_batch *bt, int32_t use_graph)
         (e = ensure(&b.power, &b.c_power, (size_t)n_power)) != hipSuccess ||
         (e = ensure(&b.stats, &b.c_stats, (size_t)n_stats)) != hipSuccess ||
         (e = ensure(&b.runs, &b.c_runs, (size_t)n_runs)) != hipSuccess ||
-        (e = ensure(&b.counters, &b.c_counters, (size_t)std::max(tile_count() + 1, 129))) != hipSuccess ||
+        (e = ensure(&b.counters, &b.c_counters, (size_t)std::max(tile_count() + 2, 129))) != hipSuccess ||
         (e = ensure(&b.cand, &b.c_cand, (size_t)n_runs * cap)) != hipSuccess ||
         (e = ensure(&b.s64, &b.c_s64, (size_t)n_runs * cap)) != hipSuccess ||
         (e = ensure(&b.out, &b.c_out, (size_t)n_runs * k)) != hipSuccess ||
@@ -3111,14 +3141,17 @@ ft_status ft_eval_batch(ft_ctx c, const ft_batch *bt, int32_t use_graph)
         plan_tiles();
     }
     // work items grouped by tile (the direct kernel's last)
-    pl.small_chunk = choose_small_chunk(pl);
+    for (int r = 0; r < n_runs; ++r)
+        if (pl.tile[r] < 0) pl.local[r] = local_bank(pl, r, runs[r], f0h.data(), f1h.data(), skyh.data(), bt->t_sft);
+    pl.small_chunk = choose_small_chunk(pl, false);
+    pl.local_chunk = choose_small_chunk(pl, true);
     int64_t total_items = 0;
     for (int r = 0; r < n_runs; ++r) total_items += run_items(pl, r);
     if (total_items >= 0x7fffffff) return fail(c, FT_E_UNSUPPORTED, "too many work items");
     pl.group_wtp.assign(tile_count() + 1, 64);
     for (int r = 0; r < n_runs; ++r) {
         const int t = pl.tile[r];
-        append_items(pl, r, pl.items[t >= 0 ? t : tile_count()]);
+        append_items(pl, r, pl.items[t >= 0 ? t : tile_count() + (pl.local[r] ? 1 : 0)]);
         if (t >= 0) pl.group_wtp[t] = std::max(pl.group_wtp[t], pl.runs[r].wtp);
     }
     // longest first within each group (an item's time grows with its run's

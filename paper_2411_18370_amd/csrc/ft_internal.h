@@ -299,6 +299,13 @@ hipError_t launch_eval_batch(const EvalRun *runs, const int2 *items, int n_items
 // zero at launch.
 hipError_t launch_eval_batch_small(const EvalRun *runs, const int2 *items, int n_items, int f0_chunk,
                                    unsigned *counter, int grid, hipStream_t s);
+// Batch runs with a local bank (eval_local.hip): items[i] = (run, f0 chunk *
+// n_js_chunks + js chunk), f0 chunks of f0_chunk (5 or 8), js chunks of
+// LOCAL_JS (f1, sky) pairs whose bins stay within LOCAL_W columns per block.
+constexpr int LOCAL_W = 64, LOCAL_JS = 256;
+hipError_t launch_eval_batch_local(const EvalRun *runs, const int2 *items, int n_items, int f0_chunk, unsigned *counter,
+                                   int grid, hipStream_t s);
+
 // Exact per-run toplists of a batch (one workgroup per run, all of a run's
 // templates form one segment): out[r*k + rank], n_out[r], max_z[r].
 hipError_t launch_select_batch(const EvalRun *runs, int n_runs, int k, int cap_per_run,
