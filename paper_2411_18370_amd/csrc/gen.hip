@@ -27,6 +27,8 @@
 // those columns equal the full table's.
 #include "ft_internal.h"
 
+#include <algorithm>
+
 namespace ft {
 
 namespace {
@@ -199,49 +201,134 @@ __global__ void gen_prep_kernel(const GenRun *runs, int n_runs, const int64_t *s
     }
 }
 
-// Noise (and signals) of the table rows: each wavefront takes four SFT rows,
-// sixteen lanes to a row, over the row's columns (its band for batch runs,
-// which is a few tens of columns wide for a local bank).
-constexpr int kRowLanes = 16;
+// One cell of a row: the noise of column b of SFT kk of a run, before signals.
+__device__ __forceinline__ void gen_cell(uint64_t seed, uint32_t kk, uint32_t run, int b, double &re, double &im)
+{
+    uint32_t c[4] = {(uint32_t)b, kk, run, 0u};
+    philox4x32_10(c, (uint32_t)seed, (uint32_t)(seed >> 32));
+    const double u1 = unit53(c[0], c[1]);
+    const double u2 = unit53(c[2], c[3]);
+    const double r = sqrt(-2.0 * lib_log(u1));
+    const double th = 2.0 * M_PI * u2;
+    double sth, cth;
+    lib_sincos(th, sth, cth);
+    re = r * cth;
+    im = r * sth;
+}
 
+// Noise (and signals) of the table rows, over each row's columns (its band for
+// batch runs).  Bound by the vector units (the counter rounds, a logarithm, a
+// sine and cosine in FP64), so the lanes are kept full: a workgroup takes the
+// cells of GEN_ROWS rows one after the other, whatever the rows' widths -- a
+// local bank's are 10 to 40 columns, of which sixteen lanes to a row left 40%
+// idle, and every row's run was searched for again (1024 runs x 10^4 SFTs: 3.5
+// ms, now 1.9 ms).  Rows of more than GEN_WIDTH columns on average, whose last
+// sixteen cells matter little, and rows with several signals take sixteen lanes
+// each (64 runs' rows of a few hundred columns: 0.42 ms, by cells 0.44 ms).
+constexpr int GEN_WIDTH = 96, kRowLanes = 16;
+
+struct GenRow {
+    float *row;
+    uint64_t seed;
+    double amp[3];
+    uint32_t kk, run;
+    int32_t lo, off, sig;  // first column, cells before the row, signal's column (INT32_MIN: none)
+};
+
+template <int GEN_ROWS>
 __global__ __launch_bounds__(256) void gen_noise_kernel(const GenRun *runs, int n_runs,
                                                         const int64_t *row_prefix, int64_t total_rows)
 {
-    const int lane = threadIdx.x % kRowLanes;
-    const int64_t group0 = (int64_t)blockIdx.x * (blockDim.x / kRowLanes) + threadIdx.x / kRowLanes;
-    const int64_t n_groups = (int64_t)gridDim.x * (blockDim.x / kRowLanes);
-    for (int64_t q = group0; q < total_rows; q += n_groups) {
-        const int rr = find_run(row_prefix, n_runs, q);
-        const GenRun &g = runs[rr];
-        const int k = (int)(q - row_prefix[rr]);
-        int lo = 0, hi = g.n_bins - 1;
-        if (g.band_mode) {
-            lo = g.band[2 * k];
-            hi = g.band[2 * k + 1];
-        }
-        float *row = g.table + (int64_t)k * g.n_bins;
-        for (int b = lo + lane; b <= hi; b += kRowLanes) {
-            uint32_t c[4] = {(uint32_t)b, (uint32_t)(k + g.sft_offset), g.run, 0u};
-            philox4x32_10(c, (uint32_t)g.seed, (uint32_t)(g.seed >> 32));
-            const double u1 = unit53(c[0], c[1]);
-            const double u2 = unit53(c[2], c[3]);
-            const double r = sqrt(-2.0 * lib_log(u1));
-            const double th = 2.0 * M_PI * u2;
-            double sth, cth;
-            lib_sincos(th, sth, cth);
-            double re = r * cth;
-            const double im = r * sth;
-            for (int i = 0; i < g.n_inj; ++i) {
-                const int64_t ki = (int64_t)i * g.n_sft + k;
-                const int32_t B = g.inj_bin[ki];
-                if (B == INT32_MIN) continue;
-                const int64_t m = g.first_bin + b - (int64_t)B;
-                if (m >= -1 && m <= 1) re = re + g.inj_amp[3 * ki + (int)(m + 1)];
+    __shared__ GenRow rows[GEN_ROWS];
+    constexpr int GEN_CELLS = GEN_WIDTH * GEN_ROWS;
+    __shared__ uint8_t id[GEN_CELLS];
+    __shared__ int cells, rr_s[GEN_ROWS], hi_s[GEN_ROWS];
+    __shared__ bool several;
+    const int tid = threadIdx.x;
+    for (int64_t base = (int64_t)blockIdx.x * GEN_ROWS; base < total_rows; base += (int64_t)gridDim.x * GEN_ROWS) {
+        const int n = (int)min((int64_t)GEN_ROWS, total_rows - base);
+        __syncthreads();  // the last rows' cells are done
+        if (tid < 64) {
+            int w = 0;
+            bool multi = false;
+            if (tid < n) {
+                const int rr = find_run(row_prefix, n_runs, base + tid);
+                const GenRun &g = runs[rr];
+                const int k = (int)(base + tid - row_prefix[rr]);
+                int lo = 0, hi = g.n_bins - 1;
+                if (g.band_mode) {
+                    lo = g.band[2 * k];
+                    hi = g.band[2 * k + 1];
+                }
+                w = max(hi - lo + 1, 0);
+                GenRow &q = rows[tid];
+                q.row = g.table + (int64_t)k * g.n_bins;
+                q.seed = g.seed;
+                q.kk = (uint32_t)(k + g.sft_offset);
+                q.run = g.run;
+                q.lo = lo;
+                q.sig = INT32_MIN;
+                if (g.n_inj == 1 && g.inj_bin[k] != INT32_MIN) {
+                    q.sig = (int32_t)((int64_t)g.inj_bin[k] - g.first_bin);
+                    for (int m = 0; m < 3; ++m) q.amp[m] = g.inj_amp[3 * k + m];
+                }
+                multi = g.n_inj > 1;
+                rr_s[tid] = rr;
+                hi_s[tid] = hi;
             }
-            row[b] = (float)(re * re + im * im);
+            const bool any = __builtin_amdgcn_ballot_w64(multi) != 0;
+            int64_t incl = w;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int64_t y = __shfl_up(incl, o, 64);
+                if (tid >= o) incl += y;
+            }
+            const int64_t all = __shfl(incl, 63, 64);
+            if (tid < n) rows[tid].off = (int)min(incl - w, (int64_t)GEN_CELLS);
+            if (tid == 0) {
+                cells = (int)min(all, (int64_t)GEN_CELLS + 1);
+                several = any;
+            }
+        }
+        __syncthreads();
+        const auto cell = [](const GenRow &g, int b) {
+            double re, im;
+            gen_cell(g.seed, g.kk, g.run, b, re, im);
+            const int m = b - g.sig;
+            if (g.sig != INT32_MIN && m >= -1 && m <= 1) re = re + g.amp[m + 1];
+            g.row[b] = (float)(re * re + im * im);
+        };
+        if (cells <= GEN_WIDTH * n && !several) {
+            constexpr int P = 256 / GEN_ROWS;  // threads a row
+            const int q = tid / P;
+            if (q < n)
+                for (int b = rows[q].lo + tid % P; b <= hi_s[q]; b += P) id[rows[q].off + b - rows[q].lo] = (uint8_t)q;
+            __syncthreads();
+            for (int c = tid; c < cells; c += 256) cell(rows[id[c]], rows[id[c]].lo + (c - rows[id[c]].off));
+        } else if (!several) {
+            for (int q = tid / kRowLanes; q < n; q += 256 / kRowLanes)
+                for (int b = rows[q].lo + tid % kRowLanes; b <= hi_s[q]; b += kRowLanes) cell(rows[q], b);
+        } else {
+            for (int q = tid / kRowLanes; q < n; q += 256 / kRowLanes) {
+                const GenRun &g = runs[rr_s[q]];
+                const int k = (int)(base + q - row_prefix[rr_s[q]]);
+                for (int b = rows[q].lo + tid % kRowLanes; b <= hi_s[q]; b += kRowLanes) {
+                    double re, im;
+                    gen_cell(g.seed, rows[q].kk, g.run, b, re, im);
+                    for (int i = 0; i < g.n_inj; ++i) {
+                        const int64_t ki = (int64_t)i * g.n_sft + k;
+                        const int32_t B = g.inj_bin[ki];
+                        if (B == INT32_MIN) continue;
+                        const int64_t m = g.first_bin + b - (int64_t)B;
+                        if (m >= -1 && m <= 1) re = re + g.inj_amp[3 * ki + (int)(m + 1)];
+                    }
+                    rows[q].row[b] = (float)(re * re + im * im);
+                }
+            }
         }
     }
 }
+
 // Random template bank of sources in circular binary systems, uniform in the
 // binary appendix's xi coordinates (Eq. unif_transform: up to constants xi is
 // (f0^6, alpha, sin delta, a_p^3, Omega^4, phi_b)).  Template i draws six
@@ -390,10 +477,12 @@ hipError_t launch_gen_tables(const GenRun *prep, int n_prep, const int64_t *prep
                            total_prep_sft);
     }
     if (n_runs > 0 && total_rows > 0) {
-        int64_t b2 = (total_rows + 15) / 16;  // sixteen rows per block
-        if (b2 > 65536) b2 = 65536;
-        hipLaunchKernelGGL(gen_noise_kernel, dim3((unsigned)b2), dim3(256), 0, s, runs, n_runs, row_prefix,
-                           total_rows);
+        // 64 rows a workgroup once that leaves some thousand workgroups (10^4
+        // rows of 100 columns: 47 us with 64 rows, 27 us with 16)
+        const int rows = total_rows >= (1 << 18) ? 64 : 16;
+        const unsigned b2 = (unsigned)std::min<int64_t>((total_rows + rows - 1) / rows, 65536);
+        auto *kern = rows == 64 ? gen_noise_kernel<64> : gen_noise_kernel<16>;
+        hipLaunchKernelGGL(kern, dim3(b2), dim3(256), 0, s, runs, n_runs, row_prefix, total_rows);
     }
     return hipGetLastError();
 }
