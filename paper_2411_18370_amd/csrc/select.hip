@@ -867,20 +867,20 @@ __global__ __launch_bounds__(1024) void select_small_kernel(const float *stats, 
 // Batches: one workgroup per run does the whole exact selection of that run
 // (runs hold at most a few 1e5 templates): radix select in LDS, candidate
 // compaction, FP64 re-summation (four wavefronts per candidate) and ranking.
-// SB_THREADS threads: the re-summation takes SB_GROUPS candidates at a time, four
-// wavefronts each (three form terms, one adds them).
+// The re-summation takes GROUPS candidates at a time, four wavefronts each
+// (three form terms, one adds them); the keys are read eight ahead and a wave
+// chooses a digit (a lane alone took 55 us over a run's four).
 // ---------------------------------------------------------------------------
-constexpr int SB_THREADS = 1024;
 constexpr int SB_GROUP_WAVES = 4;
-constexpr int SB_GROUPS = SB_THREADS / 64 / SB_GROUP_WAVES;
 
-__global__ __launch_bounds__(SB_THREADS) void select_batch_kernel(const EvalRun *runs, int k, int cap,
-                                                           int64_t *cand_all, double *s64_all,
-                                                           ft_candidate *out, int32_t *n_out,
-                                                           double *max_z, uint32_t *err)
+template <int SB_GROUPS>
+__global__ __launch_bounds__(256 * SB_GROUPS) void select_batch_kernel(const EvalRun *runs, int k, int cap,
+                                                                int64_t *cand_all, double *s64_all,
+                                                                ft_candidate *out, int32_t *n_out,
+                                                                double *max_z, uint32_t *err)
 {
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t st_prefix, st_mask, st_krem, st_thr, st_done, n_cand;
+    constexpr int SB_THREADS = 256 * SB_GROUPS;
+    __shared__ uint32_t hist[256], st[ST], n_cand;
     __shared__ SeqBuf<SB_GROUP_WAVES, false> seq[SB_GROUPS];
     const int r = blockIdx.x;
     const EvalRun R = runs[r];
@@ -891,63 +891,42 @@ __global__ __launch_bounds__(SB_THREADS) void select_batch_kernel(const EvalRun 
     int64_t *cand = cand_all + (int64_t)r * cap;
     double *s64 = s64_all + (int64_t)r * cap;
     if (tid == 0) {
-        st_prefix = 0;
-        st_mask = 0;
-        st_krem = (uint32_t)k;
-        st_done = 0;
-        st_thr = 0;
+        st[S_PREFIX] = st[S_MASK] = st[S_DONE] = st[S_THR] = 0;
+        st[S_KREM] = (uint32_t)k;
         n_cand = 0;
     }
+    // f(t, key) for every template's statistic that is a number
+    auto keys = [&](auto f) {
+        for (int64_t t0 = tid; t0 < n_t; t0 += 8 * SB_THREADS) {
+            uint32_t key[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                key[i] = t0 + i * SB_THREADS < n_t ? __float_as_uint(R.stats[t0 + i * SB_THREADS]) : ~0u;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (key[i] <= NAN_KEY) f(t0 + i * SB_THREADS, key[i]);
+        }
+    };
     for (int pass = 0; pass < 4; ++pass) {
         const int shift = 24 - 8 * pass;
         if (tid < 256) hist[tid] = 0;
         __syncthreads();
-        if (!st_done) {
-            const uint32_t mask = st_mask, prefix = st_prefix;
-            for (int64_t t = tid; t < n_t; t += SB_THREADS) {
-                const uint32_t key = __float_as_uint(R.stats[t]);
-                if (key > NAN_KEY || (key & mask) != prefix) continue;
-                atomicAdd(&hist[(key >> shift) & 255u], 1u);
-            }
+        if (!st[S_DONE]) {
+            const uint32_t mask = st[S_MASK], prefix = st[S_PREFIX];
+            keys([&](int64_t, uint32_t key) {
+                if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+            });
         }
         __syncthreads();
-        if (tid == 0 && !st_done) {
-            uint32_t cum = 0;
-            int found = -1;
-            for (int d = 255; d >= 0; --d) {
-                if (cum + hist[d] >= st_krem) {
-                    found = d;
-                    break;
-                }
-                cum += hist[d];
-            }
-            if (found < 0) {
-                st_done = 1;
-                st_thr = 0;
-            } else {
-                st_prefix |= (uint32_t)found << shift;
-                st_mask |= 255u << shift;
-                st_krem -= cum;
-                if (shift == 0) {
-                    const double kth = (double)__uint_as_float(st_prefix);
-                    const double thr = kth * (1.0 - two_e) / (1.0 + two_e);
-                    float tf = (float)thr;
-                    if ((double)tf > thr) tf = nextafterf(tf, 0.f);
-                    if (!(tf > 0.f)) tf = 0.f;
-                    st_thr = __float_as_uint(tf);
-                    st_done = 1;
-                }
-            }
-        }
+        if (tid < 64) choose_digit([&](int d) { return hist[d]; }, st, shift, two_e);
         __syncthreads();
     }
-    const uint32_t thr = st_thr;
-    for (int64_t t = tid; t < n_t; t += SB_THREADS) {
-        const uint32_t key = __float_as_uint(R.stats[t]);
-        if (key > NAN_KEY || key < thr) continue;
+    const uint32_t thr = st[S_THR];
+    keys([&](int64_t t, uint32_t key) {
+        if (key < thr) return;
         const uint32_t pos = atomicAdd(&n_cand, 1u);
         if (pos < (uint32_t)cap) cand[pos] = t;
-    }
+    });
     __syncthreads();
     int nc = (int)n_cand;
     if (nc > cap) {
@@ -1039,8 +1018,13 @@ hipError_t launch_select_batch(const EvalRun *runs, int n_runs, int k, int cap_p
                                int32_t *n_out, double *max_z, uint32_t *err, hipStream_t s)
 {
     if (n_runs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(select_batch_kernel, dim3((unsigned)n_runs), dim3(SB_THREADS), 0, s, runs, k,
-                       cap_per_run, cand, cand_s64, out, n_out, max_z, err);
+    // one or two candidates a run and runs for every CU: a group each, so that
+    // four and more runs share a CU (1024 runs of 10^4 SFTs, toplists of one:
+    // 435 us with four groups, 304 us with one)
+    auto *kern = k <= 2 && n_runs > 256 ? select_batch_kernel<1> : select_batch_kernel<4>;
+    const int threads = k <= 2 && n_runs > 256 ? 256 : 1024;
+    hipLaunchKernelGGL(kern, dim3((unsigned)n_runs), dim3(threads), 0, s, runs, k, cap_per_run, cand, cand_s64, out, n_out,
+                       max_z, err);
     return hipGetLastError();
 }
 
