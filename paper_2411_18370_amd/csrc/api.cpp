@@ -177,6 +177,8 @@ struct ft_ctx_s {
         size_t c_out = 0;
         uint8_t *labels = nullptr;
         size_t c_labels = 0;
+        float *bsum = nullptr;
+        size_t c_bsum = 0;
     } bb;
     bool have_batch = false;
     int batch_runs = 0, batch_k = 0, batch_cap = 0;
@@ -718,6 +720,7 @@ void ft_destroy(ft_ctx c)
         release(&c->d_probe, &c->cap_probe);
         release(&b.out, &b.c_out);
         release(&b.labels, &b.c_labels);
+        release(&b.bsum, &b.c_bsum);
     }
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
     if (c->graph) (void)hipGraphDestroy(c->graph);
@@ -2527,28 +2530,26 @@ ft_status ft_count_index_mismatches_noalloc(ft_ctx c, const ft_bank *bank, doubl
 // ---------------------------------------------------------------------------
 namespace {
 
-// Tile of one batch run: fewest wasted lanes over the tiles whose f1 tile
-// suits small f1 sets.
+// Tile of one batch run: the least time per template with the GPU full (the
+// batch's runs share it, split over SFT blocks where they do not fill it), lanes
+// past the bank included.  64 runs of 18 to 360 f0, 3 f1, 500 to 5000 SFTs: the
+// largest group's tile L5_J3_W4_K8 took 16% more per template than
+// L5_J3_W4_K8_O4.
 int choose_batch_tile(int64_t n_f0, int64_t n_f1, bool uniform)
 {
-    const int with_runs[] = {15, 16, 2, 8};  // L3_J3, L5_J3, L3_J4, L5_J4
-    const int plain[] = {14, 1};             // L1_J3, L1_J4
-    double best = 1e30;
+    double best = 1e300;
     int best_id = 14;
-    auto consider = [&](int id) {
-        const TileCfg &t = tile_cfg(id);
-        const double f0w = std::ceil((double)n_f0 / (64.0 * t.L)) * 64.0 * t.L / (double)n_f0;
-        const double f1w = std::ceil((double)n_f1 / t.JT) * t.JT / (double)n_f1;
-        const double ops = t.L > 1 ? (7.0 + t.L) / t.L : 7.0;
-        const double cost = f0w * f1w * ops;
-        if (cost < best - 1e-9) {
+    for (const TileTime &t : kTileTime) {
+        const TileCfg &cfg = tile_cfg(t.id);
+        if (!tile_has_split(t.id, false) || (cfg.L > 1 && !uniform)) continue;
+        const double f0w = std::ceil((double)n_f0 / (64.0 * cfg.L)) * 64.0 * cfg.L / (double)n_f0;
+        const double f1w = std::ceil((double)n_f1 / cfg.JT) * cfg.JT / (double)n_f1;
+        const double cost = f0w * f1w * (t.first + t.more * (t.most - 1)) / (t.most * 64.0 * cfg.L * cfg.JT * cfg.NW);
+        if (cost < best) {
             best = cost;
-            best_id = id;
+            best_id = t.id;
         }
-    };
-    if (uniform && n_f0 >= 32)
-        for (int id : with_runs) consider(id);
-    for (int id : plain) consider(id);
+    }
     return best_id;
 }
 
@@ -2566,6 +2567,8 @@ struct BatchPlan {
     int small_chunk = 8;                   // f0 values per item of the small-bank kernel (5 or 8)
     int local_chunk = 8;                   // and of the local-bank kernel
     std::vector<char> local;               // per run without a tile: the local-bank kernel takes it
+    int bps = 0;                           // summation blocks per row of the split (0: not split)
+    int64_t bsum_len = 0, max_t = 0;       // block sums of all runs; templates of the largest
 };
 
 // Tile-dependent fields of batch run r for `tile` (0-based, -1: direct).
@@ -2591,14 +2594,45 @@ int assign_run_tile(BatchPlan &pl, int r, int tile, const ft_run &R, const doubl
 }
 
 // Work items of batch run r: its tiles, or for the small-bank kernel its
-// (f0 chunk, 64-wide (f1, sky) chunk) pairs.
-int64_t run_items(const BatchPlan &pl, int r)
+// (f0 chunk, 64-wide (f1, sky) chunk) pairs (local-bank kernel: 256-wide), each
+// times the rows of a split.
+int64_t unsplit_items(const BatchPlan &pl, int r)
 {
     const EvalRun &E = pl.runs[r];
     if (pl.tile[r] >= 0) return (int64_t)E.tiles_f0 * E.tiles_f1 * E.tiles_sky;
     if (pl.local[r])
         return (int64_t)((E.n_f0 + pl.local_chunk - 1) / pl.local_chunk) * (((int64_t)E.n_f1 * E.n_sky + LOCAL_JS - 1) / LOCAL_JS);
     return (int64_t)((E.n_f0 + pl.small_chunk - 1) / pl.small_chunk) * (((int64_t)E.n_f1 * E.n_sky + 63) / 64);
+}
+
+int64_t run_items(const BatchPlan &pl, int r) { return unsplit_items(pl, r) * run_rows(pl.runs[r]); }
+
+// Splits a batch over SFT blocks when its items leave the GPU idle: fewer than
+// BATCH_WAVES wavefronts, four rounds of the 4096 that work at a time.  Rows of
+// at least two blocks (each starts a pipeline), about as many as make up that
+// number; the block sums take at most 1 GiB.  64 runs, 1.4e3 items: evaluation
+// 3.3 ms unsplit, 1.3 ms split.
+void plan_batch_split(BatchPlan &pl)
+{
+    constexpr int64_t BATCH_WAVES = 16384;
+    int64_t waves = 0, blocks = 0;
+    pl.bps = 0;
+    pl.bsum_len = 0;
+    pl.max_t = 0;
+    for (size_t r = 0; r < pl.runs.size(); ++r) {
+        const EvalRun &E = pl.runs[r];
+        const int64_t n_t = (int64_t)E.n_f0 * E.n_f1 * E.n_sky, n_blk = (E.n_sft + SUM_BLOCK - 1) / SUM_BLOCK;
+        const int tile = pl.tile[r];
+        if (tile >= 0 && !tile_has_split(tile, false)) return;
+        const int64_t w = unsplit_items(pl, (int)r) * (tile >= 0 ? tile_cfg(tile).NW : pl.local[r] ? LOCAL_JS / 64 : 1);
+        waves += w;
+        blocks += w * n_blk;
+        pl.bsum_len += n_blk * n_t;
+        pl.max_t = std::max(pl.max_t, n_t);
+    }
+    if (waves >= BATCH_WAVES || (double)pl.bsum_len * 4.0 > kGridSplitBytes || pl.runs.size() > 65535) return;
+    const int64_t rows = (BATCH_WAVES + waves - 1) / waves;
+    pl.bps = (int)std::max<int64_t>(2, blocks / waves / rows);
 }
 
 // Whether batch run r (without a tile) suits the local-bank kernel: a uniform
@@ -2700,7 +2734,7 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
         hipStream_t s = i == 0 || n_side == 0 ? st : c->side[(i - 1) % n_side];
         if (L.id < tile_count())
             e = launch_eval_batch(b.runs, b.items + L.off, L.n, pl.group_wtp[L.id], b.counters + L.id,
-                                  std::min(L.n, 2048), tile_cfg(L.id), s);
+                                  std::min(L.n, 2048), tile_cfg(L.id), pl.bps > 0, s);
         else if (L.id == tile_count() + 1)
             e = launch_eval_batch_local(b.runs, b.items + L.off, L.n, pl.local_chunk, b.counters + L.id,
                                         std::min(L.n, 1024), s);
@@ -2713,6 +2747,7 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
         if (ej == hipSuccess) ej = hipStreamWaitEvent(st, c->join_ev[i], 0);
         if (e == hipSuccess) e = ej;
     }
+    if (e == hipSuccess && pl.bps > 0) e = launch_batch_block_sum(b.runs, n_runs, pl.max_t, st);
     if (e == hipSuccess)
         e = launch_select_batch(b.runs, n_runs, c->batch_k, c->batch_cap, b.cand, b.s64, b.out, b.nout, b.maxz, c->d_err,
                                 st);
@@ -2815,7 +2850,7 @@ static ft_status tune_batch(ft_ctx c, BatchPlan &pl, const std::vector<ft_run> &
             e = hipEventRecord(ev[2 * q], c->stream);
             if (e == hipSuccess)
                 e = launch_eval_batch(b.runs, b.items + off[q], n_items, wtp[q], b.counters + q, std::min(n_items, 2048),
-                                      tile_cfg(cls[q].cand[p]), c->stream);
+                                      tile_cfg(cls[q].cand[p]), false, c->stream);
             if (e == hipSuccess) e = hipEventRecord(ev[2 * q + 1], c->stream);
         }
         // the host item list is reused by the next pass
@@ -3145,6 +3180,20 @@ ft_status ft_eval_batch(ft_ctx c, const ft_batch *bt, int32_t use_graph)
         if (pl.tile[r] < 0) pl.local[r] = local_bank(pl, r, runs[r], f0h.data(), f1h.data(), skyh.data(), bt->t_sft);
     pl.small_chunk = choose_small_chunk(pl, false);
     pl.local_chunk = choose_small_chunk(pl, true);
+    plan_batch_split(pl);
+    if (pl.bps > 0 && ensure(&b.bsum, &b.c_bsum, (size_t)pl.bsum_len) != hipSuccess) {
+        (void)hipGetLastError();  // no room: not split
+        pl.bps = 0;
+    }
+    if (pl.bps > 0) {
+        int64_t at = 0;
+        for (EvalRun &E : pl.runs) {
+            E.seg_blocks = pl.bps;
+            E.bsum = b.bsum + at;
+            E.bsum_n = (int64_t)E.n_f0 * E.n_f1 * E.n_sky;
+            at += (E.n_sft + SUM_BLOCK - 1) / SUM_BLOCK * E.bsum_n;
+        }
+    }
     int64_t total_items = 0;
     for (int r = 0; r < n_runs; ++r) total_items += run_items(pl, r);
     if (total_items >= 0x7fffffff) return fail(c, FT_E_UNSUPPORTED, "too many work items");

@@ -707,15 +707,7 @@ __global__ __launch_bounds__(64 * NW, OCC > 0 ? OCC : 1) void eval_grid_kernel(E
 {
     extern __shared__ float win[];  // [2][KS][wtp]
     __shared__ Shared<L, JT, NW, KS> sh;
-    if (SPLIT) {
-        const int b0 = (int)blockIdx.y * r.seg_blocks, k0 = b0 * SUM_BLOCK;
-        r.power_w += (int64_t)k0 * r.n_bins;
-        r.v += 3 * (int64_t)k0;
-        r.dt += k0;
-        if (SKYW) r.arms += 6 * (int64_t)k0;
-        r.bsum += b0 * r.bsum_n;
-        r.n_sft = min(r.n_sft - k0, r.seg_blocks * SUM_BLOCK);
-    }
+    if (SPLIT) take_row(r, (int)blockIdx.y);
     const int64_t nt = (int64_t)r.tiles_f0 * r.tiles_f1 * r.tiles_sky;
     const int64_t full = nt - (nt & 7);
     for (int64_t b0 = blockIdx.x; b0 < nt; b0 += gridDim.x) {
@@ -728,7 +720,9 @@ __global__ __launch_bounds__(64 * NW, OCC > 0 ? OCC : 1) void eval_grid_kernel(E
 // shared by every run of a batch until it is drained; each item is one tile of
 // one run's grid bank.  The queue counter is reset by the launcher's preceding
 // fill kernel, so the sequence can be captured in a HIP graph.
-template <int L, int JT, int NW, int KS, int OCC, bool PIPE>
+//
+// SPLIT: every run is split; an item is tile * rows + row.
+template <int L, int JT, int NW, int KS, int OCC, bool PIPE, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, OCC > 0 ? OCC : 1) void eval_batch_kernel(const EvalRun *runs,
                                                                                 const int2 *items, int n_items,
                                                                                 unsigned *counter)
@@ -743,18 +737,24 @@ __global__ __launch_bounds__(64 * NW, OCC > 0 ? OCC : 1) void eval_batch_kernel(
         const int item = __builtin_amdgcn_readfirstlane(item_sh);
         if (item >= n_items) break;
         const int2 it = items[item];
-        const EvalRun r = runs[__builtin_amdgcn_readfirstlane(it.x)];
-        eval_tile<L, JT, NW, KS, PIPE, false>(r, __builtin_amdgcn_readfirstlane(it.y), win, sh);
+        EvalRun r = runs[__builtin_amdgcn_readfirstlane(it.x)];
+        int tile = __builtin_amdgcn_readfirstlane(it.y);
+        if (SPLIT) {
+            const int rows = run_rows(r);
+            take_row(r, tile % rows);
+            tile /= rows;
+        }
+        eval_tile<L, JT, NW, KS, PIPE, false, SPLIT>(r, tile, win, sh);
     }
 }
 
-template <int L, int JT, int NW, int KS, int OCC, bool PIPE>
+template <int L, int JT, int NW, int KS, int OCC, bool PIPE, bool SPLIT = false>
 hipError_t launch_batch_t(const EvalRun *runs, const int2 *items, int n_items, int max_wtp,
                           unsigned *counter, int grid, hipStream_t s)
 {
     if (n_items <= 0) return hipSuccess;
     const size_t lds = (size_t)2 * KS * max_wtp * sizeof(float);
-    hipLaunchKernelGGL((eval_batch_kernel<L, JT, NW, KS, OCC, PIPE>), dim3((unsigned)grid), dim3(64 * NW), lds,
+    hipLaunchKernelGGL((eval_batch_kernel<L, JT, NW, KS, OCC, PIPE, SPLIT>), dim3((unsigned)grid), dim3(64 * NW), lds,
                        s, runs, items, n_items, counter);
     return hipGetLastError();
 }
@@ -854,6 +854,7 @@ struct TileEntry {
     ProbeLauncher probe_fn;
     Launcher sky_fn;  // sky-dependent weights, or nullptr (no such form of the tile)
     Launcher split_fn = nullptr, sky_split_fn = nullptr;  // split over SFT blocks, likewise
+    BatchLauncher batch_split_fn = nullptr;
 };
 
 #define FT_TILE_X(id, L, JT, NW, KS, SKY)                                                          \
@@ -871,7 +872,8 @@ struct TileEntry {
      &launch_batch_t<L, JT, NW, KS, OCC, false>, sizeof(Shared<L, JT, NW, KS>),                     \
      &launch_probe_t<L, JT, NW, KS, OCC>, SKY ? &launch_t<L, JT, NW, KS, OCC, false, SKY != 0> : nullptr, \
      &launch_t<L, JT, NW, KS, OCC, false, false, true>,                                                 \
-     SKY ? &launch_t<L, JT, NW, KS, OCC, false, SKY != 0, true> : nullptr}
+     SKY ? &launch_t<L, JT, NW, KS, OCC, false, SKY != 0, true> : nullptr,                              \
+     &launch_batch_t<L, JT, NW, KS, OCC, false, true>}
 #define FT_TILE_PX(id, L, JT, NW, KS, OCC, SKY)                                                     \
     {{id, "L" #L "_J" #JT "_W" #NW "_K" #KS "_O" #OCC "_P", L, JT, NW, KS}, &launch_t<L, JT, NW, KS, OCC, true>, \
      &launch_batch_t<L, JT, NW, KS, OCC, true>, sizeof(Shared<L, JT, NW, KS>),                     \
@@ -893,7 +895,7 @@ const TileEntry kTiles[] = {
     FT_TILE(11, 7, 2, 4, 16),
     FT_TILE(12, 9, 2, 4, 16),
     FT_TILE(13, 3, 8, 4, 8),
-    FT_TILE(14, 1, 3, 4, 16),
+    FT_TILE_S(14, 1, 3, 4, 16, 0, "L1_J3_W4_K16", 0),
     FT_TILE(15, 3, 3, 4, 16),
     FT_TILE(16, 5, 3, 4, 8),
     FT_TILE_S(17, 5, 4, 4, 8, 4, "L5_J4_W4_K8_O4", 1),
@@ -950,9 +952,10 @@ hipError_t launch_eval_grid(const EvalRun &run, const TileCfg &cfg, hipStream_t 
 }
 
 hipError_t launch_eval_batch(const EvalRun *runs, const int2 *items, int n_items, int max_wtp,
-                             unsigned *counter, int grid, const TileCfg &cfg, hipStream_t s)
+                             unsigned *counter, int grid, const TileCfg &cfg, bool split, hipStream_t s)
 {
-    return kTiles[cfg.id].batch_fn(runs, items, n_items, max_wtp, counter, grid, s);
+    const BatchLauncher fn = split ? kTiles[cfg.id].batch_split_fn : kTiles[cfg.id].batch_fn;
+    return fn ? fn(runs, items, n_items, max_wtp, counter, grid, s) : hipErrorInvalidValue;
 }
 
 hipError_t launch_lds_probe(const TileCfg &cfg, int n_blocks, int n_step, int wtp, float *out, hipStream_t s)

@@ -336,12 +336,18 @@ __global__ __launch_bounds__(64) void eval_batch_small_kernel(const EvalRun *__r
         const int item = __builtin_amdgcn_readlane((int)got, 0);
         if (item >= n_items) break;
         const int2 it = items[item];
-        const EvalRun r = runs[it.x];
+        EvalRun r = runs[it.x];
+        int chunk = it.y;
+        if (r.seg_blocks > 0) {  // split: chunk * rows + row
+            const int rows = run_rows(r);
+            take_row(r, chunk % rows);
+            chunk /= rows;
+        }
         const int n_js = r.n_f1 * r.n_sky;
         const int n_jsc = (n_js + 63) / 64;
-        const int i0 = (it.y / n_jsc) * SF0;
+        const int i0 = (chunk / n_jsc) * SF0;
         const int n_i = min(SF0, r.n_f0 - i0);
-        const int js_raw = (it.y % n_jsc) * 64 + lane;
+        const int js_raw = (chunk % n_jsc) * 64 + lane;
         const bool live = js_raw < n_js;
         const int js = live ? js_raw : n_js - 1;
         const int j = js % r.n_f1, s = js / r.n_f1;
@@ -384,7 +390,14 @@ __global__ __launch_bounds__(64) void eval_batch_small_kernel(const EvalRun *__r
                 small_add(vb, acc);
             }
             if (k < ke) small_add(va, acc);  // odd tail: k = n - 1
-            if (r.sum_mode == FT_SUM_BLOCKED) {
+            if (r.bsum) {
+                float *out = r.bsum + kb / SUM_BLOCK * r.bsum_n + (int64_t)js * r.n_f0 + i0;
+#pragma unroll
+                for (int l = 0; l < SF0; ++l) {
+                    if (live && l < n_i) out[l] = acc[l];
+                    acc[l] = 0.f;
+                }
+            } else if (r.sum_mode == FT_SUM_BLOCKED) {
 #pragma unroll
                 for (int l = 0; l < SF0; ++l) {
                     tot[l] += (double)acc[l];
@@ -393,7 +406,7 @@ __global__ __launch_bounds__(64) void eval_batch_small_kernel(const EvalRun *__r
             }
         }
         if (bad && live) atomicOr(r.err, ERR_RANGE);
-        if (live) {
+        if (live && !r.bsum) {
             float *out = r.stats + (int64_t)js * r.n_f0 + i0;
 #pragma unroll
             for (int l = 0; l < SF0; ++l)
@@ -655,6 +668,26 @@ __global__ __launch_bounds__(256) void block_sum_kernel(const float *bsum, int64
         for (; b < n_blk; ++b) tot += (double)bsum[(int64_t)b * n + t];
         stats[order ? order[t] : t] = (float)tot;
     }
+}
+
+// The same for batch runs, blockIdx.y the run.
+__global__ __launch_bounds__(256) void batch_block_sum_kernel(const EvalRun *__restrict__ runs)
+{
+    const EvalRun r = runs[blockIdx.y];
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (!r.bsum || t >= r.bsum_n) return;
+    const int n_blk = (r.n_sft + SUM_BLOCK - 1) / SUM_BLOCK;
+    double tot = 0.0;
+    int b = 0;
+    for (; b + 8 <= n_blk; b += 8) {
+        float x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = r.bsum[(int64_t)(b + i) * r.bsum_n + t];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) tot += (double)x[i];
+    }
+    for (; b < n_blk; ++b) tot += (double)r.bsum[(int64_t)b * r.bsum_n + t];
+    r.stats[t] = (float)tot;
 }
 
 // Largest error of the hardware cosine over every float x in [0, 1]:
@@ -929,6 +962,12 @@ hipError_t launch_block_sum(const float *bsum, int64_t n, int n_blk, float *stat
 {
     hipLaunchKernelGGL(block_sum_kernel, dim3(grid_for(n, 256, (1u << 16))), dim3(256), 0, s, bsum, n, n_blk,
                        stats, order);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_block_sum(const EvalRun *runs, int n_runs, int64_t max_t, hipStream_t s)
+{
+    hipLaunchKernelGGL(batch_block_sum_kernel, dim3((unsigned)((max_t + 255) / 256), (unsigned)n_runs), dim3(256), 0, s, runs);
     return hipGetLastError();
 }
 

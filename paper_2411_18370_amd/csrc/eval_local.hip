@@ -87,9 +87,14 @@ __global__ __launch_bounds__(LOCAL_THREADS, 4) void eval_batch_local_kernel(cons
         const int item = __builtin_amdgcn_readfirstlane(sh.item);
         if (item >= n_items) return;
         const int2 it = items[item];
-        const EvalRun r = runs[__builtin_amdgcn_readfirstlane(it.x)];
+        EvalRun r = runs[__builtin_amdgcn_readfirstlane(it.x)];
+        int chunk = __builtin_amdgcn_readfirstlane(it.y);
+        if (r.seg_blocks > 0) {  // split: chunk * rows + row
+            const int rows = run_rows(r);
+            take_row(r, chunk % rows);
+            chunk /= rows;
+        }
         const int n_js = r.n_f1 * r.n_sky, n_jsc = (n_js + LOCAL_THREADS - 1) / LOCAL_THREADS;
-        const int chunk = __builtin_amdgcn_readfirstlane(it.y);
         const int i0 = chunk / n_jsc * L, n_i = min(L, r.n_f0 - i0);
         const int js_raw = chunk % n_jsc * LOCAL_THREADS + tid;
         const bool live = js_raw < n_js;
@@ -266,7 +271,14 @@ __global__ __launch_bounds__(LOCAL_THREADS, 4) void eval_batch_local_kernel(cons
                         }
                     }
                 }
-                if (r.sum_mode == FT_SUM_BLOCKED) {
+                if (r.bsum) {
+                    float *out = r.bsum + (int64_t)b * r.bsum_n + (int64_t)js * r.n_f0 + i0;
+#pragma unroll
+                    for (int l = 0; l < L; ++l) {
+                        if (live && l < n_i) out[l] = acc[l];
+                        acc[l] = 0.f;
+                    }
+                } else if (r.sum_mode == FT_SUM_BLOCKED) {
 #pragma unroll
                     for (int l = 0; l < L; ++l) {
                         tot[l] += (double)acc[l];
@@ -278,7 +290,7 @@ __global__ __launch_bounds__(LOCAL_THREADS, 4) void eval_batch_local_kernel(cons
             lo1 = lo2;
         }
         if (bad && live) atomicOr(r.err, ERR_RANGE);
-        if (live) {
+        if (live && !r.bsum) {
             float *out = r.stats + (int64_t)js * r.n_f0 + i0;
 #pragma unroll
             for (int l = 0; l < L; ++l)

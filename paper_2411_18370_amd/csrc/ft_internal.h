@@ -271,6 +271,24 @@ struct EvalRun {
     int64_t bsum_n = 0;
 };
 
+// Row `row` of a run split over SFT blocks: its SFTs alone, block sums in place.
+__device__ __forceinline__ void take_row(EvalRun &r, int row)
+{
+    const int b0 = row * r.seg_blocks, k0 = b0 * SUM_BLOCK;
+    r.power_w += (int64_t)k0 * r.n_bins;
+    r.v += 3 * (int64_t)k0;
+    r.dt += k0;
+    if (r.arms) r.arms += 6 * (int64_t)k0;
+    r.bsum += b0 * r.bsum_n;
+    r.n_sft = min(r.n_sft - k0, r.seg_blocks * SUM_BLOCK);
+}
+__host__ __device__ inline int run_rows(const EvalRun &r)
+{
+    if (r.seg_blocks == 0) return 1;
+    const int n_blk = (r.n_sft + SUM_BLOCK - 1) / SUM_BLOCK;
+    return (n_blk + r.seg_blocks - 1) / r.seg_blocks;
+}
+
 // Tile configurations of the grid kernel.
 struct TileCfg {
     int id;
@@ -292,7 +310,9 @@ int tile_companion(int id, int jt);
 hipError_t launch_eval_grid(const EvalRun &run, const TileCfg &cfg, hipStream_t s);
 // items[i] = (run, tile within the run); counter must be zero at launch.
 hipError_t launch_eval_batch(const EvalRun *runs, const int2 *items, int n_items, int max_wtp,
-                             unsigned *counter, int grid, const TileCfg &cfg, hipStream_t s);
+                             unsigned *counter, int grid, const TileCfg &cfg, bool split, hipStream_t s);
+// The statistics of n_runs split runs from their block sums (max_t: templates of the largest).
+hipError_t launch_batch_block_sum(const EvalRun *runs, int n_runs, int64_t max_t, hipStream_t s);
 // Batch runs outside the tile kernel (one wavefront per item): items[i] =
 // (run, chunk), chunk = f0 chunk * ceil(n_f1 n_sky / 64) + (f1, sky) chunk,
 // f0 chunks of f0_chunk values (5 or 8; one choice per batch); counter must be
