@@ -57,6 +57,34 @@ struct LocalShared {
     int item;
 };
 
+// f over the lanes of a wave (f(x, x) = x), by moves between lanes of the vector
+// unit: a shuffle goes through LDS, 130 cycles each in a chain of six.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int lane_move(int x)
+{
+    return __builtin_amdgcn_update_dpp(x, x, CTRL, ROWS, 0xf, false);
+}
+template <typename F>
+__device__ __forceinline__ int wave_reduce(int x, F f)
+{
+    x = f(x, lane_move<0x111, 0xf>(x));  // row_shr 1, 2, 4, 8: rows of 16
+    x = f(x, lane_move<0x112, 0xf>(x));
+    x = f(x, lane_move<0x114, 0xf>(x));
+    x = f(x, lane_move<0x118, 0xf>(x));
+    x = f(x, lane_move<0x142, 0xa>(x));  // row_bcast 15 and 31
+    x = f(x, lane_move<0x143, 0xc>(x));
+    return __builtin_amdgcn_readlane(x, 63);
+}
+__device__ __forceinline__ int wave_min(int x) { return wave_reduce(x, [](int a, int b) { return min(a, b); }); }
+__device__ __forceinline__ int wave_max(int x) { return wave_reduce(x, [](int a, int b) { return max(a, b); }); }
+// of floats that are not negative: their bits order like them
+__device__ __forceinline__ float wave_maxf(float x) { return __int_as_float(wave_max(__float_as_int(x))); }
+
+__device__ __forceinline__ double read_lane(double x, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
 // The canonical bins of one step, read from the table.
 template <int L>
 __device__ __attribute__((noinline)) bool local_canonical(const float *row, const double *f0, const double *v, double dt,
@@ -120,17 +148,13 @@ __global__ __launch_bounds__(LOCAL_THREADS, 4) void eval_batch_local_kernel(cons
             if (wave != 0 || b >= n_blk) return;
             double mid[4];
 #pragma unroll
-            for (int d = 0; d < 4; ++d) mid[d] = __shfl(raw[d], SUM_BLOCK / 2, 64);
+            for (int d = 0; d < 4; ++d) mid[d] = read_lane(raw[d], SUM_BLOCK / 2);
             f32x4 c;
             c[0] = (float)(raw[3] - mid[3]);
 #pragma unroll
             for (int d = 0; d < 3; ++d) c[d + 1] = (float)(raw[d] - mid[d]);
-            float dv = fabsf(c[1]) + fabsf(c[2]) + fabsf(c[3]), ds = fabsf(c[0]);
-#pragma unroll
-            for (int o = SUM_BLOCK / 2; o > 0; o >>= 1) {
-                dv = fmaxf(dv, __shfl_xor(dv, o, 64));
-                ds = fmaxf(ds, __shfl_xor(ds, o, 64));
-            }
+            const bool in = tid < SUM_BLOCK;
+            const float dv = wave_maxf(in ? fabsf(c[1]) + fabsf(c[2]) + fabsf(c[3]) : 0.f), ds = wave_maxf(in ? fabsf(c[0]) : 0.f);
             if (tid < SUM_BLOCK) sh.par[b % RING][tid] = c;
             if (tid == 0) {
                 LocalBlock &q = sh.blk[b % RING];
@@ -147,12 +171,7 @@ __global__ __launch_bounds__(LOCAL_THREADS, 4) void eval_batch_local_kernel(cons
             const LocalBlock &q = sh.blk[b % RING];
             const double g = 1.0 + fma(nz, q.v[2], fma(ny, q.v[1], nx * q.v[0]));
             const double aT = fma(f1, q.tau, f0) * T, w = (aT * (double)q.dv + fabs(f1) * (double)q.ds * T) * 1.001;
-            int lo = (int)floor(fma(aT, g, 0.5 - w)) - 1, hi = (int)floor(fma(aT + span, g, 0.5 + w)) + 1;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                lo = min(lo, __shfl_xor(lo, o, 64));
-                hi = max(hi, __shfl_xor(hi, o, 64));
-            }
+            const int lo = wave_min((int)floor(fma(aT, g, 0.5 - w)) - 1), hi = wave_max((int)floor(fma(aT + span, g, 0.5 + w)) + 1);
             if (lane == 0) {
                 sh.lo[b & 1][wave] = lo;
                 sh.hi[b & 1][wave] = hi;
@@ -237,7 +256,7 @@ __global__ __launch_bounds__(LOCAL_THREADS, 4) void eval_batch_local_kernel(cons
 #pragma unroll 1
                     for (int k = 0; k < len; k += 4) {
                         float v[4][L];
-                        uint64_t fail[4], any = 0;
+                        float fr[4];
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {  // rows past the last SFT repeat it
                             const f32x4 c = sh.par[b % RING][k + i];
@@ -245,16 +264,15 @@ __global__ __launch_bounds__(LOCAL_THREADS, 4) void eval_batch_local_kernel(cons
                             x = __builtin_fmaf(c[1], gx, x);
                             x = __builtin_fmaf(c[2], gy, x);
                             x = __builtin_fmaf(c[3], gz, x);
-                            fail[i] = __builtin_amdgcn_ballot_w64(!(__builtin_amdgcn_fractf(x) < w));
-                            any |= fail[i];
+                            fr[i] = __builtin_amdgcn_fractf(x);
                             const float *at = wl + (k + i) * LOCAL_W + (int)x;
 #pragma unroll
                             for (int l = 0; l < L; ++l) v[i][l] = at[l];
                         }
-                        if (any) {
+                        if (__builtin_amdgcn_ballot_w64(!(fmaxf(fmaxf(fr[0], fr[1]), fmaxf(fr[2], fr[3])) < w)) != 0) {
 #pragma unroll
                             for (int i = 0; i < 4; ++i)
-                                if (fail[i]) {
+                                if (__builtin_amdgcn_ballot_w64(!(fr[i] < w)) != 0) {
                                     const int q = min(k0 + k + i, r.n_sft - 1);
                                     const auto *vk = as_const(r.v + 3 * (int64_t)q);
                                     const double gk = doppler_factor(vk[0], vk[1], vk[2], nx, ny, nz), ck = f1 * as_const(r.dt)[q];
