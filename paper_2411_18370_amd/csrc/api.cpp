@@ -195,6 +195,11 @@ struct ft_ctx_s {
 
     // last evaluation
     bool have_eval = false;
+    // the last evaluation's flags and toplists in mapped host memory (valid once
+    // the stream is done); delivered is cleared by whatever else uses the flags
+    char *h_top = nullptr, *h_top_dev = nullptr;
+    size_t cap_h_top = 0;
+    bool delivered = false;
     EvalRun last_run{};
     bool last_grid = true;
     int last_k = 0, last_nsub = 0;
@@ -295,13 +300,8 @@ hipError_t fetch(std::vector<T> &dst, const T *src, size_t count)
 
 bool is_finite(double x) { return std::isfinite(x); }
 
-ft_status sync_and_check(ft_ctx c)
+ft_status check_flags(ft_ctx c, uint32_t flags)
 {
-    hipError_t e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, "stream synchronize");
-    uint32_t flags = 0;
-    e = hipMemcpy(&flags, c->d_err, sizeof flags, hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hip_fail(c, e, "read error flags");
     if (flags & ERR_RANGE)
         return fail(c, FT_E_RANGE, "a template track left the SFT table [first_bin, first_bin + n_bins)");
     if (flags & ERR_WINDOW)
@@ -309,6 +309,18 @@ ft_status sync_and_check(ft_ctx c)
     if (flags & ERR_BAD_POWER)
         return fail(c, FT_E_INVALID, "power table or weights hold a non-finite or negative value");
     return FT_OK;
+}
+
+// Waits for the stream and reads the error flags, into *seen too.
+ft_status sync_and_check(ft_ctx c, uint32_t *seen = nullptr)
+{
+    hipError_t e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "stream synchronize");
+    uint32_t flags = 0;
+    e = hipMemcpy(&flags, c->d_err, sizeof flags, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return hip_fail(c, e, "read error flags");
+    if (seen) *seen = flags;
+    return check_flags(c, flags);
 }
 
 // Doppler-coherent visiting order of the sky points: bands of equal height in
@@ -657,6 +669,7 @@ void ft_destroy(ft_ctx c)
     release(&c->d_dt, &c->cap_dt);
     release(&c->d_mu_sigma, nullptr);
     release(&c->d_err, nullptr);
+    if (c->h_top) (void)hipHostFree(c->h_top);
     release(&c->d_f0, &c->cap_f0);
     release(&c->d_bin, &c->cap_bin);
     release(&c->d_sincos, &c->cap_sincos);
@@ -782,6 +795,7 @@ ft_status ft_set_sfts(ft_ctx c, int32_t n_det, const int32_t *n_sft, const doubl
         e = hipMemcpyAsync(c->d_weight, weight, (size_t)total * sizeof(float), hipMemcpyDefault, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "copy SFT data");
     // Validate the table on the device (it may be large and device-resident).
+    c->delivered = false;
     if ((e = launch_fill_u32(c->d_err, 0u, 1, c->stream)) != hipSuccess) return hip_fail(c, e, "clear flags");
     if ((e = launch_check_table(c->d_power, weight ? c->d_weight : nullptr, total, n_bins, c->d_err,
                                 c->stream)) != hipSuccess)
@@ -1958,6 +1972,34 @@ static hipError_t launch_grid(const EvalRun &run, int tile, const WindowPlan *ta
     return e == hipSuccess ? grid_block_sum(run, s) : e;
 }
 
+// Delivers the selection's results to mapped host memory, up to 8 MiB of them
+// (longer toplists, and contexts without room for them, are copied on reading).
+static hipError_t deliver(ft_ctx c, int n_seg, int k, const SelectBufs &sb)
+{
+    constexpr size_t kMost = size_t(8) << 20;
+    const size_t bytes = deliver_entries_at(n_seg) + (size_t)n_seg * k * sizeof(ft_candidate);
+    if (bytes > kMost) return hipSuccess;
+    if (bytes > c->cap_h_top) {
+        hipError_t e = hipStreamSynchronize(c->stream);  // an earlier evaluation may still be writing
+        if (e != hipSuccess) return e;
+        if (c->h_top) (void)hipHostFree(c->h_top);
+        c->h_top = nullptr;
+        c->cap_h_top = 0;
+        const size_t want = std::min(std::max(bytes + bytes / 4, size_t(1) << 16), kMost);
+        if (hipHostMalloc((void **)&c->h_top, want, hipHostMallocMapped) != hipSuccess ||
+            hipHostGetDevicePointer((void **)&c->h_top_dev, c->h_top, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            if (c->h_top) (void)hipHostFree(c->h_top);
+            c->h_top = nullptr;
+            return hipSuccess;
+        }
+        c->cap_h_top = want;
+    }
+    const hipError_t e = launch_deliver(c->d_err, n_seg, k, sb, c->h_top_dev, c->stream);
+    c->delivered = e == hipSuccess;
+    return e;
+}
+
 static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile, int64_t n_t, int64_t n_seg_map,
                                     const ft_eval_opts *opts, const std::vector<double> &edges, float *stats,
                                     const WindowPlan *tail)
@@ -2002,6 +2044,8 @@ static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile,
     if (e == hipSuccess) e = launch_select(run, grid, n_seg, k, rel_err, sb, c->stream);
     if (e == hipSuccess) e = launch_rescore_rank(run, grid, n_seg, k, sb, c->stream);
     if (e == hipSuccess) e = hipEventRecord(c->ev[2], c->stream);
+    c->delivered = false;
+    if (e == hipSuccess) e = deliver(c, n_seg, k, sb);
     if (e == hipSuccess && stats)
         e = hipMemcpyAsync(stats, c->d_stats, (size_t)n_t * sizeof(float), hipMemcpyDefault, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "launch evaluation");
@@ -2171,6 +2215,7 @@ ft_status ft_eval_binary_boxes(ft_ctx c, const ft_binary_region *reg, uint64_t s
     st = plan_binary(c, run, bank);
     if (st != FT_OK) return st;
     c->have_eval = false;  // the bank and statistics are replaced
+    c->delivered = false;
     const double N = (double)c->n_sft;
     const double rel_err = opts->sum_mode == FT_SUM_BLOCKED ? 40.0 * std::ldexp(1.0, -24) + 4.0 * N * std::ldexp(1.0, -53)
                                                             : (N + 8.0) * std::ldexp(1.0, -24) + 4.0 * N * std::ldexp(1.0, -53);
@@ -2208,11 +2253,18 @@ ft_status ft_sync(ft_ctx c)
 {
     if (!c) return FT_E_INVALID;
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, FT_E_DEVICE, "hipSetDevice");
-    ft_status st = sync_and_check(c);
+    uint32_t flags = 0;
+    ft_status st;
+    if (c->have_eval && c->delivered) {
+        const hipError_t e = hipStreamSynchronize(c->stream);
+        if (e != hipSuccess) return hip_fail(c, e, "stream synchronize");
+        flags = ((const DeliverHead *)c->h_top)->flags;
+        st = check_flags(c, flags);
+    } else {
+        st = sync_and_check(c, &flags);
+    }
     if (st != FT_OK || !c->have_eval) return st;
     // Grow the candidate buffer and redo the compaction if it overflowed.
-    uint32_t flags = 0;
-    hipMemcpy(&flags, c->d_err, sizeof flags, hipMemcpyDeviceToHost);
     if (flags & ERR_CAND_OVERFLOW) {
         uint32_t total = 0;
         hipMemcpy(&total, c->d_off + c->last_nsub, sizeof total, hipMemcpyDeviceToHost);
@@ -2231,9 +2283,10 @@ ft_status ft_sync(ft_ctx c)
         if (e == hipSuccess) e = launch_select(c->last_run, c->last_grid, c->last_nsub, c->last_k, c->last_rel_err, sb, c->stream);
         if (e == hipSuccess) e = launch_rescore_rank(c->last_run, c->last_grid, c->last_nsub, c->last_k, sb, c->stream);
         if (e != hipSuccess) return hip_fail(c, e, "relaunch selection");
-        st = sync_and_check(c);
+        c->delivered = false;
+        if (deliver(c, c->last_nsub, c->last_k, sb) != hipSuccess) return fail(c, FT_E_DEVICE, "relaunch selection");
+        st = sync_and_check(c, &flags);
         if (st != FT_OK) return st;
-        hipMemcpy(&flags, c->d_err, sizeof flags, hipMemcpyDeviceToHost);
         if (flags & ERR_CAND_OVERFLOW) return fail(c, FT_E_INTERNAL, "candidate buffer overflow after growth");
     }
     return FT_OK;
@@ -2249,6 +2302,16 @@ ft_status ft_toplist(ft_ctx c, int32_t sub, ft_candidate *out, int32_t *n_out)
     ft_status st = ft_sync(c);
     if (st != FT_OK) return st;
     int32_t n = 0;
+    hipPointerAttribute_t at{};
+    if (c->delivered && (hipPointerGetAttributes(&at, out) != hipSuccess || at.type != hipMemoryTypeDevice)) {
+        (void)hipGetLastError();  // ordinary host memory has no attributes
+        n = ((const int32_t *)(c->h_top + sizeof(DeliverHead)))[sub];
+        if (n > 0)
+            std::memcpy(out, c->h_top + deliver_entries_at(c->last_nsub) + (size_t)sub * c->last_k * sizeof(ft_candidate),
+                        (size_t)n * sizeof(ft_candidate));
+        *n_out = n;
+        return FT_OK;
+    }
     hipError_t e = hipMemcpy(&n, c->d_nout + sub, sizeof n, hipMemcpyDeviceToHost);
     if (e == hipSuccess && n > 0)
         e = hipMemcpy(out, c->d_out + (size_t)sub * c->last_k, (size_t)n * sizeof(ft_candidate), hipMemcpyDefault);
@@ -2698,6 +2761,7 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
 {
     auto &b = c->bb;
     const int n_runs = (int)pl.runs.size();
+    c->delivered = false;
     hipError_t e = launch_fill_u32(c->d_err, 0u, 1, st);
     if (e == hipSuccess) e = launch_fill_u32(b.counters, 0u, tile_count() + 2, st);
     if (e == hipSuccess)
@@ -3272,6 +3336,7 @@ ft_status ft_batch_replay(ft_ctx c)
     c->err.clear();
     if (!c->have_batch || !c->graph_exec) return fail(c, FT_E_STATE, "no captured batch to replay");
     hipError_t e = hipEventRecord(c->bev[0], c->stream);
+    c->delivered = false;
     if (e == hipSuccess) e = hipGraphLaunch(c->graph_exec, c->stream);
     if (e == hipSuccess) e = hipEventRecord(c->bev[1], c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "replay graph");
@@ -3285,11 +3350,9 @@ ft_status ft_batch_toplist(ft_ctx c, int32_t run, ft_candidate *out, int32_t *n_
     if (!c->have_batch) return fail(c, FT_E_STATE, "no batch evaluated");
     if (run < 0 || run >= c->batch_runs) return fail(c, FT_E_INVALID, "run %d out of range", run);
     if (!out || !n_out) return fail(c, FT_E_INVALID, "out and n_out must be non-null");
-    ft_status st = sync_and_check(c);
-    if (st != FT_OK) return st;
     uint32_t flags = 0;
-    if (hipMemcpy(&flags, c->d_err, sizeof flags, hipMemcpyDeviceToHost) != hipSuccess)
-        return fail(c, FT_E_DEVICE, "read flags");
+    ft_status st = sync_and_check(c, &flags);
+    if (st != FT_OK) return st;
     if (flags & ERR_CAND_OVERFLOW)
         return fail(c, FT_E_UNSUPPORTED, "a run has more tied toplist candidates than the batch buffer holds");
     int32_t n = 0;
@@ -3313,11 +3376,9 @@ ft_status ft_batch_labels(ft_ctx c, double tau, uint8_t *labels, double *max_z)
     if (e == hipSuccess && max_z)
         e = hipMemcpyAsync(max_z, c->bb.maxz, (size_t)c->batch_runs * sizeof(double), hipMemcpyDefault, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "labels");
-    ft_status st = sync_and_check(c);
-    if (st != FT_OK) return st;
     uint32_t flags = 0;
-    if (hipMemcpy(&flags, c->d_err, sizeof flags, hipMemcpyDeviceToHost) != hipSuccess)
-        return fail(c, FT_E_DEVICE, "read flags");
+    ft_status st = sync_and_check(c, &flags);
+    if (st != FT_OK) return st;
     if (flags & ERR_CAND_OVERFLOW)
         return fail(c, FT_E_UNSUPPORTED, "a run has more tied toplist candidates than the batch buffer holds");
     return FT_OK;
