@@ -170,35 +170,6 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
-// Sequential FP64 sum of u_k ab_k(n) over the SFTs k = 0 .. n_sft-1 in SFT order,
-// by one wavefront: lanes form 256 terms at a time into buf[256] (the wave's own
-// LDS slice) and lane 0 adds them one after another.  Every lane returns the sum.
-// This is the normaliser of the all-sky weights w_k = u_k (ab_k / W).
-template <typename ArmPtr>
-__device__ __forceinline__ double sky_norm_sum(ArmPtr arms, const float *weight, int n_sft, double nx, double ny,
-                                               double nz, double *buf, int lane)
-{
-    double acc = 0.0;
-    for (int k0 = 0; k0 < n_sft; k0 += 256) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int k = k0 + 64 * j + lane;
-            double term = 0.0;
-            if (k < n_sft) term = (weight ? (double)weight[k] : 1.0) * sky_ab(arms + 6 * (int64_t)k, nx, ny, nz);
-            buf[64 * j + lane] = term;
-        }
-        wave_lds_sync();
-        if (lane == 0) {
-            const int m = min(256, n_sft - k0);
-            for (int q = 0; q < m; ++q) acc = acc + buf[q];
-        }
-        wave_lds_sync();
-    }
-    const int lo = __builtin_amdgcn_readfirstlane(__double2loint(acc));
-    const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(acc));
-    return __hiloint2double(hi, lo);
-}
-
 // Number-count threshold (Eq. number_count): P > 3.2 as real numbers, which for
 // FP32 P is P >= 3.2f (the float nearest 3.2 lies above it).
 constexpr float NC_THRESHOLD_F = 3.2f;
