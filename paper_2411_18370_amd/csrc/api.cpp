@@ -123,6 +123,9 @@ struct ft_ctx_s {
     struct ListBounds {
         double f0_lo = 0.0, f0_hi = 0.0, f1_abs = 0.0, dt_lo = 0.0, dt_hi = 0.0, t_ref = 0.0;
     } list_bounds;
+    double *d_f0_new = nullptr, *d_f1_new = nullptr, *d_sky_new = nullptr;  // a list bank being checked
+    size_t cap_f0_new = 0, cap_f1_new = 0, cap_sky_new = 0, cap_list_check = 0;
+    ListCheck *d_list_check = nullptr;
     int32_t *d_order = nullptr;
     uint32_t *d_order_cnt = nullptr;
     size_t cap_order = 0, cap_order_cnt = 0;
@@ -684,6 +687,10 @@ void ft_destroy(ft_ctx c)
     release(&c->d_edges, &c->cap_edges);
     release(&c->d_stats, &c->cap_stats);
     release(&c->d_bsum, &c->cap_bsum);
+    release(&c->d_f0_new, &c->cap_f0_new);
+    release(&c->d_f1_new, &c->cap_f1_new);
+    release(&c->d_sky_new, &c->cap_sky_new);
+    release(&c->d_list_check, &c->cap_list_check);
     release(&c->d_order, &c->cap_order);
     release(&c->d_order_cnt, &c->cap_order_cnt);
     release(&c->d_seg_mask, &c->cap_seg_mask);
@@ -1160,6 +1167,44 @@ static bool binary_range_ok(ft_ctx c, double f0_lo, double f0_hi, double aw_max)
     return lo >= (double)c->first_bin && hi < (double)c->first_bin + (double)c->n_bins;
 }
 
+constexpr int64_t kListDevice = 1024;  // templates
+
+// Copies a list bank's arrays beside the current bank's and checks them there,
+// with the host checks' order and messages.
+static ft_status check_list(ft_ctx c, const ft_bank *bank, double dt_min, double dt_max, ListCheck &r)
+{
+    const size_t n = (size_t)bank->n_list;
+    hipError_t e;
+    if ((e = ensure(&c->d_f0_new, &c->cap_f0_new, n)) != hipSuccess ||
+        (e = ensure(&c->d_f1_new, &c->cap_f1_new, n)) != hipSuccess ||
+        (e = ensure(&c->d_sky_new, &c->cap_sky_new, n * 3)) != hipSuccess ||
+        (e = ensure(&c->d_list_check, &c->cap_list_check, 1)) != hipSuccess)
+        return hip_fail(c, e, "alloc bank");
+    // work on other streams that produces the arrays ends before a synchronous
+    // copy of them: one element each orders the copies on our stream after it
+    double one;
+    for (const double *p : {bank->f0, bank->sky_xyz, bank->f1})
+        if (hipMemcpy(&one, p, sizeof one, hipMemcpyDefault) != hipSuccess)
+            return fail(c, FT_E_INVALID, "cannot read the bank arrays");
+    if (hipMemcpyAsync(c->d_f0_new, bank->f0, n * sizeof(double), hipMemcpyDefault, c->stream) != hipSuccess ||
+        hipMemcpyAsync(c->d_sky_new, bank->sky_xyz, n * 3 * sizeof(double), hipMemcpyDefault, c->stream) != hipSuccess ||
+        hipMemcpyAsync(c->d_f1_new, bank->f1, n * sizeof(double), hipMemcpyDefault, c->stream) != hipSuccess)
+        return fail(c, FT_E_INVALID, "cannot read the bank arrays");
+    e = launch_list_check(c->d_f0_new, c->d_f1_new, c->d_sky_new, (int64_t)n, dt_min, dt_max, c->d_list_check, c->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(&r, c->d_list_check, sizeof r, hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "check bank");
+    if (r.bad_f0 != ~0ull) return fail(c, FT_E_INVALID, "f0 must be finite and > 0");
+    if (r.bad_f1 != ~0ull) return fail(c, FT_E_INVALID, "f1 must be finite");
+    if (r.bad_sky != ~0ull) {
+        if (!(r.bad_sky & 1)) return fail(c, FT_E_INVALID, "sky holds a non-finite value");
+        return fail(c, FT_E_INVALID, "sky vectors must have unit norm (template %lld)", (long long)(r.bad_sky >> 1));
+    }
+    if (r.bad_track != ~0ull)
+        return fail(c, FT_E_INVALID, "f0 + f1*(t - t_ref) must stay > 0 (template %lld)", (long long)r.bad_track);
+    return FT_OK;
+}
+
 static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalRun &run,
                               bool &grid, int64_t &n_t)
 {
@@ -1189,9 +1234,15 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
     if (grid && (n_t / ns / n1 != n0 || n_t > (1LL << 40)))
         return fail(c, FT_E_UNSUPPORTED, "more than 2^40 templates in one call");
     hipError_t e;
-    if (fetch(c->f0_h, bank->f0, (size_t)n0) != hipSuccess || fetch(c->sky_h, bank->sky_xyz, (size_t)ns * 3) != hipSuccess)
+    // Lists are checked on the device from kListDevice templates: host reading,
+    // checking and copying take 7 ns a template (calls of 2e5: 2.12 ms, device
+    // 0.87 ms; of 2000: 225 us, device 198 us).
+    const bool on_device = !grid && !binary && n0 >= kListDevice;
+    if (on_device) {
+    } else if (fetch(c->f0_h, bank->f0, (size_t)n0) != hipSuccess || fetch(c->sky_h, bank->sky_xyz, (size_t)ns * 3) != hipSuccess)
         return fail(c, FT_E_INVALID, "cannot read the bank arrays");
-    if (binary) {
+    if (on_device) {
+    } else if (binary) {
         c->f1_h.assign((size_t)n1, 0.0);  // no spindown in the binary model
         if (fetch(c->ap_h, bank->ap, (size_t)n0) != hipSuccess || fetch(c->omega_h, bank->omega, (size_t)n0) != hipSuccess ||
             fetch(c->phib_h, bank->phib, (size_t)n0) != hipSuccess)
@@ -1206,6 +1257,15 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
         dt_max = std::max(dt_max, t - t_ref);
     }
     double f0_min = 1e300, f0_max = -1e300, f1_min = 1e300, f1_max = -1e300;
+    if (on_device) {
+        ListCheck r;
+        ft_status st = check_list(c, bank, dt_min, dt_max, r);
+        if (st != FT_OK) return st;
+        f0_min = from_ordered_bits(r.f0_lo);
+        f0_max = from_ordered_bits(r.f0_hi);
+        f1_min = from_ordered_bits(r.f1_lo);
+        f1_max = from_ordered_bits(r.f1_hi);
+    } else
     for (int64_t i = 0; i < n0; ++i) {
         const double f = c->f0_h[i];
         if (!is_finite(f) || !(f > 0.0)) return fail(c, FT_E_INVALID, "f0 must be finite and > 0");
@@ -1213,13 +1273,13 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
         f0_min = std::min(f0_min, f);
         f0_max = std::max(f0_max, f);
     }
-    for (int64_t j = 0; j < n1; ++j) {
+    for (int64_t j = 0; j < n1 && !on_device; ++j) {
         const double f = c->f1_h[j];
         if (!is_finite(f)) return fail(c, FT_E_INVALID, "f1 must be finite");
         f1_min = std::min(f1_min, f);
         f1_max = std::max(f1_max, f);
     }
-    for (int64_t s = 0; s < ns; ++s) {
+    for (int64_t s = 0; s < ns && !on_device; ++s) {
         const double x = c->sky_h[3 * s], y = c->sky_h[3 * s + 1], z = c->sky_h[3 * s + 2];
         if (!is_finite(x) || !is_finite(y) || !is_finite(z)) return fail(c, FT_E_INVALID, "sky holds a non-finite value");
         if (std::fabs(std::sqrt(x * x + y * y + z * z) - 1.0) > 1e-12)
@@ -1234,7 +1294,7 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
     }
     if (grid) {
         if (!(f0_min + c_min > 0.0)) return fail(c, FT_E_INVALID, "f0 + f1*(t - t_ref) must stay > 0");
-    } else {
+    } else if (!on_device) {
         for (int64_t t = 0; t < n0; ++t) {
             const double a = c->f0_h[t] + std::min(c->f1_h[t] * dt_min, c->f1_h[t] * dt_max);
             if (!(a > 0.0)) return fail(c, FT_E_INVALID, "f0 + f1*(t - t_ref) must stay > 0 (template %lld)", (long long)t);
@@ -1277,11 +1337,19 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
     }
 
     // upload
-    if ((e = ensure(&c->d_f0, &c->cap_f0, (size_t)n0)) != hipSuccess ||
-        (e = ensure(&c->d_f1, &c->cap_f1, (size_t)n1)) != hipSuccess ||
-        (e = ensure(&c->d_sky, &c->cap_sky, (size_t)ns * 3)) != hipSuccess ||
+    if ((!on_device && ((e = ensure(&c->d_f0, &c->cap_f0, (size_t)n0)) != hipSuccess ||
+                        (e = ensure(&c->d_f1, &c->cap_f1, (size_t)n1)) != hipSuccess ||
+                        (e = ensure(&c->d_sky, &c->cap_sky, (size_t)ns * 3)) != hipSuccess)) ||
         (e = ensure(&c->d_stats, &c->cap_stats, (size_t)n_t)) != hipSuccess)
         return hip_fail(c, e, "alloc bank");
+    if (on_device) {  // the checked copies become the bank
+        std::swap(c->d_f0, c->d_f0_new);
+        std::swap(c->cap_f0, c->cap_f0_new);
+        std::swap(c->d_f1, c->d_f1_new);
+        std::swap(c->cap_f1, c->cap_f1_new);
+        std::swap(c->d_sky, c->d_sky_new);
+        std::swap(c->cap_sky, c->cap_sky_new);
+    }
     if (grid) {
         const bool same_sky = c->sky_order_valid && c->sky_order_of.size() == c->sky_h.size() &&
                               std::memcmp(c->sky_order_of.data(), c->sky_h.data(), c->sky_h.size() * sizeof(double)) == 0;
@@ -1303,11 +1371,14 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
             c->sky_order_valid = true;
         }
     }
-    e = hipMemcpyAsync(c->d_f0, c->f0_h.data(), n0 * sizeof(double), hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(c->d_f1, c->f1_h.data(), n1 * sizeof(double), hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(c->d_sky, c->sky_h.data(), ns * 3 * sizeof(double), hipMemcpyHostToDevice, c->stream);
+    e = hipSuccess;
+    if (!on_device) {
+        e = hipMemcpyAsync(c->d_f0, c->f0_h.data(), n0 * sizeof(double), hipMemcpyHostToDevice, c->stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(c->d_f1, c->f1_h.data(), n1 * sizeof(double), hipMemcpyHostToDevice, c->stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(c->d_sky, c->sky_h.data(), ns * 3 * sizeof(double), hipMemcpyHostToDevice, c->stream);
+    }
     if (e == hipSuccess && binary) {
         if ((e = ensure(&c->d_bin, &c->cap_bin, (size_t)n0 * 3)) != hipSuccess) return hip_fail(c, e, "alloc binary bank");
         e = hipMemcpyAsync(c->d_bin, c->ap_h.data(), n0 * sizeof(double), hipMemcpyHostToDevice, c->stream);

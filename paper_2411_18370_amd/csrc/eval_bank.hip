@@ -583,6 +583,60 @@ __global__ __launch_bounds__(BANK_THREADS, 4) void eval_list_kernel(EvalRun r, B
     if (!SPLIT && live) r.stats[t] = (float)(tot + (double)acc);
 }
 
+__device__ __forceinline__ uint64_t ordered_bits(double x)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    return u >> 63 ? ~u : u | 1ull << 63;
+}
+
+__global__ __launch_bounds__(64) void list_check_init_kernel(ListCheck *res)
+{
+    uint64_t *q = (uint64_t *)res;
+    if (threadIdx.x < sizeof(ListCheck) / 8) q[threadIdx.x] = threadIdx.x == 1 || threadIdx.x == 3 ? 0ull : ~0ull;
+}
+
+// Every array is read once; a workgroup's extremes are joined by one atomic each.
+__global__ __launch_bounds__(256) void list_check_kernel(const double *f0, const double *f1, const double *sky, int64_t n,
+                                                         double dt_lo, double dt_hi, ListCheck *res)
+{
+    __shared__ uint64_t sh[4][8];
+    uint64_t v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = q == 1 || q == 3 ? 0ull : ~0ull;
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < n; t += (int64_t)gridDim.x * 256) {
+        const double a = f0[t], b = f1[t], x = sky[3 * t], y = sky[3 * t + 1], z = sky[3 * t + 2];
+        const uint64_t ua = ordered_bits(a), ub = ordered_bits(b);
+        v[0] = min(v[0], ua);
+        v[1] = max(v[1], ua);
+        v[2] = min(v[2], ub);
+        v[3] = max(v[3], ub);
+        if (!__builtin_isfinite(a) || !(a > 0.0)) v[4] = min(v[4], (uint64_t)t);
+        if (!__builtin_isfinite(b)) v[5] = min(v[5], (uint64_t)t);
+        if (!__builtin_isfinite(x) || !__builtin_isfinite(y) || !__builtin_isfinite(z)) v[6] = min(v[6], 2 * (uint64_t)t);
+        else if (fabs(sqrt(x * x + y * y + z * z) - 1.0) > 1e-12) v[6] = min(v[6], 2 * (uint64_t)t + 1);
+        if (!(a + fmin(b * dt_lo, b * dt_hi) > 0.0)) v[7] = min(v[7], (uint64_t)t);
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const uint64_t y = __shfl_xor(v[q], o, 64);
+            v[q] = q == 1 || q == 3 ? max(v[q], y) : min(v[q], y);
+        }
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][q] = v[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < 8) {
+        const int q = threadIdx.x;
+        const bool most = q == 1 || q == 3;
+        uint64_t x = sh[0][q];
+        for (int w = 1; w < 4; ++w) x = most ? max(x, sh[w][q]) : min(x, sh[w][q]);
+        unsigned long long *at = (unsigned long long *)res + q;
+        if (most) atomicMax(at, (unsigned long long)x);
+        else if (x != ~0ull) atomicMin(at, (unsigned long long)x);
+    }
+}
+
 // Templates in the order of LIST_KEYS equal steps of f0 (any order within one):
 // counts, their running sum, places.  A workgroup counts 4096 templates in LDS
 // and adds or takes its share of a step with one atomic.
@@ -818,6 +872,15 @@ hipError_t launch_eval_bank(const EvalRun &run, const BankPlan &pl, float *bsum,
     if (e == hipSuccess && bsum)
         e = launch_block_sum(bsum, run.n_list, n_blk, run.stats, nullptr, s);
     return e;
+}
+
+hipError_t launch_list_check(const double *f0, const double *f1, const double *sky, int64_t n, double dt_lo, double dt_hi,
+                             ListCheck *res, hipStream_t s)
+{
+    hipLaunchKernelGGL(list_check_init_kernel, dim3(1), dim3(64), 0, s, res);
+    const unsigned g = (unsigned)((n + 255) / 256 < 512 ? (n + 255) / 256 : 512);
+    hipLaunchKernelGGL(list_check_kernel, dim3(g), dim3(256), 0, s, f0, f1, sky, n, dt_lo, dt_hi, res);
+    return hipGetLastError();
 }
 
 size_t list_order_keys() { return LIST_KEYS; }

@@ -354,6 +354,24 @@ struct ListPlan {
     int32_t *order;  // [n_list]
     uint32_t *cnt;   // [list_order_keys()]
 };
+// Bounds and validity of a list bank's arrays on the device.  Doubles are held as
+// integers in their order (ordered_bits); the indices are the first offending
+// template's, ~0 when there is none.
+struct ListCheck {
+    uint64_t f0_lo, f0_hi, f1_lo, f1_hi;
+    uint64_t bad_f0, bad_f1;  // a non-finite (f0: or not positive) value
+    uint64_t bad_sky;         // 2 s: a non-finite component, 2 s + 1: not of unit norm
+    uint64_t bad_track;       // f0 + f1 (t - t_ref) not positive somewhere
+};
+inline double from_ordered_bits(uint64_t u)
+{
+    u = u >> 63 ? u & ~(1ull << 63) : ~u;
+    double x;
+    __builtin_memcpy(&x, &u, sizeof x);
+    return x;
+}
+hipError_t launch_list_check(const double *f0, const double *f1, const double *sky, int64_t n, double dt_lo, double dt_hi,
+                             ListCheck *res, hipStream_t s);
 size_t list_order_keys();
 hipError_t launch_list_window(const EvalRun &run, const BankPlan &plan, const ListPlan &list, float *bsum, int n_seg,
                               hipStream_t s);
