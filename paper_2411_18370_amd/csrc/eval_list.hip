@@ -888,46 +888,14 @@ __global__ void nc_table_kernel(const float *power, const float *weight, float *
     }
 }
 
-// add(x[0]) .. add(x[m - 1]) in order by one lane, x in LDS: four groups of
-// eight in registers, a group read again 24 additions before its turn.
-template <typename F>
-__device__ __forceinline__ void lane_chain(const double *x, int m, F add)
-{
-    int q = 0;
-    double a[4][8];
-    auto read = [&](int g, int at) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) a[g][i] = x[at + i];
-    };
-    auto sum = [&](int g) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) add(a[g][i]);
-    };
-    if (m >= 32) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) read(g, 8 * g);
-        for (; q + 64 <= m; q += 32)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                sum(g);
-                read(g, q + 32 + 8 * g);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) sum(g);
-        q += 32;
-    }
-    for (; q < m; ++q) add(x[q]);
-}
-
 // Sky-dependent weights, one wavefront per sky point: norm = 1 / W with
 // W = sum_k u_k ab_k(n), then the moments W1 = sum w_k, W2 = sum w_k^2 of
 // w_k = u_k (ab_k norm).  All three sums are sequential in SFT order (lanes
-// form 256 terms at a time into the wave's LDS slice, lane 0 adds them), the
-// canonical order of the oracle, so norm and the moments are bit-exact.  Bound
-// by that chain, about ten cycles an addition: the arms of the next 256 SFTs
-// are requested before it (1201 points x 3000 SFTs: 293 us with an LDS read
-// before every addition, 123 us now).
+// form 256 terms at a time into the wave's LDS slice for wave_chain), the
+// canonical order of the oracle, so norm and the moments are bit-exact.  The
+// arms of the next 256 SFTs are requested before the additions (1201 points x
+// 3000 SFTs: 293 us with an LDS read before every addition, 123 us with reads
+// ahead on one lane, 89 us now).
 __global__ __launch_bounds__(256) void sky_moments_kernel(const double *arms, const float *weight, int n_sft,
                                                           const double *sky, int64_t n_sky, int stat, double *norm,
                                                           double *ms, uint32_t *err)
@@ -947,7 +915,7 @@ __global__ __launch_bounds__(256) void sky_moments_kernel(const double *arms, co
                 u[j] = weight ? (double)weight[k] : 1.0;
             }
         };
-        // chain over term(u, ab) of every SFT
+        // term(u, ab) of every SFT into buf, 256 at a time; add(m) adds them
         auto pass = [&](auto term, auto add) {
             load(0);
             for (int k0 = 0; k0 < n_sft; k0 += 256) {
@@ -955,14 +923,13 @@ __global__ __launch_bounds__(256) void sky_moments_kernel(const double *arms, co
                 for (int j = 0; j < 4; ++j) buf[64 * j + lane] = term(u[j], sky_ab(arm[j], nx, ny, nz));
                 wave_lds_sync();
                 if (k0 + 256 < n_sft) load(k0 + 256);
-                if (lane == 0) lane_chain(buf, min(256, n_sft - k0), add);
+                add(min(256, n_sft - k0));
                 wave_lds_sync();
             }
         };
-        double acc = 0.0;
-        pass([](double w, double ab) { return w * ab; }, [&](double x) { acc = acc + x; });
-        const double c1 = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(acc)),
-                                           __builtin_amdgcn_readfirstlane(__double2loint(acc)));
+        double c1 = 0.0;
+        pass([](double w, double ab) { return w * ab; },
+             [&](int m) { c1 = wave_chain(c1, [&](int q) { return buf[q]; }, m); });
         if (!(c1 > 0.0 && c1 < 1e300)) {
             if (lane == 0) {
                 atomicOr(err, ERR_BAD_POWER);
@@ -975,9 +942,9 @@ __global__ __launch_bounds__(256) void sky_moments_kernel(const double *arms, co
         const double inv = 1.0 / c1;
         double w1 = 0.0, w2 = 0.0;
         pass([&](double w, double ab) { return w * (ab * inv); },
-             [&](double x) {
-                 w1 = w1 + x;
-                 w2 = w2 + x * x;
+             [&](int m) {
+                 w1 = wave_chain(w1, [&](int q) { return buf[q]; }, m);
+                 w2 = wave_chain(w2, [&](int q) { return buf[q] * buf[q]; }, m);
              });
         if (lane == 0) {
             norm[s] = inv;

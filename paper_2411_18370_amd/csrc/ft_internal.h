@@ -170,6 +170,85 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
+// Sum over the lanes of a wave, by moves between lanes of the vector unit (a
+// shuffle goes through LDS, 130 cycles each); every lane gets it.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lane_shift(double x)
+{
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ double wave_total(double x)
+{
+    x = x + lane_shift<0x111, 0xf>(x);  // row_shr 1, 2, 4, 8: rows of 16
+    x = x + lane_shift<0x112, 0xf>(x);
+    x = x + lane_shift<0x114, 0xf>(x);
+    x = x + lane_shift<0x118, 0xf>(x);
+    x = x + lane_shift<0x142, 0xa>(x);  // row_bcast 15 and 31
+    x = x + lane_shift<0x143, 0xc>(x);
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63), __builtin_amdgcn_readlane(__double2loint(x), 63));
+}
+
+// s + get(0) + .. + get(m - 1), m <= 256, added one after the other in FP64 -- the
+// same bits -- by a wave whose lanes hold the same s.
+//
+// While the sum stays in one binade [2^e, 2^(e+1)), an addition of x >= 0 raises
+// it by x rounded to a multiple of u = 2^(e-52), whatever the sum is; only a tie
+// (x halfway between multiples) also looks at the sum's last bit.  So the lanes
+// form d = (s + x) - s, which is that multiple exactly, and add the d's, an exact
+// sum in any order since all are multiples of u below 2^53 u.  If s plus that
+// stays below 2^(e+1) and no x is a tie, it is the sequential result: had a
+// partial sum reached 2^(e+1), so would the total.  Else (the binades' ends, a
+// tie, a negative or non-finite x, a sum near zero) the terms are added one by
+// one.  A chain of 256 takes 2700 cycles, the lanes 350; 10^4 terms cross some
+// seven binades after their first 256.
+template <typename G>
+__device__ __forceinline__ double wave_chain(double s, G get, int m)
+{
+    const int lane = threadIdx.x & 63;
+    const int e = (int)((uint32_t)__double2hiint(s) >> 20);  // sign and biased exponent
+    const double half = __hiloint2double((e - 53) << 20, 0);
+    double d[4];
+    bool ok = e > 64 && e < 2046;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int q = 64 * j + lane;
+        const double x = q < m ? get(q) : 0.0;
+        d[j] = (s + x) - s;
+        ok = ok && x >= 0.0 && fabs(x - d[j]) < half;
+    }
+    const double t = s + wave_total((d[0] + d[1]) + (d[2] + d[3]));
+    if (__builtin_amdgcn_ballot_w64(!(ok && (int)((uint32_t)__double2hiint(t) >> 20) == e)) == 0) return t;
+    int q = 0;
+    // four groups of eight in registers: a group is read again 24 additions
+    // before its turn (an LDS read takes about 13 of them)
+    double a[4][8];
+    auto read = [&](int g, int at) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a[g][i] = get(at + i);
+    };
+    auto add = [&](int g) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s = s + a[g][i];
+    };
+    if (m >= 32) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) read(g, 8 * g);
+        for (; q + 64 <= m; q += 32)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                add(g);
+                read(g, q + 32 + 8 * g);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) add(g);
+        q += 32;
+    }
+    for (; q < m; ++q) s = s + get(q);
+    return s;
+}
+
 // Number-count threshold (Eq. number_count): P > 3.2 as real numbers, which for
 // FP32 P is P >= 3.2f (the float nearest 3.2 lies above it).
 constexpr float NC_THRESHOLD_F = 3.2f;

@@ -11,8 +11,8 @@
 //    per sub-band.
 // 3. Each candidate is re-summed in FP64 in SFT order with canonical bins
 //    (a workgroup per candidate: three wavefronts form the weighted terms and
-//    store them to LDS; one lane of the fourth adds them to the running sum one
-//    by one in SFT order, so the sum is the plain sequential FP64 sum).
+//    store them to LDS; the fourth adds them to the running sum, 256 at a time
+//    with the bits of the plain sequential FP64 sum).
 // 4. Candidates are ranked within their sub-band by (S64 desc, index asc);
 //    ranks < K are the toplist, identical to sorting all FP64 statistics.
 #include "ft_internal.h"
@@ -480,15 +480,14 @@ __device__ __forceinline__ void rescore_terms(const EvalRun &r, const TemplatePa
 
 // Sequential FP64 sums over the SFTs, a group of NW waves per template: waves
 // 1 .. NW-1 of the group form the terms of a chunk of 256 (NW - 1) SFTs into one
-// of two LDS buffers while wave 0's first lane adds an earlier chunk term by
-// term in SFT order.  terms(k, p, w) gives the table values of SFTs k + 64 j,
+// of two LDS buffers while wave 0 adds an earlier chunk in SFT order (the same
+// bits as term by term).  terms(k, p, w) gives the table values of SFTs k + 64 j,
 // j < 4 (loads in flight until the next chunk's bins are formed; anything past
 // the last SFT) and their weights; acc = sum w p, and
 // with MOM sw = sum w, sw2 = sum w^2 (the results are wave 0 lane 0's).
-// What binds it is the chain of dependent additions, 10^4 of them in 55 us with
-// the LDS reads 24 additions ahead (110 us with eight ahead: each group waited
-// for its reads); with one wave doing both, the terms' gathers and FP64 bins
-// came on top (245 us).  Called by every thread of the workgroup with the same n_sft (the
+// What binds it are the terms' dependent gathers, hidden one chunk deep; added
+// term by term by one lane, 10^4 additions took 57 us, 33 us as wave_chain does
+// them.  Called by every thread of the workgroup with the same n_sft (the
 // groups share its barriers); a group without a template is inactive.
 constexpr int SEQ_PER_WAVE = 256;
 template <int NW, bool MOM>
@@ -530,49 +529,15 @@ __device__ __forceinline__ void seq_sums(F terms, int n_sft, SeqBuf<NW, MOM> &bu
                 p[j] = pn[j];
                 w[j] = wn[j];
             }
-        } else if (it > 1 && lane == 0) {
+        } else if (it > 1) {
             const double *x = buf.val[it & 1], *y = buf.w[MOM ? it & 1 : 0];
             const int m = min(CH, n_sft - (it - 2) * CH);
-            int q = 0;
-            // four groups of eight in registers: a group is read again 24
-            // additions before its turn (an LDS read takes about 13 of them)
-            double a[4][8], b[4][8];
-            auto read = [&](int g, int at) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    a[g][i] = x[at + i];
-                    if (MOM) b[g][i] = y[at + i];
-                }
-            };
-            auto add = [&](int g) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    acc = acc + a[g][i];
-                    if (MOM) {
-                        sw = sw + b[g][i];
-                        sw2 = sw2 + b[g][i] * b[g][i];
-                    }
-                }
-            };
-            if (m >= 32) {
-#pragma unroll
-                for (int g = 0; g < 4; ++g) read(g, 8 * g);
-                for (; q + 64 <= m; q += 32)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        add(g);
-                        read(g, q + 32 + 8 * g);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-#pragma unroll
-                for (int g = 0; g < 4; ++g) add(g);
-                q += 32;
-            }
-            for (; q < m; ++q) {
-                acc = acc + x[q];
+            for (int q0 = 0; q0 < m; q0 += 256) {
+                const int n = min(256, m - q0);
+                acc = wave_chain(acc, [&](int q) { return x[q0 + q]; }, n);
                 if (MOM) {
-                    sw = sw + y[q];
-                    sw2 = sw2 + y[q] * y[q];
+                    sw = wave_chain(sw, [&](int q) { return y[q0 + q]; }, n);
+                    sw2 = wave_chain(sw2, [&](int q) { return y[q0 + q] * y[q0 + q]; }, n);
                 }
             }
         }
@@ -647,18 +612,8 @@ __device__ __forceinline__ double rescore_wave(const EvalRun &r, bool grid, int6
 #pragma unroll
         for (int j = 0; j < RS_UNROLL; ++j) buf[64 * j + lane] = val[j];
         wave_lds_sync();
-        if (lane == 0) {
-            const int m = min(64 * RS_UNROLL, r.n_sft - k0);
-            int q = 0;
-            for (; q + 8 <= m; q += 8) {
-                double x[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) x[i] = buf[q + i];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) acc = acc + x[i];
-            }
-            for (; q < m; ++q) acc = acc + buf[q];
-        }
+        static_assert(64 * RS_UNROLL <= 256, "one step of wave_chain");
+        acc = wave_chain(acc, [&](int q) { return buf[q]; }, min(64 * RS_UNROLL, r.n_sft - k0));
         wave_lds_sync();
     }
     return acc;
