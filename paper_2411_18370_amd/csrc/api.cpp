@@ -188,9 +188,9 @@ struct ft_ctx_s {
     hipStream_t capture_stream = nullptr;
     // side streams (default priority) and events of a batch's concurrent
     // evaluation launches
-    static constexpr int kSide = 3;
-    hipStream_t side[kSide] = {nullptr, nullptr, nullptr};
-    hipEvent_t fork_ev = nullptr, join_ev[kSide] = {nullptr, nullptr, nullptr};
+    static constexpr int kSide = 2;
+    hipStream_t side[kSide] = {nullptr, nullptr};
+    hipEvent_t fork_ev = nullptr, join_ev[kSide] = {nullptr, nullptr};
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
     hipEvent_t bev[2] = {nullptr, nullptr};
@@ -2844,7 +2844,10 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
     // small-bank kernel) draw on disjoint work and run concurrently: the
     // first on st, the others on side streams forked from st and joined back
     // before the selection (a captured graph gets parallel branches), so one
-    // launch's last workgroups overlap the next launch
+    // launch's last workgroups overlap the next launch.  A process has four
+    // hardware queues, of which a fourth branch got one that was taken and ran
+    // by itself (64 uneven runs: the launches together 1305 us, in three
+    // branches 1155 us)
     struct Launch {
         int id;  // tile, tile_count() for the small-bank kernel, the next for the local-bank kernel
         int64_t off;
@@ -2857,6 +2860,9 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
         if (n_items > 0) ls.push_back({id, item_off, n_items});
         item_off += n_items;
     }
+    // the small runs' few waves first: behind the tiles' workgroups, which fill
+    // every CU, they would start when the tiles have ended
+    std::stable_partition(ls.begin(), ls.end(), [](const Launch &L) { return L.id >= tile_count(); });
     const int n_side = std::min<int>((int)ls.size() - 1, ft_ctx_s::kSide);
     if (e == hipSuccess && n_side > 0) e = hipEventRecord(c->fork_ev, st);
     int joined = 0;  // side streams that waited on the fork (and must be joined back)
@@ -2866,7 +2872,8 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
     }
     for (size_t i = 0; i < ls.size() && e == hipSuccess; ++i) {
         const Launch &L = ls[i];
-        hipStream_t s = i == 0 || n_side == 0 ? st : c->side[(i - 1) % n_side];
+        const int q = (int)i % (n_side + 1);
+        hipStream_t s = q == 0 ? st : c->side[q - 1];
         if (L.id < tile_count())
             e = launch_eval_batch(b.runs, b.items + L.off, L.n, pl.group_wtp[L.id], b.counters + L.id,
                                   std::min(L.n, 2048), tile_cfg(L.id), pl.bps > 0, s);
