@@ -356,7 +356,10 @@ double model_cost(int id, double n_f0, double n_f1)
     const double f0w = std::ceil(n_f0 / (64.0 * t.L)) * 64.0 * t.L / n_f0;
     const double f1w = std::ceil(n_f1 / t.JT) * t.JT / n_f1;
     const double ops = t.L > 1 ? (7.0 + t.L) / t.L : 7.0;
-    return f0w * f1w * ops;
+    // a run tile's staging and parameters are shared by its f1 values: one
+    // takes 2.4 times, two 1.4 times the time a slot of three (5 f0 values)
+    const double few = t.L > 1 && t.JT < 3 ? (t.JT == 1 ? 2.2 : 1.4) : 1.0;
+    return f0w * f1w * ops * few;
 }
 
 // Measured time of a round of workgroups of a tile, per SFT: first + (q - 1)
