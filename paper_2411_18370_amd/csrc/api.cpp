@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -242,8 +243,10 @@ ft_status hip_fail(ft_ctx c, hipError_t e, const char *what)
     return fail(c, FT_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
-// Test hook: FT_FAULT=alloc:n makes the n-th device allocation (1-based) of the
-// process fail, to exercise the FT_E_NOMEM path from the host.
+// Test hooks, to exercise the FT_E_NOMEM paths from the host: FT_FAULT=alloc:n
+// makes the n-th device allocation (1-based) of the process fail,
+// FT_FAULT=budget:b every one that would bring the device memory held by
+// contexts above b bytes.
 int fault_alloc_countdown()
 {
     static int n = [] {
@@ -253,7 +256,28 @@ int fault_alloc_countdown()
     }();
     return n;
 }
+size_t fault_budget()
+{
+    static size_t b = [] {
+        const char *s = getenv("FT_FAULT");
+        if (s && strncmp(s, "budget:", 7) == 0) return (size_t)strtoull(s + 7, nullptr, 10);
+        return ~size_t(0);
+    }();
+    return b;
+}
 int g_alloc_calls = 0;
+std::atomic<size_t> g_alloc_bytes{0};
+
+template <typename T>
+void release(T **p, size_t *cap)
+{
+    if (*p) (void)hipFree(*p);
+    *p = nullptr;
+    if (cap) {
+        g_alloc_bytes -= *cap * sizeof(T);
+        *cap = 0;
+    }
+}
 
 template <typename T>
 hipError_t ensure(T **p, size_t *cap, size_t count)
@@ -263,33 +287,19 @@ hipError_t ensure(T **p, size_t *cap, size_t count)
     ++g_alloc_calls;
     if (fault_alloc_countdown() > 0 && g_alloc_calls == fault_alloc_countdown())
         return hipErrorOutOfMemory;
-    if (*p) {
-        (void)hipFree(*p);
-        *p = nullptr;
-        *cap = 0;
-    }
-    const size_t want = std::max(count, *cap + *cap / 4);
-    hipError_t e = hipMalloc((void **)p, want * sizeof(T));
-    if (e != hipSuccess) {
-        e = hipMalloc((void **)p, count * sizeof(T));
-        if (e != hipSuccess) {
-            *p = nullptr;
-            (void)hipGetLastError();
-            return hipErrorOutOfMemory;
+    const size_t grown = *cap + *cap / 4;
+    release(p, cap);
+    for (const size_t want : {std::max(count, grown), count}) {
+        if (g_alloc_bytes + want * sizeof(T) > fault_budget()) continue;
+        if (hipMalloc((void **)p, want * sizeof(T)) == hipSuccess) {
+            *cap = want;
+            g_alloc_bytes += want * sizeof(T);
+            return hipSuccess;
         }
-        *cap = count;
-        return hipSuccess;
+        *p = nullptr;
+        (void)hipGetLastError();
     }
-    *cap = want;
-    return hipSuccess;
-}
-
-template <typename T>
-void release(T **p, size_t *cap)
-{
-    if (*p) (void)hipFree(*p);
-    *p = nullptr;
-    if (cap) *cap = 0;
+    return hipErrorOutOfMemory;
 }
 
 // Copy `count` elements from a host or device pointer into a host vector.
@@ -3195,7 +3205,10 @@ ft_status ft_eval_batch(ft_ctx c, const ft_batch *bt, int32_t use_graph)
     const int k = bt->k;
     const int cap = std::max(4096, 8 * k);
 
-    // device buffers
+    // device buffers.  From here on the previous batch's are freed or written
+    // over: should this call fail, neither its results nor its captured graph
+    // can be used any more.
+    c->have_batch = false;
     auto &b = c->bb;
     hipError_t e;
     const int64_t n_dt = pl.dt_prefix[n_runs], n_stats = pl.stats_prefix[n_runs];
@@ -3370,7 +3383,6 @@ ft_status ft_eval_batch(ft_ctx c, const ft_batch *bt, int32_t use_graph)
     c->batch_runs = n_runs;
     c->batch_k = k;
     c->batch_cap = cap;
-    c->have_batch = false;
     if (c->graph_exec) {
         (void)hipGraphExecDestroy(c->graph_exec);
         c->graph_exec = nullptr;
@@ -3512,6 +3524,7 @@ static hipError_t mlp_alloc(ft_mlp p, T **dst, size_t n)
     *dst = nullptr;
     hipError_t e = ensure(dst, &cap, n);
     if (e == hipSuccess) p->allocs.push_back((void *)*dst);
+    g_alloc_bytes -= cap * sizeof(T);  // a network's memory is not its context's
     return e;
 }
 
