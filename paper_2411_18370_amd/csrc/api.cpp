@@ -1218,6 +1218,14 @@ static ft_status check_list(ft_ctx c, const ft_bank *bank, double dt_min, double
     return FT_OK;
 }
 
+// A step of an evaluation that fails for memory or on the device may have freed
+// buffers that the last evaluation refers to: that one is over.
+static ft_status checked_step(ft_ctx c, ft_status st)
+{
+    if (st == FT_E_NOMEM || st == FT_E_DEVICE) c->have_eval = false;
+    return st;
+}
+
 static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalRun &run,
                               bool &grid, int64_t &n_t)
 {
@@ -1756,9 +1764,9 @@ ft_status ft_eval_templates(ft_ctx c, const ft_bank *bank, double t_ref, const f
     EvalRun run;
     bool grid;
     int64_t n_t;
-    ft_status st = prepare_bank(c, bank, t_ref, run, grid, n_t);
+    ft_status st = checked_step(c, prepare_bank(c, bank, t_ref, run, grid, n_t));
     if (st != FT_OK) return st;
-    st = apply_stat_weights(c, opts, grid, grid ? bank->n_sky : 0, run);
+    st = checked_step(c, apply_stat_weights(c, opts, grid, grid ? bank->n_sky : 0, run));
     if (st != FT_OK) return st;
     const bool sky = run.sky_norm != nullptr;
     run.sum_mode = opts->sum_mode;
@@ -1811,8 +1819,8 @@ ft_status ft_eval_templates(ft_ctx c, const ft_bank *bank, double t_ref, const f
         }
     }
 
-    return launch_eval_select(c, run, grid, tile, n_t, grid ? bank->n_f0 : n_t, opts, edges, stats,
-                              gp.tail.tile >= 0 ? &gp.tail : nullptr);
+    return checked_step(c, launch_eval_select(c, run, grid, tile, n_t, grid ? bank->n_f0 : n_t, opts, edges, stats,
+                                              gp.tail.tile >= 0 ? &gp.tail : nullptr));
 }
 
 // Launch sequence of an evaluation: clear flags, map sub-bands, evaluate,
@@ -2256,9 +2264,9 @@ ft_status ft_eval_binary_random(ft_ctx c, const ft_binary_region *reg, uint64_t 
     ft_status st = check_eval_opts(c, opts, edges);
     if (st != FT_OK) return st;
     EvalRun run;
-    st = binary_random_run(c, reg, seed, n, t_ref, opts, run, nullptr, nullptr);
+    st = checked_step(c, binary_random_run(c, reg, seed, n, t_ref, opts, run, nullptr, nullptr));
     if (st != FT_OK) return st;
-    return launch_eval_select(c, run, false, -1, n, n, opts, edges, stats);
+    return checked_step(c, launch_eval_select(c, run, false, -1, n, n, opts, edges, stats));
 }
 
 ft_status ft_eval_binary_boxes(ft_ctx c, const ft_binary_region *reg, uint64_t seed, int64_t n, double t_ref,
@@ -2293,7 +2301,7 @@ ft_status ft_eval_binary_boxes(ft_ctx c, const ft_binary_region *reg, uint64_t s
             return hip_fail(c, e, "alloc box buffers");
     }
     EvalRun run;
-    st = binary_random_run(c, reg, seed, n, t_ref, opts, run, &div, c->d_box);
+    st = checked_step(c, binary_random_run(c, reg, seed, n, t_ref, opts, run, &div, c->d_box));
     if (st != FT_OK) return st;
     BankPlan bank;
     st = plan_binary(c, run, bank);
@@ -2565,7 +2573,7 @@ ft_status ft_bins(ft_ctx c, const ft_bank *bank, double t_ref, int32_t precision
     EvalRun run;
     bool grid;
     int64_t n_t;
-    ft_status st = prepare_bank(c, bank, t_ref, run, grid, n_t);
+    ft_status st = checked_step(c, prepare_bank(c, bank, t_ref, run, grid, n_t));
     if (st != FT_OK) return st;
     const size_t n = (size_t)n_t * (size_t)c->n_sft;
     hipError_t e = ensure(&c->d_bins, &c->cap_bins, n);
@@ -2589,7 +2597,7 @@ ft_status ft_count_index_mismatches(ft_ctx c, const ft_bank *bank, double t_ref,
     EvalRun run;
     bool grid;
     int64_t n_t;
-    ft_status st = prepare_bank(c, bank, t_ref, run, grid, n_t);
+    ft_status st = checked_step(c, prepare_bank(c, bank, t_ref, run, grid, n_t));
     if (st != FT_OK) return st;
     unsigned long long cnt[2] = {0, 0};
     hipError_t e = hipMemsetAsync(c->d_count, 0, sizeof cnt, c->stream);

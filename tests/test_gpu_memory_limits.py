@@ -46,3 +46,35 @@ with ft.Context(0) as c:
     c.batch_replay()
     assert [[t.index for t in c.batch_toplist(r, 3)] for r in range(4)] == before
 """)
+
+
+def test_failed_evaluation_ends_the_one_before(ft):
+    """Its buffers may be gone; a bank that is refused for what it holds leaves it whole."""
+    _run(ft, 64 << 20, """
+w = synth.tiny_bank(40, 1, 1, 20)
+def bank(n):
+    rng = np.random.default_rng(n)
+    return rng.uniform(150.0, 150.02, n), rng.uniform(-1e-9, 0, n), synth.isotropic_sky(n, rng)
+edges = np.array([149.0, 151.0])
+with ft.Context(0) as c:
+    c.set_sfts(w.n_sft_per_det, w.t_mid, w.t_sft, w.first_bin, w.power, None)
+    c.set_velocities(w.v)
+    def ev(n, k=4):
+        f0, f1, sky = bank(n)
+        c.eval_templates(f0, f1, sky, w.t_ref, k, edges, kind=ft.FT_BANK_LIST)
+    def tops():
+        return [t.index for t in c.toplist(0, 4)], c.toplist_number_count(0, 4)[0].tolist()
+    ev(2000)
+    before = tops()
+    f0, f1, sky = bank(300000)
+    f0[0] = np.nan
+    refused(ft.FT_E_INVALID, lambda: c.eval_templates(f0, f1, sky, w.t_ref, 4, edges, kind=ft.FT_BANK_LIST))
+    assert tops() == before
+    many = np.linspace(149.0, 151.0, 301)
+    f0, f1, sky = bank(200000)
+    refused(ft.FT_E_NOMEM, lambda: c.eval_templates(f0, f1, sky, w.t_ref, 65536, many, kind=ft.FT_BANK_LIST))
+    refused(ft.FT_E_STATE, lambda: c.toplist(0, 4))
+    refused(ft.FT_E_STATE, lambda: c.toplist_number_count(0, 4))
+    ev(2000)
+    assert tops() == before
+""")
