@@ -255,8 +255,10 @@ typedef struct {
  * n_templates * ceil(N / 32) floats of context memory for its per-block sums
  * (BINARY: at most 256 MB; GRID and LIST: at most 1 GiB; the runs of an
  * ft_eval_batch together likewise), and a LIST bank 4 bytes a template for its
- * order by f0; without that memory it is evaluated as before, and the
- * statistics are the same bits either way.
+ * order by f0 and, from 1024 templates, 40 bytes a template for a second copy
+ * (the bank before it is held until the new one is found valid).  Without that
+ * memory the bank is evaluated and checked in slower ways; the statistics are
+ * the same bits and the errors the same either way.
  */
 ft_status ft_eval_templates(ft_ctx ctx, const ft_bank *bank, double t_ref,
                             const ft_eval_opts *opts, float *stats);

@@ -1182,17 +1182,26 @@ static bool binary_range_ok(ft_ctx c, double f0_lo, double f0_hi, double aw_max)
 
 constexpr int64_t kListDevice = 1024;  // templates
 
-// Copies a list bank's arrays beside the current bank's and checks them there,
-// with the host checks' order and messages.
+// Buffers for a second copy of a list bank of n templates, given back when they
+// cannot all be had.
+static bool list_room(ft_ctx c, size_t n)
+{
+    if (ensure(&c->d_f0_new, &c->cap_f0_new, n) == hipSuccess && ensure(&c->d_f1_new, &c->cap_f1_new, n) == hipSuccess &&
+        ensure(&c->d_sky_new, &c->cap_sky_new, n * 3) == hipSuccess &&
+        ensure(&c->d_list_check, &c->cap_list_check, 1) == hipSuccess)
+        return true;
+    release(&c->d_f0_new, &c->cap_f0_new);
+    release(&c->d_f1_new, &c->cap_f1_new);
+    release(&c->d_sky_new, &c->cap_sky_new);
+    return false;
+}
+
+// Copies a list bank's arrays beside the current bank's (list_room) and checks
+// them there, with the host checks' order and messages.
 static ft_status check_list(ft_ctx c, const ft_bank *bank, double dt_min, double dt_max, ListCheck &r)
 {
     const size_t n = (size_t)bank->n_list;
     hipError_t e;
-    if ((e = ensure(&c->d_f0_new, &c->cap_f0_new, n)) != hipSuccess ||
-        (e = ensure(&c->d_f1_new, &c->cap_f1_new, n)) != hipSuccess ||
-        (e = ensure(&c->d_sky_new, &c->cap_sky_new, n * 3)) != hipSuccess ||
-        (e = ensure(&c->d_list_check, &c->cap_list_check, 1)) != hipSuccess)
-        return hip_fail(c, e, "alloc bank");
     // work on other streams that produces the arrays ends before a synchronous
     // copy of them: one element each orders the copies on our stream after it
     double one;
@@ -1257,8 +1266,9 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
     hipError_t e;
     // Lists are checked on the device from kListDevice templates: host reading,
     // checking and copying take 7 ns a template (calls of 2e5: 2.12 ms, device
-    // 0.87 ms; of 2000: 225 us, device 198 us).
-    const bool on_device = !grid && !binary && n0 >= kListDevice;
+    // 0.87 ms; of 2000: 225 us, device 198 us).  The current bank must survive one
+    // that is refused, so that takes room for both; without it the host checks.
+    const bool on_device = !grid && !binary && n0 >= kListDevice && list_room(c, (size_t)n0);
     if (on_device) {
     } else if (fetch(c->f0_h, bank->f0, (size_t)n0) != hipSuccess || fetch(c->sky_h, bank->sky_xyz, (size_t)ns * 3) != hipSuccess)
         return fail(c, FT_E_INVALID, "cannot read the bank arrays");

@@ -78,3 +78,38 @@ with ft.Context(0) as c:
     ev(2000)
     assert tops() == before
 """)
+
+
+LIST = """
+w = synth.tiny_bank(40, 1, 1, 20)
+edges = np.array([149.0, 151.0])
+def bank(seed, n=200000):
+    rng = np.random.default_rng(seed)
+    return rng.uniform(150.0, 150.02, n), rng.uniform(-1e-9, 0, n), synth.isotropic_sky(n, rng)
+def top(c, b):
+    c.eval_templates(*b, w.t_ref, 4, edges, kind=ft.FT_BANK_LIST)
+    return [(t.index, t.s64) for t in c.toplist(0, 4)]
+def load(c):
+    c.set_sfts(w.n_sft_per_det, w.t_mid, w.t_sft, w.first_bin, w.power, None)
+    c.set_velocities(w.v)
+"""
+
+
+@pytest.mark.parametrize("mb", [14, 18, 64])
+def test_list_without_room_for_a_second_copy(ft, mb):
+    """200,000 templates take 8 MB a copy; the checks of a bank are the same either way."""
+    _run(ft, mb << 20, LIST + """
+import oracle
+want = []
+for s in (1, 2, 3):
+    s64, bad = oracle.eval_list(w.t_mid, w.t_ref, w.t_sft, w.first_bin, w.power, None, w.v, *bank(s))
+    want.append([(i, s64[i]) for i in oracle.toplist(s64, oracle.subband(bank(s)[0], edges), 1, 4)[0]])
+with ft.Context(0) as c:
+    load(c)
+    assert [top(c, bank(s)) for s in (1, 2)] == want[:2]
+    b = bank(3)
+    b[2][777] *= 1.1
+    refused(ft.FT_E_INVALID, lambda: top(c, b))
+    assert [(t.index, t.s64) for t in c.toplist(0, 4)] == want[1]
+    assert top(c, bank(3)) == want[2]
+""")
