@@ -258,7 +258,8 @@ typedef struct {
  * order by f0 and, from 1024 templates, 40 bytes a template for a second copy
  * (the bank before it is held until the new one is found valid).  Without that
  * memory the bank is evaluated and checked in slower ways; the statistics are
- * the same bits and the errors the same either way.
+ * the same bits and the errors the same either way.  A later call of the
+ * context that finds no memory for what it cannot do without frees it first.
  */
 ft_status ft_eval_templates(ft_ctx ctx, const ft_bank *bank, double t_ref,
                             const ft_eval_opts *opts, float *stats);

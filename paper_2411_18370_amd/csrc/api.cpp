@@ -336,6 +336,37 @@ ft_status sync_and_check(ft_ctx c, uint32_t *seen = nullptr)
     return check_flags(c, flags);
 }
 
+// Frees what evaluations only keep to be faster: block sums, a list's order, its
+// predecessor's copy, and a batch's block sums once its captured graph can no
+// longer be replayed.  True if there was anything.
+bool give_back(ft_ctx c)
+{
+    const bool any = c->d_bsum || c->d_order || c->d_f0_new || (!c->have_batch && c->bb.bsum);
+    release(&c->d_bsum, &c->cap_bsum);
+    release(&c->d_order, &c->cap_order);
+    release(&c->d_f0_new, &c->cap_f0_new);
+    release(&c->d_f1_new, &c->cap_f1_new);
+    release(&c->d_sky_new, &c->cap_sky_new);
+    if (!c->have_batch) release(&c->bb.bsum, &c->bb.c_bsum);
+    return any;
+}
+
+hipError_t first_error(std::initializer_list<hipError_t> es)
+{
+    for (hipError_t e : es)
+        if (e != hipSuccess) return e;
+    return hipSuccess;
+}
+
+// Allocations that a call cannot do without: a second attempt without the
+// scratch of earlier ones.  Not between taking that scratch and its use.
+template <typename F>
+hipError_t with_room(ft_ctx c, F alloc)
+{
+    const hipError_t e = alloc();
+    return e == hipErrorOutOfMemory && give_back(c) ? alloc() : e;
+}
+
 // Doppler-coherent visiting order of the sky points: bands of equal height in
 // sin(declination), right ascension ascending in even bands and descending in
 // odd ones, about as many bands as points per band.  Consecutive points are
@@ -801,12 +832,14 @@ ft_status ft_set_sfts(ft_ctx c, int32_t n_det, const int32_t *n_sft, const doubl
         if (!is_finite(t)) return fail(c, FT_E_INVALID, "t_mid holds a non-finite value");
     hipError_t e;
     const size_t n_cells = (size_t)total * (size_t)n_bins;
-    if ((e = ensure(&c->d_power, &c->cap_power, n_cells + TABLE_PAD)) != hipSuccess) return hip_fail(c, e, "alloc power");
-    if ((e = ensure(&c->d_tmid, &c->cap_tmid, (size_t)total)) != hipSuccess) return hip_fail(c, e, "alloc t_mid");
-    if ((e = ensure(&c->d_dt, &c->cap_dt, (size_t)total)) != hipSuccess) return hip_fail(c, e, "alloc dt");
-    if (weight && ((e = ensure(&c->d_weight, &c->cap_weight, (size_t)total)) != hipSuccess ||
-                   (e = ensure(&c->d_power_w, &c->cap_power_w, n_cells + TABLE_PAD)) != hipSuccess))
-        return hip_fail(c, e, "alloc weight");
+    e = with_room(c, [&] {
+        return first_error({ensure(&c->d_power, &c->cap_power, n_cells + TABLE_PAD),
+                            ensure(&c->d_tmid, &c->cap_tmid, (size_t)total),
+                            ensure(&c->d_dt, &c->cap_dt, (size_t)total),
+                            weight ? ensure(&c->d_weight, &c->cap_weight, (size_t)total) : hipSuccess,
+                            weight ? ensure(&c->d_power_w, &c->cap_power_w, n_cells + TABLE_PAD) : hipSuccess});
+    });
+    if (e != hipSuccess) return hip_fail(c, e, "alloc SFT data");
     e = hipMemcpyAsync(c->d_power, power, n_cells * sizeof(float), hipMemcpyDefault, c->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(c->d_tmid, tm.data(), (size_t)total * sizeof(double), hipMemcpyHostToDevice,
@@ -880,10 +913,12 @@ static ft_status ensure_nc(ft_ctx c)
     if (c->ind_valid) return FT_OK;
     const size_t n_cells = (size_t)c->n_sft * (size_t)c->n_bins;
     hipError_t e;
-    if ((e = ensure(&c->d_ind, &c->cap_ind, n_cells + TABLE_PAD)) != hipSuccess ||
-        (c->has_weight && (e = ensure(&c->d_ind_w, &c->cap_ind_w, n_cells + TABLE_PAD)) != hipSuccess) ||
-        (e = ensure(&c->d_mu_sigma_nc, &c->cap_mu_sigma_nc, 2)) != hipSuccess)
-        return hip_fail(c, e, "alloc number-count tables");
+    e = with_room(c, [&] {
+        return first_error({ensure(&c->d_ind, &c->cap_ind, n_cells + TABLE_PAD),
+                            c->has_weight ? ensure(&c->d_ind_w, &c->cap_ind_w, n_cells + TABLE_PAD) : hipSuccess,
+                            ensure(&c->d_mu_sigma_nc, &c->cap_mu_sigma_nc, 2)});
+    });
+    if (e != hipSuccess) return hip_fail(c, e, "alloc number-count tables");
     e = launch_nc_table(c->d_power, c->has_weight ? c->d_weight : nullptr, c->d_ind, c->d_ind_w, c->n_sft, c->n_bins,
                         c->stream);
     if (e == hipSuccess)
@@ -988,13 +1023,15 @@ ft_status ft_gen_sfts(ft_ctx c, int32_t n_det, const int32_t *n_sft, const doubl
     // SFT bookkeeping first (as ft_set_sfts), then the velocities
     hipError_t e;
     const size_t n_cells = (size_t)total * (size_t)n_bins;
-    if ((e = ensure(&c->d_power, &c->cap_power, n_cells + TABLE_PAD)) != hipSuccess ||
-        (e = ensure(&c->d_tmid, &c->cap_tmid, (size_t)total)) != hipSuccess ||
-        (e = ensure(&c->d_dt, &c->cap_dt, (size_t)total)) != hipSuccess ||
-        (e = ensure(&c->d_arms, &c->cap_arms, (size_t)total * 6)) != hipSuccess ||
-        (e = ensure(&c->d_inj_bin, &c->cap_inj_bin, (size_t)total * std::max(n_inj, 1))) != hipSuccess ||
-        (e = ensure(&c->d_inj_amp, &c->cap_inj_amp, (size_t)total * 3 * std::max(n_inj, 1))) != hipSuccess)
-        return hip_fail(c, e, "alloc generated SFTs");
+    e = with_room(c, [&] {
+        return first_error({ensure(&c->d_power, &c->cap_power, n_cells + TABLE_PAD),
+                            ensure(&c->d_tmid, &c->cap_tmid, (size_t)total),
+                            ensure(&c->d_dt, &c->cap_dt, (size_t)total),
+                            ensure(&c->d_arms, &c->cap_arms, (size_t)total * 6),
+                            ensure(&c->d_inj_bin, &c->cap_inj_bin, (size_t)total * std::max(n_inj, 1)),
+                            ensure(&c->d_inj_amp, &c->cap_inj_amp, (size_t)total * 3 * std::max(n_inj, 1))});
+    });
+    if (e != hipSuccess) return hip_fail(c, e, "alloc generated SFTs");
     e = hipMemcpyAsync(c->d_tmid, tm.data(), (size_t)total * sizeof(double), hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(c->d_arms, ah.data(), ah.size() * sizeof(double), hipMemcpyHostToDevice, c->stream);
@@ -1368,11 +1405,6 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
     }
 
     // upload
-    if ((!on_device && ((e = ensure(&c->d_f0, &c->cap_f0, (size_t)n0)) != hipSuccess ||
-                        (e = ensure(&c->d_f1, &c->cap_f1, (size_t)n1)) != hipSuccess ||
-                        (e = ensure(&c->d_sky, &c->cap_sky, (size_t)ns * 3)) != hipSuccess)) ||
-        (e = ensure(&c->d_stats, &c->cap_stats, (size_t)n_t)) != hipSuccess)
-        return hip_fail(c, e, "alloc bank");
     if (on_device) {  // the checked copies become the bank
         std::swap(c->d_f0, c->d_f0_new);
         std::swap(c->cap_f0, c->cap_f0_new);
@@ -1381,6 +1413,14 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
         std::swap(c->d_sky, c->d_sky_new);
         std::swap(c->cap_sky, c->cap_sky_new);
     }
+    e = with_room(c, [&] {
+        return first_error({on_device ? hipSuccess : ensure(&c->d_f0, &c->cap_f0, (size_t)n0),
+                            on_device ? hipSuccess : ensure(&c->d_f1, &c->cap_f1, (size_t)n1),
+                            on_device ? hipSuccess : ensure(&c->d_sky, &c->cap_sky, (size_t)ns * 3),
+                            binary ? ensure(&c->d_bin, &c->cap_bin, (size_t)n0 * 3) : hipSuccess,
+                            ensure(&c->d_stats, &c->cap_stats, (size_t)n_t)});
+    });
+    if (e != hipSuccess) return hip_fail(c, e, "alloc bank");
     if (grid) {
         const bool same_sky = c->sky_order_valid && c->sky_order_of.size() == c->sky_h.size() &&
                               std::memcmp(c->sky_order_of.data(), c->sky_h.data(), c->sky_h.size() * sizeof(double)) == 0;
@@ -1411,7 +1451,6 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
             e = hipMemcpyAsync(c->d_sky, c->sky_h.data(), ns * 3 * sizeof(double), hipMemcpyHostToDevice, c->stream);
     }
     if (e == hipSuccess && binary) {
-        if ((e = ensure(&c->d_bin, &c->cap_bin, (size_t)n0 * 3)) != hipSuccess) return hip_fail(c, e, "alloc binary bank");
         e = hipMemcpyAsync(c->d_bin, c->ap_h.data(), n0 * sizeof(double), hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(c->d_bin + n0, c->omega_h.data(), n0 * sizeof(double), hipMemcpyHostToDevice, c->stream);
@@ -1457,18 +1496,20 @@ static ft_status prepare_bank(ft_ctx c, const ft_bank *bank, double t_ref, EvalR
 static ft_status ensure_select(ft_ctx c, int n_seg, int k, int64_t n_seg_map, int64_t cap)
 {
     hipError_t e;
-    if ((e = ensure(&c->d_hist, &c->cap_hist, (size_t)n_seg * 1024 + SEL_TICKETS)) != hipSuccess ||
-        (e = ensure(&c->d_state, &c->cap_state, (size_t)n_seg * 8)) != hipSuccess ||
-        (e = ensure(&c->d_cnt, &c->cap_cnt, (size_t)n_seg)) != hipSuccess ||
-        (e = ensure(&c->d_off, &c->cap_off, (size_t)n_seg + 1)) != hipSuccess ||
-        (e = ensure(&c->d_fill, &c->cap_fill, (size_t)n_seg)) != hipSuccess ||
-        (e = ensure(&c->d_cand, &c->cap_cand, (size_t)cap)) != hipSuccess ||
-        (e = ensure(&c->d_cand_s64, &c->cap_cand_s64, (size_t)cap)) != hipSuccess ||
-        (e = ensure(&c->d_cand_mom, &c->cap_cand_mom, (size_t)cap * 2)) != hipSuccess ||
-        (e = ensure(&c->d_seg, &c->cap_seg, (size_t)n_seg_map)) != hipSuccess ||
-        (e = ensure(&c->d_out, &c->cap_out, (size_t)n_seg * k)) != hipSuccess ||
-        (e = ensure(&c->d_nout, &c->cap_nout, (size_t)n_seg)) != hipSuccess)
-        return hip_fail(c, e, "alloc selection buffers");
+    e = with_room(c, [&] {
+        return first_error({ensure(&c->d_hist, &c->cap_hist, (size_t)n_seg * 1024 + SEL_TICKETS),
+                            ensure(&c->d_state, &c->cap_state, (size_t)n_seg * 8),
+                            ensure(&c->d_cnt, &c->cap_cnt, (size_t)n_seg),
+                            ensure(&c->d_off, &c->cap_off, (size_t)n_seg + 1),
+                            ensure(&c->d_fill, &c->cap_fill, (size_t)n_seg),
+                            ensure(&c->d_cand, &c->cap_cand, (size_t)cap),
+                            ensure(&c->d_cand_s64, &c->cap_cand_s64, (size_t)cap),
+                            ensure(&c->d_cand_mom, &c->cap_cand_mom, (size_t)cap * 2),
+                            ensure(&c->d_seg, &c->cap_seg, (size_t)n_seg_map),
+                            ensure(&c->d_out, &c->cap_out, (size_t)n_seg * k),
+                            ensure(&c->d_nout, &c->cap_nout, (size_t)n_seg)});
+    });
+    if (e != hipSuccess) return hip_fail(c, e, "alloc selection buffers");
     return FT_OK;
 }
 
@@ -1817,16 +1858,7 @@ ft_status ft_eval_templates(ft_ctx c, const ft_bank *bank, double t_ref, const f
         run.tiles_sky = wp.tiles_sky;
         if ((int64_t)run.tiles_f0 * run.tiles_f1 * run.tiles_sky >= 0x7fffffffLL)
             return fail(c, FT_E_UNSUPPORTED, "too many tiles");
-        if (tile >= 0 && gp.bps > 0) {
-            const size_t n_blk = (size_t)((run.n_sft + SUM_BLOCK - 1) / SUM_BLOCK);
-            if (ensure(&c->d_bsum, &c->cap_bsum, n_blk * (size_t)n_t) == hipSuccess) {
-                run.seg_blocks = (int32_t)gp.bps;
-                run.bsum = c->d_bsum;
-                run.bsum_n = n_t;
-            } else {
-                (void)hipGetLastError();  // no room: not split
-            }
-        }
+        if (tile >= 0) run.seg_blocks = (int32_t)gp.bps;
     }
 
     return checked_step(c, launch_eval_select(c, run, grid, tile, n_t, grid ? bank->n_f0 : n_t, opts, edges, stats,
@@ -2110,14 +2142,6 @@ static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile,
     ft_status st;
     const int n_seg = opts->n_sub;
     const int k = opts->k;
-    BankPlan bank;
-    if (run.ap) {
-        st = plan_binary(c, run, bank);
-        if (st != FT_OK) return st;
-    } else if (!grid) {
-        st = plan_list(c, run, bank);
-        if (st != FT_OK) return st;
-    }
     // first guess of the candidate buffer: 64 per toplist slot, never more than
     // the templates themselves nor 2^26 entries (ft_sync regrows it to the
     // exact count when the threshold ties many templates)
@@ -2125,6 +2149,24 @@ static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile,
                                            std::max<int64_t>(n_t, 1), (int64_t)1 << 26});
     st = ensure_select(c, n_seg, k, n_seg_map, cap);
     if (st != FT_OK) return st;
+    // from here on scratch is held: nothing may be given back
+    BankPlan bank;
+    if (run.seg_blocks > 0) {  // a split grid
+        const size_t n_blk = (size_t)((run.n_sft + SUM_BLOCK - 1) / SUM_BLOCK);
+        if (ensure(&c->d_bsum, &c->cap_bsum, n_blk * (size_t)n_t) == hipSuccess) {
+            run.bsum = c->d_bsum;
+            run.bsum_n = n_t;
+        } else {
+            (void)hipGetLastError();  // no room: not split
+            run.seg_blocks = 0;
+        }
+    } else if (run.ap) {
+        st = plan_binary(c, run, bank);
+        if (st != FT_OK) return st;
+    } else if (!grid) {
+        st = plan_list(c, run, bank);
+        if (st != FT_OK) return st;
+    }
     if ((e = ensure(&c->d_edges, &c->cap_edges, edges.size())) != hipSuccess) return hip_fail(c, e, "alloc edges");
     e = hipMemcpyAsync(c->d_edges, edges.data(), edges.size() * sizeof(double), hipMemcpyHostToDevice, c->stream);
     SelectBufs sb = select_bufs(c, cap, opts->statistic);
@@ -2226,10 +2268,13 @@ static ft_status binary_random_run(ft_ctx c, const ft_binary_region *reg, uint64
     const double x_max = reg->f0_hi * (1.0 + c->vmax + reg->ap_hi * reg->omega_hi) * c->t_sft;
     if (!(x_max < 2147483000.0)) return fail(c, FT_E_UNSUPPORTED, "track frequencies above 2^31/T_sft");
     hipError_t e;
-    if ((e = ensure(&c->d_f0, &c->cap_f0, (size_t)n)) != hipSuccess || (e = ensure(&c->d_sky, &c->cap_sky, (size_t)n * 3)) != hipSuccess ||
-        (e = ensure(&c->d_bin, &c->cap_bin, (size_t)n * 3)) != hipSuccess ||
-        (e = ensure(&c->d_stats, &c->cap_stats, (size_t)n)) != hipSuccess)
-        return hip_fail(c, e, "alloc bank");
+    e = with_room(c, [&] {
+        return first_error({ensure(&c->d_f0, &c->cap_f0, (size_t)n),
+                            ensure(&c->d_sky, &c->cap_sky, (size_t)n * 3),
+                            ensure(&c->d_bin, &c->cap_bin, (size_t)n * 3),
+                            ensure(&c->d_stats, &c->cap_stats, (size_t)n)});
+    });
+    if (e != hipSuccess) return hip_fail(c, e, "alloc bank");
     e = launch_gen_binary_bank(*reg, seed, 0, n, c->d_f0, c->d_sky, c->d_bin, c->d_bin + n, c->d_bin + 2 * n, c->stream,
                                div, box);
     if (e == hipSuccess) e = launch_dt(c->d_tmid, t_ref, c->d_dt, c->n_sft, c->stream);
@@ -2301,14 +2346,16 @@ ft_status ft_eval_binary_boxes(ft_ctx c, const ft_binary_region *reg, uint64_t s
     }
     if (n >= 1 && n < (1LL << 31)) {
         hipError_t e;
-        if ((e = ensure(&c->d_box, &c->cap_box, (size_t)n)) != hipSuccess ||
-            (e = ensure(&c->d_bcount, &c->cap_bcount, (size_t)n_boxes)) != hipSuccess ||
-            (e = ensure(&c->d_bmax32, &c->cap_bmax32, (size_t)n_boxes)) != hipSuccess ||
-            (e = ensure(&c->d_bmax64, &c->cap_bmax64, (size_t)n_boxes)) != hipSuccess ||
-            (e = ensure(&c->d_bidx, &c->cap_bidx, (size_t)n_boxes)) != hipSuccess ||
-            (e = ensure(&c->d_bout, &c->cap_bout, (size_t)n_boxes)) != hipSuccess ||
-            (e = ensure(&c->d_bncand, &c->cap_bncand, 2)) != hipSuccess)
-            return hip_fail(c, e, "alloc box buffers");
+        e = with_room(c, [&] {
+            return first_error({ensure(&c->d_box, &c->cap_box, (size_t)n),
+                                ensure(&c->d_bcount, &c->cap_bcount, (size_t)n_boxes),
+                                ensure(&c->d_bmax32, &c->cap_bmax32, (size_t)n_boxes),
+                                ensure(&c->d_bmax64, &c->cap_bmax64, (size_t)n_boxes),
+                                ensure(&c->d_bidx, &c->cap_bidx, (size_t)n_boxes),
+                                ensure(&c->d_bout, &c->cap_bout, (size_t)n_boxes),
+                                ensure(&c->d_bncand, &c->cap_bncand, 2)});
+        });
+        if (e != hipSuccess) return hip_fail(c, e, "alloc box buffers");
     }
     EvalRun run;
     st = checked_step(c, binary_random_run(c, reg, seed, n, t_ref, opts, run, &div, c->d_box));
@@ -3231,33 +3278,36 @@ ft_status ft_eval_batch(ft_ctx c, const ft_batch *bt, int32_t use_graph)
     hipError_t e;
     const int64_t n_dt = pl.dt_prefix[n_runs], n_stats = pl.stats_prefix[n_runs];
     const int64_t n_power = gen ? pl.gen_prefix_elem[n_runs] : bt->power_len;
-    if ((e = ensure(&b.tmid, &b.c_tmid, (size_t)NS)) != hipSuccess || (e = ensure(&b.v, &b.c_v, (size_t)NS * 3)) != hipSuccess ||
-        (gen && (e = ensure(&b.arms, &b.c_arms, (size_t)NS * 6)) != hipSuccess) ||
-        (e = ensure(&b.dt, &b.c_dt, (size_t)n_dt)) != hipSuccess ||
-        (e = ensure(&b.f0, &b.c_f0, (size_t)bt->n_f0_total)) != hipSuccess ||
-        (e = ensure(&b.f1, &b.c_f1, (size_t)bt->n_f1_total)) != hipSuccess ||
-        (e = ensure(&b.sky, &b.c_sky, (size_t)bt->n_sky_total * 3)) != hipSuccess ||
-        (e = ensure(&b.sky_tile, &b.c_sky_tile, pl.sky_tile.size())) != hipSuccess ||
-        (e = ensure(&b.perm, &b.c_perm, pl.perm.size())) != hipSuccess ||
-        (e = ensure(&b.tref, &b.c_tref, (size_t)n_runs)) != hipSuccess ||
-        (e = ensure(&b.sft_begin, &b.c_sft_begin, (size_t)n_runs)) != hipSuccess ||
-        (e = ensure(&b.dt_prefix, &b.c_dt_prefix, (size_t)n_runs + 1)) != hipSuccess ||
-        (e = ensure(&b.power, &b.c_power, (size_t)n_power)) != hipSuccess ||
-        (e = ensure(&b.stats, &b.c_stats, (size_t)n_stats)) != hipSuccess ||
-        (e = ensure(&b.runs, &b.c_runs, (size_t)n_runs)) != hipSuccess ||
-        (e = ensure(&b.counters, &b.c_counters, (size_t)std::max(tile_count() + 2, 129))) != hipSuccess ||
-        (e = ensure(&b.cand, &b.c_cand, (size_t)n_runs * cap)) != hipSuccess ||
-        (e = ensure(&b.s64, &b.c_s64, (size_t)n_runs * cap)) != hipSuccess ||
-        (e = ensure(&b.out, &b.c_out, (size_t)n_runs * k)) != hipSuccess ||
-        (e = ensure(&b.nout, &b.c_nout, (size_t)n_runs)) != hipSuccess ||
-        (e = ensure(&b.maxz, &b.c_maxz, (size_t)n_runs)) != hipSuccess ||
-        (e = ensure(&b.labels, &b.c_labels, (size_t)n_runs)) != hipSuccess ||
-        (gen && ((e = ensure(&b.gen, &b.c_gen, (size_t)n_runs)) != hipSuccess ||
-                 (e = ensure(&b.gen_prefix, &b.c_gen_prefix, (size_t)(n_runs + 1) * 2)) != hipSuccess ||
-                 (e = ensure(&b.inj_bin, &b.c_inj_bin, (size_t)pl.gen_prefix_sft[n_runs])) != hipSuccess ||
-                 (e = ensure(&b.inj_amp, &b.c_inj_amp, (size_t)pl.gen_prefix_sft[n_runs] * 3)) != hipSuccess ||
-                 (e = ensure(&b.band, &b.c_band, (size_t)pl.gen_prefix_sft[n_runs] * 2)) != hipSuccess)))
-        return hip_fail(c, e, "alloc batch buffers");
+    e = with_room(c, [&] {
+        return first_error({ensure(&b.tmid, &b.c_tmid, (size_t)NS),
+                            ensure(&b.v, &b.c_v, (size_t)NS * 3),
+                            gen ? ensure(&b.arms, &b.c_arms, (size_t)NS * 6) : hipSuccess,
+                            ensure(&b.dt, &b.c_dt, (size_t)n_dt),
+                            ensure(&b.f0, &b.c_f0, (size_t)bt->n_f0_total),
+                            ensure(&b.f1, &b.c_f1, (size_t)bt->n_f1_total),
+                            ensure(&b.sky, &b.c_sky, (size_t)bt->n_sky_total * 3),
+                            ensure(&b.sky_tile, &b.c_sky_tile, pl.sky_tile.size()),
+                            ensure(&b.perm, &b.c_perm, pl.perm.size()),
+                            ensure(&b.tref, &b.c_tref, (size_t)n_runs),
+                            ensure(&b.sft_begin, &b.c_sft_begin, (size_t)n_runs),
+                            ensure(&b.dt_prefix, &b.c_dt_prefix, (size_t)n_runs + 1),
+                            ensure(&b.power, &b.c_power, (size_t)n_power),
+                            ensure(&b.stats, &b.c_stats, (size_t)n_stats),
+                            ensure(&b.runs, &b.c_runs, (size_t)n_runs),
+                            ensure(&b.counters, &b.c_counters, (size_t)std::max(tile_count() + 2, 129)),
+                            ensure(&b.cand, &b.c_cand, (size_t)n_runs * cap),
+                            ensure(&b.s64, &b.c_s64, (size_t)n_runs * cap),
+                            ensure(&b.out, &b.c_out, (size_t)n_runs * k),
+                            ensure(&b.nout, &b.c_nout, (size_t)n_runs),
+                            ensure(&b.maxz, &b.c_maxz, (size_t)n_runs),
+                            ensure(&b.labels, &b.c_labels, (size_t)n_runs),
+                            gen ? ensure(&b.gen, &b.c_gen, (size_t)n_runs) : hipSuccess,
+                            gen ? ensure(&b.gen_prefix, &b.c_gen_prefix, (size_t)(n_runs + 1) * 2) : hipSuccess,
+                            gen ? ensure(&b.inj_bin, &b.c_inj_bin, (size_t)pl.gen_prefix_sft[n_runs]) : hipSuccess,
+                            gen ? ensure(&b.inj_amp, &b.c_inj_amp, (size_t)pl.gen_prefix_sft[n_runs] * 3) : hipSuccess,
+                            gen ? ensure(&b.band, &b.c_band, (size_t)pl.gen_prefix_sft[n_runs] * 2) : hipSuccess});
+    });
+    if (e != hipSuccess) return hip_fail(c, e, "alloc batch buffers");
     // device pointers of every run
     for (int r = 0; r < n_runs; ++r) {
         const ft_run &R = runs[r];

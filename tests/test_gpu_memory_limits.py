@@ -113,3 +113,38 @@ with ft.Context(0) as c:
     assert [(t.index, t.s64) for t in c.toplist(0, 4)] == want[1]
     assert top(c, bank(3)) == want[2]
 """)
+
+
+def test_scratch_is_given_back_to_what_needs_it(ft):
+    """The block sums a split grid keeps (15 MB) make way for a table, a bank and a batch."""
+    _run(ft, 40 << 20, LIST + """
+def grid(c):
+    f0 = 150.0 + np.arange(200) / 1800.0
+    sky = synth.isotropic_sky(100, np.random.default_rng(4))
+    f1 = np.linspace(-1e-9, 0, 3)
+    rng = np.random.default_rng(5)
+    t = np.sort(synth.EPOCH + 1800.0 * rng.choice(2400, 2000, replace=False) + 900.0)
+    v = synth.detector_velocity(t, synth.DETECTORS[0])
+    vm = float(np.max(np.linalg.norm(v, axis=1)))
+    first, nb = synth.table_range(f0[0], f0[-1], f1[0], f1[-1], t[0] - synth.EPOCH, t[-1] - synth.EPOCH, vm, 1800.0)
+    c.set_sfts([2000], t, 1800.0, first, np.ones((2000, nb), np.float32))
+    c.set_velocities(v)
+    c.eval_templates(f0, f1, sky, synth.EPOCH, 4, np.array([149.0, 151.0]))
+    c.toplist(0, 4)
+with ft.Context(0) as c:
+    grid(c)
+    n = 2000
+    rng = np.random.default_rng(6)
+    t = np.sort(synth.EPOCH + 1800.0 * rng.choice(2400, n, replace=False) + 900.0)
+    c.set_sfts([n], t, 1800.0, 270000, np.ones((n, 3500), np.float32))  # 28 MB
+    c.set_velocities(synth.detector_velocity(t, synth.DETECTORS[0]))
+with ft.Context(0) as c:
+    grid(c)
+    load(c)
+    top(c, bank(1, 450000))  # 18 MB, with its statistics 22
+with ft.Context(0) as c:
+    grid(c)
+    cp = synth.campaign(8, seed=2, n_pool=2000, n_sft_range=(1900, 2000), nt_range=(1000, 2000), k=3)
+    c.eval_campaign(cp)
+    c.batch_toplist(0, 3)
+""")
