@@ -216,6 +216,20 @@ __device__ __forceinline__ void gen_cell(uint64_t seed, uint32_t kk, uint32_t ru
     im = r * sth;
 }
 
+// Which of a signal's three amplitudes, at its column sig (INT32_MIN: none) and
+// the two beside it, cell b >= 0 takes; -1: none.  Unsigned, as sig lies anywhere:
+// the difference of the two is below 2^32 - 2 in size.
+constexpr int signal_part(int b, int32_t sig)
+{
+    const uint32_t m = (uint32_t)b - (uint32_t)sig + 1u;
+    return sig != INT32_MIN && m < 3u ? (int)m : -1;
+}
+// a constant expression holds no signed overflow
+static_assert(signal_part(0, INT32_MIN) == -1 && signal_part(0x0fffffff, INT32_MIN) == -1 &&
+              signal_part(0x0fffffff, INT32_MIN + 1) == -1 && signal_part(0x0fffffff, -1) == -1 &&
+              signal_part(0, INT32_MAX) == -1 && signal_part(0, -2) == -1 && signal_part(0, -1) == 2 &&
+              signal_part(7, 8) == 0 && signal_part(7, 7) == 1 && signal_part(7, 6) == 2 && signal_part(7, 5) == -1);
+
 // Noise (and signals) of the table rows, over each row's columns (its band for
 // batch runs).  Bound by the vector units (the counter rounds, a logarithm, a
 // sine and cosine in FP64), so the lanes are kept full: a workgroup takes the
@@ -294,8 +308,8 @@ __global__ __launch_bounds__(256) void gen_noise_kernel(const GenRun *runs, int 
         const auto cell = [](const GenRow &g, int b) {
             double re, im;
             gen_cell(g.seed, g.kk, g.run, b, re, im);
-            const int m = b - g.sig;
-            if (g.sig != INT32_MIN && m >= -1 && m <= 1) re = re + g.amp[m + 1];
+            const int m = signal_part(b, g.sig);
+            if (m >= 0) re = re + g.amp[m];
             g.row[b] = (float)(re * re + im * im);
         };
         if (cells <= GEN_WIDTH * n && !several) {
