@@ -237,9 +237,9 @@ static_assert(signal_part(0, INT32_MIN) == -1 && signal_part(0x0fffffff, INT32_M
 // local bank's are 10 to 40 columns, of which sixteen lanes to a row left 40%
 // idle, and every row's run was searched for again (1024 runs x 10^4 SFTs: 3.5
 // ms, now 1.9 ms).  Rows of more than GEN_WIDTH columns on average, whose last
-// sixteen cells matter little, and rows with several signals take sixteen lanes
+// cells matter little, and rows with several signals take sixteen lanes or more
 // each (64 runs' rows of a few hundred columns: 0.42 ms, by cells 0.44 ms).
-constexpr int GEN_WIDTH = 96, kRowLanes = 16;
+constexpr int GEN_WIDTH = 96;
 
 struct GenRow {
     float *row;
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(256) void gen_noise_kernel(const GenRun *runs, int 
                                                         const int64_t *row_prefix, int64_t total_rows)
 {
     __shared__ GenRow rows[GEN_ROWS];
-    constexpr int GEN_CELLS = GEN_WIDTH * GEN_ROWS;
+    constexpr int GEN_CELLS = GEN_WIDTH * GEN_ROWS, kRowLanes = GEN_ROWS < 16 ? 256 / GEN_ROWS : 16;
     __shared__ uint8_t id[GEN_CELLS];
     __shared__ int cells, rr_s[GEN_ROWS], hi_s[GEN_ROWS];
     __shared__ bool several;
@@ -305,12 +305,12 @@ __global__ __launch_bounds__(256) void gen_noise_kernel(const GenRun *runs, int 
             }
         }
         __syncthreads();
-        const auto cell = [](const GenRow &g, int b) {
+        const auto cell = [](float *row, uint64_t seed, uint32_t kk, uint32_t run, int sig, const double *amp, int b) {
             double re, im;
-            gen_cell(g.seed, g.kk, g.run, b, re, im);
-            const int m = signal_part(b, g.sig);
-            if (m >= 0) re = re + g.amp[m];
-            g.row[b] = (float)(re * re + im * im);
+            gen_cell(seed, kk, run, b, re, im);
+            const int m = signal_part(b, sig);
+            if (m >= 0) re = re + amp[m];
+            row[b] = (float)(re * re + im * im);
         };
         if (cells <= GEN_WIDTH * n && !several) {
             constexpr int P = 256 / GEN_ROWS;  // threads a row
@@ -318,10 +318,20 @@ __global__ __launch_bounds__(256) void gen_noise_kernel(const GenRun *runs, int 
             if (q < n)
                 for (int b = rows[q].lo + tid % P; b <= hi_s[q]; b += P) id[rows[q].off + b - rows[q].lo] = (uint8_t)q;
             __syncthreads();
-            for (int c = tid; c < cells; c += 256) cell(rows[id[c]], rows[id[c]].lo + (c - rows[id[c]].off));
+            for (int c = tid; c < cells; c += 256) {
+                const GenRow &g = rows[id[c]];
+                cell(g.row, g.seed, g.kk, g.run, g.sig, g.amp, g.lo + (c - g.off));
+            }
         } else if (!several) {
-            for (int q = tid / kRowLanes; q < n; q += 256 / kRowLanes)
-                for (int b = rows[q].lo + tid % kRowLanes; b <= hi_s[q]; b += kRowLanes) cell(rows[q], b);
+            for (int q = tid / kRowLanes; q < n; q += 256 / kRowLanes) {
+                // the row in registers: for all the compiler knows, a cell's store changes it
+                const GenRow &g = rows[q];
+                float *const row = g.row;
+                const uint64_t seed = g.seed;
+                const uint32_t kk = g.kk, run = g.run;
+                const int hi = hi_s[q], sig = g.sig;
+                for (int b = g.lo + tid % kRowLanes; b <= hi; b += kRowLanes) cell(row, seed, kk, run, sig, g.amp, b);
+            }
         } else {
             for (int q = tid / kRowLanes; q < n; q += 256 / kRowLanes) {
                 const GenRun &g = runs[rr_s[q]];
@@ -491,11 +501,13 @@ hipError_t launch_gen_tables(const GenRun *prep, int n_prep, const int64_t *prep
                            total_prep_sft);
     }
     if (n_runs > 0 && total_rows > 0) {
-        // 64 rows a workgroup once that leaves some thousand workgroups (10^4
-        // rows of 100 columns: 47 us with 64 rows, 27 us with 16)
-        const int rows = total_rows >= (1 << 18) ? 64 : 16;
+        // Rows a workgroup: 64 once that leaves some thousand workgroups, fewer where
+        // it would leave CUs idle.  Columns x rows, us: 1000 x 1000 rows: 15 with 4
+        // rows, 39 with 16; 10^4 x 30: 12, 8.8 and (64 rows) 11; 80,000 x 10: 22 with
+        // 16, 13 with 64.
+        const int rows = total_rows >= (1 << 16) ? 64 : total_rows > 2048 ? 16 : 4;
         const unsigned b2 = (unsigned)std::min<int64_t>((total_rows + rows - 1) / rows, 65536);
-        auto *kern = rows == 64 ? gen_noise_kernel<64> : gen_noise_kernel<16>;
+        auto *kern = rows == 64 ? gen_noise_kernel<64> : rows == 16 ? gen_noise_kernel<16> : gen_noise_kernel<4>;
         hipLaunchKernelGGL(kern, dim3(b2), dim3(256), 0, s, runs, n_runs, row_prefix, total_rows);
     }
     return hipGetLastError();

@@ -29,3 +29,10 @@ def test_generated_widths(ft, n_sft, n_bins, signals):
     got = _gen_gpu(ft, w, 1234567, 9, inj if inj else None)
     want = inject.generate_table(1234567, 9, w.t_mid, w.t_ref, w.t_sft, w.v, w.arms, w.first_bin, n_bins, inj if inj else None)
     _assert_tables_equal(got, want)
+
+
+@pytest.mark.parametrize("n_sft,n_bins,signals", [(3, 97, 1), (5, 200, 2), (2048, 9, 1), (2049, 97, 1), (2049, 3, 2),
+                                                  (65_535, 2, 0), (65_536, 2, 1)])
+def test_generated_row_counts(ft, n_sft, n_bins, signals):
+    """The row counts where a workgroup takes 4, 16 and 64 rows."""
+    test_generated_widths(ft, n_sft, n_bins, signals)
