@@ -89,7 +89,7 @@ __device__ __forceinline__ bool last_block(uint32_t *ticket)
 // One wave chooses the digit holding the k_rem-th largest key of a segment from
 // its histogram h(d): lane l sums digits 255 - 4 l .. 252 - 4 l, a scan over the
 // lanes finds the four that hold it.  Updates the segment's state (every lane
-// calls it; the state is read before and written by lane 0).
+// calls it and reads the state; the lane that finds the digit writes it).
 template <typename H>
 __device__ __forceinline__ void choose_digit(H h, uint32_t *st, int shift, double two_e)
 {
@@ -140,7 +140,8 @@ __device__ __forceinline__ void choose_digit(H h, uint32_t *st, int shift, doubl
     }
 }
 
-// End of a histogram pass: the last workgroup chooses every segment's digit.
+// End of a histogram pass in LDS (at most 32 sub-bands): the last workgroup
+// chooses every segment's digit.
 __device__ __forceinline__ void hist_done(uint32_t *state, const uint32_t *hist, int n_seg, int shift, double two_e,
                                           uint32_t *ticket)
 {
@@ -220,7 +221,18 @@ __global__ __launch_bounds__(256) void hist_kernel(const float *stats, const int
         for (int q = threadIdx.x; q < n_seg * 256; q += blockDim.x)
             if (hsh[q]) atomicAdd(&hist[q], hsh[q]);
     }
-    hist_done(state, hist, n_seg, shift, two_e, ticket);
+    if (LDS) hist_done(state, hist, n_seg, shift, two_e, ticket);
+}
+
+// The digits after a histogram pass without LDS (more than 32 sub-bands), a wave
+// each: the pass's last workgroup alone took 0.8 ms a pass for 4096 sub-bands,
+// a thread each 37 us, this 6 us.
+__global__ __launch_bounds__(256) void digits_kernel(uint32_t *state, const uint32_t *hist, int n_seg, int shift, double two_e)
+{
+    const int sg = (int)(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (sg >= n_seg) return;
+    const uint32_t *h = hist + (int64_t)sg * 256;
+    choose_digit([&](int d) { return h[d]; }, state + (int64_t)sg * ST, shift, two_e);
 }
 
 // Grid banks: a row is one (sky, f1) pair of n_f0 templates and the sub-band
@@ -1059,9 +1071,12 @@ hipError_t launch_select(const EvalRun &r, bool grid, int n_seg, int k, double r
         else if (lds_hist)
             hipLaunchKernelGGL(hist_kernel<true>, dim3(nb), dim3(256), hl, s, r.stats, b.seg_of_f0, rw, b.state, hist,
                                n_seg, shift, two_e, ticket);
-        else
+        else {
             hipLaunchKernelGGL(hist_kernel<false>, dim3(nb), dim3(256), 0, s, r.stats, b.seg_of_f0, rw, b.state, hist,
                                n_seg, shift, two_e, ticket);
+            hipLaunchKernelGGL(digits_kernel, dim3((unsigned)((n_seg + 3) / 4)), dim3(256), 0, s, b.state, hist, n_seg,
+                               shift, two_e);
+        }
     }
     const size_t cl = (size_t)n_seg * sizeof(uint32_t);
     if (cols == 4)

@@ -60,3 +60,10 @@ def test_select_grid(ft, shape, n_sub, k):
     with _ctx(ft, w) as c:
         c.eval_templates(w.f0, w.f1, w.sky, w.t_ref, k, edges)
         _check(c, s64, f0, edges, k)
+
+
+@pytest.mark.parametrize("n_sub", [34, 35, 4093, 4096])
+def test_select_many_sub_bands(ft, n_sub):
+    """Digits chosen by a wave a sub-band, with the last workgroup partly filled."""
+    test_select_list(ft, 16385, n_sub, 3)
+    test_select_grid(ft, (8200, 1, 3), n_sub, 2)
