@@ -2830,7 +2830,6 @@ void plan_batch_split(BatchPlan &pl)
     int64_t waves = 0, blocks = 0;
     pl.bps = 0;
     pl.bsum_len = 0;
-    pl.max_t = 0;
     for (size_t r = 0; r < pl.runs.size(); ++r) {
         const EvalRun &E = pl.runs[r];
         const int64_t n_t = (int64_t)E.n_f0 * E.n_f1 * E.n_sky, n_blk = (E.n_sft + SUM_BLOCK - 1) / SUM_BLOCK;
@@ -2840,7 +2839,6 @@ void plan_batch_split(BatchPlan &pl)
         waves += w;
         blocks += w * n_blk;
         pl.bsum_len += n_blk * n_t;
-        pl.max_t = std::max(pl.max_t, n_t);
     }
     if (waves >= BATCH_WAVES || (double)pl.bsum_len * 4.0 > kGridSplitBytes || pl.runs.size() > 65535) return;
     const int64_t rows = (BATCH_WAVES + waves - 1) / waves;
@@ -2969,7 +2967,7 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
     }
     if (e == hipSuccess && pl.bps > 0) e = launch_batch_block_sum(b.runs, n_runs, pl.max_t, st);
     if (e == hipSuccess)
-        e = launch_select_batch(b.runs, n_runs, c->batch_k, c->batch_cap, b.cand, b.s64, b.out, b.nout, b.maxz, c->d_err,
+        e = launch_select_batch(b.runs, n_runs, pl.max_t, c->batch_k, c->batch_cap, b.cand, b.s64, b.out, b.nout, b.maxz, c->d_err,
                                 st);
     if (e != hipSuccess) return hip_fail(c, e, "launch batch");
     return FT_OK;
@@ -3242,6 +3240,7 @@ ft_status ft_eval_batch(ft_ctx c, const ft_batch *bt, int32_t use_graph)
         pl.tref[r] = R.t_ref;
         pl.dt_prefix[r + 1] = pl.dt_prefix[r] + R.n_sft;
         pl.stats_prefix[r + 1] = pl.stats_prefix[r] + (int64_t)R.n_f0 * R.n_f1 * R.n_sky;
+        pl.max_t = std::max(pl.max_t, pl.stats_prefix[r + 1] - pl.stats_prefix[r]);
         pl.gen_prefix_sft[r + 1] = pl.gen_prefix_sft[r] + R.n_sft;
         pl.gen_prefix_elem[r + 1] = pl.gen_prefix_elem[r] + cells;
         pl.sky_prefix[r + 1] = pl.sky_prefix[r] + R.n_sky;

@@ -377,8 +377,8 @@ hipError_t launch_eval_batch_local(const EvalRun *runs, const int2 *items, int n
                                    int grid, hipStream_t s);
 
 // Exact per-run toplists of a batch (one workgroup per run, all of a run's
-// templates form one segment): out[r*k + rank], n_out[r], max_z[r].
-hipError_t launch_select_batch(const EvalRun *runs, int n_runs, int k, int cap_per_run,
+// templates form one segment; max_t: those of the largest): out[r*k + rank], n_out[r], max_z[r].
+hipError_t launch_select_batch(const EvalRun *runs, int n_runs, int64_t max_t, int k, int cap_per_run,
                                int64_t *cand, double *cand_s64, ft_candidate *out,
                                int32_t *n_out, double *max_z, uint32_t *err, hipStream_t s);
 hipError_t launch_labels(const double *max_z, int n_runs, double tau, uint8_t *labels,

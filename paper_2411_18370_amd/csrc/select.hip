@@ -601,9 +601,9 @@ __device__ __forceinline__ double rescore_one(const EvalRun &r, bool grid, int64
 }
 
 // The same sum by one wavefront (per-SFT or per-sky-point weights): lanes form
-// 256 terms at a time in the wave's LDS slice and lane 0 adds them; the next
-// terms' gathers are issued before the additions.  For candidates by the
-// thousand: waves enough are in flight, and four per candidate only wait.
+// 256 terms at a time in the wave's LDS slice for wave_chain; the next terms'
+// gathers are issued before the additions.  For candidates by the thousand:
+// waves enough are in flight, and four per candidate only wait.
 constexpr int RS_UNROLL = 4;
 
 __device__ __forceinline__ double rescore_wave(const EvalRun &r, bool grid, int64_t t, int lane, uint32_t &bad,
@@ -852,15 +852,20 @@ __global__ __launch_bounds__(256) void deliver_kernel(const uint32_t *err, int n
 // ---------------------------------------------------------------------------
 // Batches: one workgroup per run does the whole exact selection of that run
 // (runs hold at most a few 1e5 templates): radix select in LDS, candidate
-// compaction, FP64 re-summation (four wavefronts per candidate) and ranking.
-// The re-summation takes GROUPS candidates at a time, four wavefronts each
-// (three form terms, one adds them); a wave chooses a digit (a lane alone took
-// 55 us over a run's four).  A run's five passes over its keys wait on memory
-// and on the histogram's cells: sixteen keys are read ahead and equal digits of
-// a wave added together (64 runs of up to 10^5 templates: 249 us with eight and
-// an atomic a key, 181 us).
+// compaction, FP64 re-summation and ranking.  A wave chooses a digit (a lane
+// alone took 55 us over a run's four).  A run's five passes over its keys wait
+// on memory and on the histogram's cells: sixteen keys are read ahead and equal
+// digits of a wave added together (64 runs of up to 10^5 templates: 249 us with
+// eight and an atomic a key, 181 us).
+//
+// The re-summation is a chain of 256 terms at a time: 1.7 us for a wave that
+// forms and adds them, 2.7 us per 768 terms and two more such steps for a group
+// of four (three form, one adds).  So a group each takes a run's candidates only
+// where there are as few and the run is long (64 runs of up to 10^4 SFTs, one
+// candidate: 67 us, a wave each 94 us; up to 1000 SFTs: 195 and 82; 10^4 SFTs
+// and 512 candidates: 10.3 and 8.8 ms).
 // ---------------------------------------------------------------------------
-constexpr int SB_GROUP_WAVES = 4;
+constexpr int SB_GROUP_WAVES = 4, SB_LONG = 1536;
 constexpr int SB_AHEAD = 16;
 
 template <int SB_GROUPS>
@@ -930,18 +935,23 @@ __global__ __launch_bounds__(256 * SB_GROUPS) void select_batch_kernel(const Eva
         if (tid == 0) atomicOr(err, ERR_CAND_OVERFLOW);
         nc = cap;
     }
-    // FP64 re-summation in SFT order with canonical bins, SB_GROUPS candidates
-    // at a time
+    // FP64 re-summation in SFT order with canonical bins
     uint32_t bad = 0;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), group = wave / SB_GROUP_WAVES;
-    for (int p0 = 0; p0 < nc; p0 += SB_GROUPS) {
-        const int p = p0 + group;
-        const TemplateParams tp = params_of(R, true, cand[min(p, nc - 1)]);
+    if (nc > 0 && nc <= SB_GROUPS && R.n_sft > SB_LONG) {
+        const TemplateParams tp = params_of(R, true, cand[min(group, nc - 1)]);
         double acc, d0, d1;
         seq_sums<SB_GROUP_WAVES, false>(
             [&](int k_sft, float (&pw)[4], double (&w)[4]) { rescore_terms(R, tp, k_sft, false, 0.0, bad, pw, w); },
-            R.n_sft, seq[group], wave % SB_GROUP_WAVES, p < nc, acc, d0, d1);
-        if (p < nc && tid % (64 * SB_GROUP_WAVES) == 0) s64[p] = acc;
+            R.n_sft, seq[group], wave % SB_GROUP_WAVES, group < nc, acc, d0, d1);
+        if (group < nc && tid % (64 * SB_GROUP_WAVES) == 0) s64[group] = acc;
+    } else {
+        double *buf = seq[group].val[0] + 64 * RS_UNROLL * (wave % SB_GROUP_WAVES);
+        static_assert(64 * RS_UNROLL * SB_GROUP_WAVES <= 2 * SeqBuf<SB_GROUP_WAVES, false>::CH, "a slice a wave");
+        for (int p = wave; p < nc; p += SB_GROUP_WAVES * SB_GROUPS) {
+            const double acc = rescore_wave(R, true, cand[p], tid & 63, bad, buf);
+            if ((tid & 63) == 0) s64[p] = acc;
+        }
     }
     if (bad) atomicOr(err, bad);
     __syncthreads();
@@ -1010,16 +1020,19 @@ unsigned blocks_for(const Rows &rw)
 
 }  // namespace
 
-hipError_t launch_select_batch(const EvalRun *runs, int n_runs, int k, int cap_per_run,
+hipError_t launch_select_batch(const EvalRun *runs, int n_runs, int64_t max_t, int k, int cap_per_run,
                                int64_t *cand, double *cand_s64, ft_candidate *out,
                                int32_t *n_out, double *max_z, uint32_t *err, hipStream_t s)
 {
     if (n_runs <= 0) return hipSuccess;
-    // one or two candidates a run and runs for every CU: a group each, so that
-    // four and more runs share a CU (1024 runs of 10^4 SFTs, toplists of one:
-    // 435 us with four groups, 304 us with one)
-    auto *kern = k <= 2 && n_runs > 256 ? select_batch_kernel<1> : select_batch_kernel<4>;
-    const int threads = k <= 2 && n_runs > 256 ? 256 : 1024;
+    // few candidates and keys a run, and runs for every CU: a group each, so that
+    // four and more runs share a CU.  Toplists of one, with four groups and one:
+    // 1024 runs of 880 templates and 10^4 SFTs 435 and 304 us; short runs, 300 of
+    // 1000 templates 38 and 26, of 4000 39 and 54, of 2 10^5 392 and 841; 1024 of
+    // 4000 102 and 79, of 16,000 145 and 177
+    const bool small = k <= 2 && n_runs > 256 && max_t <= 8 * (int64_t)n_runs;
+    auto *kern = small ? select_batch_kernel<1> : select_batch_kernel<4>;
+    const int threads = small ? 256 : 1024;
     hipLaunchKernelGGL(kern, dim3((unsigned)n_runs), dim3(threads), 0, s, runs, k, cap_per_run, cand, cand_s64, out, n_out,
                        max_z, err);
     return hipGetLastError();
