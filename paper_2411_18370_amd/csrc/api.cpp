@@ -2772,7 +2772,7 @@ struct BatchPlan {
     std::vector<int64_t> dt_prefix, stats_prefix, gen_prefix_sft, gen_prefix_elem, sky_prefix;
     std::vector<int32_t> sft_begin, perm;
     std::vector<double> tref, sky_tile;
-    std::vector<std::vector<int2>> items;  // per tile id; then the small-bank and the local-bank kernel's
+    std::vector<int64_t> n_items;          // per tile id; then the small-bank and the local-bank kernel's
     std::vector<char> uniform;             // per run: the run-length guard applies
     std::vector<double> dt_absmax, vmax;   // per run: window inputs
     std::vector<int> group_wtp;            // per tile id: widest LDS row of its runs
@@ -2886,10 +2886,18 @@ int choose_small_chunk(const BatchPlan &pl, bool local)
     return cost[0] < cost[1] ? 5 : 8;
 }
 
-void append_items(const BatchPlan &pl, int r, std::vector<int2> &out)
+void put_items(const BatchPlan &pl, int r, int2 *out)
 {
     const int64_t n = run_items(pl, r);
-    for (int64_t t = 0; t < n; ++t) out.push_back(make_int2(r, (int)t));
+    for (int64_t t = 0; t < n; ++t) out[t] = make_int2(r, (int)t);
+}
+
+// Longest first: an item's time grows with its run's SFT count, so the workgroups
+// draining a queue end together, instead of a few long items that were queued
+// last running on an idle GPU.
+void longest_first(const BatchPlan &pl, std::vector<int> &runs)
+{
+    std::stable_sort(runs.begin(), runs.end(), [&](int a, int b) { return pl.runs[(size_t)a].n_sft > pl.runs[(size_t)b].n_sft; });
 }
 
 // Size class of a batch run for the tile cache; -1 for f0 grids too small for
@@ -2932,7 +2940,7 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
     std::vector<Launch> ls;
     int64_t item_off = 0;
     for (int id = 0; id <= tile_count() + 1; ++id) {
-        const int n_items = (int)pl.items[id].size();
+        const int n_items = (int)pl.n_items[id];
         if (n_items > 0) ls.push_back({id, item_off, n_items});
         item_off += n_items;
     }
@@ -3001,6 +3009,7 @@ static ft_status tune_batch(ft_ctx c, BatchPlan &pl, const std::vector<ft_run> &
         Cls cl;
         cl.id = kv.first;
         cl.runs = kv.second;
+        longest_first(pl, cl.runs);
         double w = 0.0, s0 = 0.0, s1 = 0.0;
         for (int r : cl.runs) {
             const ft_run &R = runs[r];
@@ -3048,11 +3057,12 @@ static ft_status tune_batch(ft_ctx c, BatchPlan &pl, const std::vector<ft_run> &
             }
             if (active[q] && (int64_t)items.size() + n_items >= 0x7fffffffLL) active[q] = 0;
             if (!active[q]) continue;
-            for (int r : cls[q].runs) append_items(pl, r, items);
-            // longest first, as the batch launch orders them
-            std::stable_sort(items.begin() + (int64_t)off[q], items.end(), [&](const int2 &a, const int2 &b2) {
-                return pl.runs[a.x].n_sft > pl.runs[b2.x].n_sft;
-            });
+            items.resize(items.size() + (size_t)n_items);
+            int2 *at = items.data() + off[q];
+            for (int r : cls[q].runs) {
+                put_items(pl, r, at);
+                at += run_items(pl, r);
+            }
         }
         off[nc] = items.size();
         if (items.empty()) continue;
@@ -3151,7 +3161,7 @@ ft_status ft_eval_batch(ft_ctx c, const ft_batch *bt, int32_t use_graph)
     BatchPlan pl;
     pl.runs.resize(n_runs);
     pl.tile.resize(n_runs);
-    pl.items.assign(tile_count() + 2, {});
+    pl.n_items.assign(tile_count() + 2, 0);
     pl.dt_prefix.assign(n_runs + 1, 0);
     pl.stats_prefix.assign(n_runs + 1, 0);
     pl.gen_prefix_sft.assign(n_runs + 1, 0);
@@ -3419,25 +3429,26 @@ ft_status ft_eval_batch(ft_ctx c, const ft_batch *bt, int32_t use_graph)
             at += (E.n_sft + SUM_BLOCK - 1) / SUM_BLOCK * E.bsum_n;
         }
     }
+    const auto group_of = [&](int r) { return pl.tile[r] >= 0 ? pl.tile[r] : tile_count() + (pl.local[r] ? 1 : 0); };
     int64_t total_items = 0;
-    for (int r = 0; r < n_runs; ++r) total_items += run_items(pl, r);
-    if (total_items >= 0x7fffffff) return fail(c, FT_E_UNSUPPORTED, "too many work items");
     pl.group_wtp.assign(tile_count() + 1, 64);
     for (int r = 0; r < n_runs; ++r) {
-        const int t = pl.tile[r];
-        append_items(pl, r, pl.items[t >= 0 ? t : tile_count() + (pl.local[r] ? 1 : 0)]);
-        if (t >= 0) pl.group_wtp[t] = std::max(pl.group_wtp[t], pl.runs[r].wtp);
+        const int64_t n = run_items(pl, r);
+        pl.n_items[group_of(r)] += n;
+        total_items += n;
+        if (pl.tile[r] >= 0) pl.group_wtp[pl.tile[r]] = std::max(pl.group_wtp[pl.tile[r]], pl.runs[r].wtp);
     }
-    // longest first within each group (an item's time grows with its run's
-    // SFT count): the workgroups draining a queue then end together, instead
-    // of a few long items that were queued last running on an idle GPU
-    for (auto &v : pl.items)
-        std::stable_sort(v.begin(), v.end(), [&](const int2 &a, const int2 &b2) {
-            return pl.runs[a.x].n_sft > pl.runs[b2.x].n_sft;
-        });
-    std::vector<int2> items_flat;
-    items_flat.reserve((size_t)total_items);
-    for (auto &v : pl.items) items_flat.insert(items_flat.end(), v.begin(), v.end());
+    if (total_items >= 0x7fffffff) return fail(c, FT_E_UNSUPPORTED, "too many work items");
+    std::vector<int> order((size_t)n_runs);
+    std::iota(order.begin(), order.end(), 0);
+    longest_first(pl, order);
+    std::vector<int64_t> at(pl.n_items.size(), 0);  // next place of each group
+    for (size_t g = 1; g < at.size(); ++g) at[g] = at[g - 1] + pl.n_items[g - 1];
+    std::vector<int2> items_flat((size_t)total_items);
+    for (int r : order) {
+        put_items(pl, r, items_flat.data() + at[group_of(r)]);
+        at[group_of(r)] += run_items(pl, r);
+    }
     if ((e = ensure(&b.items, &b.c_items, (size_t)std::max<int64_t>(total_items, 1))) != hipSuccess)
         return hip_fail(c, e, "alloc batch items");
     e = hipMemcpyAsync(b.runs, pl.runs.data(), pl.runs.size() * sizeof(EvalRun), hipMemcpyHostToDevice, c->stream);
