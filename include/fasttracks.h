@@ -595,16 +595,18 @@ const char *ft_tile_name(int32_t tile);
  * tiles on the call's own data before evaluating:
  *   GRID bank   class = (n_f0, n_f1, n_sft, floor(log2 n_sky), Doppler
  *               half-width in bins, guard eligibility); every candidate runs
- *               over one contiguous range of the Doppler-ordered sky (about
- *               2.5e11 evaluations, or the whole bank if smaller)
+ *               over the whole bank or, beyond about 1e12 evaluations, blocks
+ *               of sky points spread over the Doppler order
  *   batch       class of a run = (floor(log2 n_f0), min(n_f1, 8), guard
- *               eligibility), runs with n_f0 >= 32 only (smaller f0 grids use
- *               the direct kernel); each pass launches every class's work
+ *               eligibility), runs with n_f0 >= 32 only (smaller f0 grids have
+ *               kernels of their own); each pass launches every class's work
  *               items with its next candidate and times each class alone
  * Candidates are the tiles whose cost-model estimate (wasted lanes x VALU
- * operations per evaluation) is within 1.6x of the best and whose LDS window
- * fits; the fastest is cached per context and used by later calls of that
- * class with tile = 0 or FT_TILE_TUNE.  Tuning synchronises the stream and
+ * operations per evaluation) is within 1.6x of the best, and those that an
+ * untuned call would take, where their LDS window fits.  Each is launched as
+ * the call would launch it, split over SFT blocks where the tile can be and the
+ * bank or batch leaves the GPU idle.  The fastest is cached per context and used
+ * by later calls of that class with tile = 0 or FT_TILE_TUNE.  Tuning synchronises the stream and
  * overwrites the statistic buffer (the call then evaluates as usual).
  */
 #define FT_TILE_TUNE (-1)

@@ -1620,8 +1620,10 @@ static hipError_t launch_grid(const EvalRun &run, int tile, const WindowPlan *ta
 // spread over the whole order, about 1e12 evaluations) and returns the
 // fastest in best (0-based; -1 when no candidate's window fits in LDS).  Each
 // candidate runs as a call would run it: with its f1-tail companion when its
-// JT does not divide n_f1.
-static ft_status tune_plain(ft_ctx c, const EvalRun &run, double dt_absmax, bool uniform, int &best)
+// JT does not divide n_f1, split over SFT blocks as plan_grid_tile would (banks
+// larger than the sample are never split).  The tile that an untuned call would
+// take is among them.
+static ft_status tune_plain(ft_ctx c, const EvalRun &run, double dt_absmax, bool uniform, bool may_split, int &best)
 {
     const auto t_start = std::chrono::steady_clock::now();
     best = -1;
@@ -1674,9 +1676,14 @@ static ft_status tune_plain(ft_ctx c, const EvalRun &run, double dt_absmax, bool
         WindowPlan tail;  // tile -1: no f1-tail dispatch
     };
     std::vector<Trial> trials;
-    for (int id : tune_candidates((double)n0, (double)n1, uniform)) {
-        const WindowPlan wp = plan_window(c->f0_h.data(), n0, c->f1_h.data(), n1, c->sky_tile_h.data(), ns, dt_absmax,
-                                          c->vmax, c->t_sft, id);
+    const size_t n_blk = (size_t)((run.n_sft + SUM_BLOCK - 1) / SUM_BLOCK);
+    may_split = may_split && n_s == ns;
+    std::vector<int> ids = tune_candidates((double)n0, (double)n1, uniform);
+    const int untuned = choose_grid(c, run, dt_absmax, uniform, may_split).main.tile;
+    if (untuned >= 0 && std::find(ids.begin(), ids.end(), untuned) == ids.end()) ids.push_back(untuned);
+    for (int id : ids) {
+        const GridPlan gp = plan_grid_tile(c, run, id, dt_absmax, may_split);
+        const WindowPlan &wp = gp.main;
         if (wp.tile < 0) continue;
         EvalRun r = run;
         r.wt = wp.wt;
@@ -1687,15 +1694,13 @@ static ft_status tune_plain(ft_ctx c, const EvalRun &run, double dt_absmax, bool
         r.sky_perm = smp_perm;
         r.n_sky = (int32_t)n_s;
         r.tiles_sky = (int32_t)((n_s + tile_cfg(id).NW - 1) / tile_cfg(id).NW);
-        WindowPlan tail;
-        const int jt = tile_cfg(id).JT;
-        const int rem = (int)(n1 % jt);
-        const int comp = rem && n1 > jt ? tile_companion(id, rem) : -1;
-        if (comp >= 0 && (!run.sky_norm || tile_has_sky_weights(comp))) {
-            tail = plan_window(c->f0_h.data(), n0, c->f1_h.data() + (n1 - rem), rem, c->sky_tile_h.data(), ns,
-                               dt_absmax, c->vmax, c->t_sft, comp);
-            if (tail.tile >= 0) tail.tiles_sky = (int32_t)((n_s + tile_cfg(comp).NW - 1) / tile_cfg(comp).NW);
+        if (gp.bps > 0 && ensure(&c->d_bsum, &c->cap_bsum, n_blk * (size_t)(n0 * n1 * ns)) == hipSuccess) {
+            r.seg_blocks = (int32_t)gp.bps;
+            r.bsum = c->d_bsum;
+            r.bsum_n = n0 * n1 * ns;
         }
+        WindowPlan tail = gp.tail;
+        if (tail.tile >= 0) tail.tiles_sky = (int32_t)((n_s + tile_cfg(tail.tile).NW - 1) / tile_cfg(tail.tile).NW);
         trials.push_back({id, r, tail});
     }
     c->tune_log.clear();
@@ -1841,7 +1846,7 @@ ft_status ft_eval_templates(ft_ctx c, const ft_bank *bank, double t_ref, const f
             if (it != c->tune_cache.end()) {
                 tile = it->second;
             } else if (opts->tile == FT_TILE_TUNE) {
-                st = tune_plain(c, run, dt_absmax, uniform, tile);
+                st = tune_plain(c, run, dt_absmax, uniform, may_split, tile);
                 if (st != FT_OK) return st;
                 if (tile >= 0) c->tune_cache[key] = tile;
             }
@@ -2819,29 +2824,38 @@ int64_t unsplit_items(const BatchPlan &pl, int r)
 
 int64_t run_items(const BatchPlan &pl, int r) { return unsplit_items(pl, r) * run_rows(pl.runs[r]); }
 
+// Whether batch run r can be split over SFT blocks: every run but those on a tile
+// without such a form (one that was asked for or tuned).
+bool can_split(const BatchPlan &pl, int r) { return pl.tile[r] < 0 || tile_has_split(pl.tile[r], false); }
+
 // Splits a batch over SFT blocks when its items leave the GPU idle: fewer than
 // BATCH_WAVES wavefronts, four rounds of the 4096 that work at a time.  Rows of
 // at least two blocks (each starts a pipeline), about as many as make up that
-// number; the block sums take at most 1 GiB.  64 runs, 1.4e3 items: evaluation
-// 3.3 ms unsplit, 1.3 ms split.
+// number beside the runs that cannot be split; the block sums take at most 1
+// GiB.  64 runs, 1.4e3 items: evaluation 3.3 ms unsplit, 1.3 ms split.
 void plan_batch_split(BatchPlan &pl)
 {
     constexpr int64_t BATCH_WAVES = 16384;
-    int64_t waves = 0, blocks = 0;
+    int64_t waves = 0, whole = 0, blocks = 0;
     pl.bps = 0;
     pl.bsum_len = 0;
     for (size_t r = 0; r < pl.runs.size(); ++r) {
         const EvalRun &E = pl.runs[r];
         const int64_t n_t = (int64_t)E.n_f0 * E.n_f1 * E.n_sky, n_blk = (E.n_sft + SUM_BLOCK - 1) / SUM_BLOCK;
         const int tile = pl.tile[r];
-        if (tile >= 0 && !tile_has_split(tile, false)) return;
         const int64_t w = unsplit_items(pl, (int)r) * (tile >= 0 ? tile_cfg(tile).NW : pl.local[r] ? LOCAL_JS / 64 : 1);
+        if (!can_split(pl, (int)r)) {
+            whole += w;
+            continue;
+        }
         waves += w;
         blocks += w * n_blk;
         pl.bsum_len += n_blk * n_t;
     }
-    if (waves >= BATCH_WAVES || (double)pl.bsum_len * 4.0 > kGridSplitBytes || pl.runs.size() > 65535) return;
-    const int64_t rows = (BATCH_WAVES + waves - 1) / waves;
+    if (waves == 0 || waves + whole >= BATCH_WAVES || (double)pl.bsum_len * 4.0 > kGridSplitBytes ||
+        pl.runs.size() > 65535)
+        return;
+    const int64_t rows = (BATCH_WAVES - whole + waves - 1) / waves;
     pl.bps = (int)std::max<int64_t>(2, blocks / waves / rows);
 }
 
@@ -2960,7 +2974,7 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
         hipStream_t s = q == 0 ? st : c->side[q - 1];
         if (L.id < tile_count())
             e = launch_eval_batch(b.runs, b.items + L.off, L.n, pl.group_wtp[L.id], b.counters + L.id,
-                                  std::min(L.n, 2048), tile_cfg(L.id), pl.bps > 0, s);
+                                  std::min(L.n, 2048), tile_cfg(L.id), pl.bps > 0 && tile_has_split(L.id, false), s);
         else if (L.id == tile_count() + 1)
             e = launch_eval_batch_local(b.runs, b.items + L.off, L.n, pl.local_chunk, b.counters + L.id,
                                         std::min(L.n, 1024), s);
@@ -2985,7 +2999,9 @@ static ft_status launch_batch_sequence(ft_ctx c, const BatchPlan &pl, bool gener
 // the time offsets and tables are produced first.  Pass p launches the work
 // items of every class with its p-th candidate tile, each class in a
 // persistent launch of its own between two events, after one untimed pass
-// that brings the clocks up.  The fastest tile of each class is cached.
+// that brings the clocks up; split over SFT blocks as the untuned batch would be
+// where the tile can.  The untuned batch's tiles are among the candidates.  The
+// fastest tile of each class is cached.
 static ft_status tune_batch(ft_ctx c, BatchPlan &pl, const std::vector<ft_run> &runs, const double *f0h,
                             const double *f1h, double t_sft, bool gen, const std::map<int, std::vector<int>> &classes)
 {
@@ -3020,6 +3036,9 @@ static ft_status tune_batch(ft_ctx c, BatchPlan &pl, const std::vector<ft_run> &
         }
         cl.evals = w;
         cl.cand = tune_candidates(s0 / w, s1 / w, pl.uniform[cl.runs[0]] != 0);
+        for (int r : cl.runs)
+            if (pl.tile[r] >= 0 && std::find(cl.cand.begin(), cl.cand.end(), pl.tile[r]) == cl.cand.end())
+                cl.cand.push_back(pl.tile[r]);
         cl.rate.assign(cl.cand.size(), 0.0);
         n_pass = std::max(n_pass, cl.cand.size());
         cls.push_back(std::move(cl));
@@ -3052,6 +3071,7 @@ static ft_status tune_batch(ft_ctx c, BatchPlan &pl, const std::vector<ft_run> &
                     active[q] = 0;  // some run's window does not fit this tile
                     break;
                 }
+                pl.runs[r].seg_blocks = tile_has_split(tile, false) ? pl.bps : 0;
                 wtp[q] = std::max(wtp[q], pl.runs[r].wtp);
                 n_items += run_items(pl, r);
             }
@@ -3078,7 +3098,7 @@ static ft_status tune_batch(ft_ctx c, BatchPlan &pl, const std::vector<ft_run> &
             e = hipEventRecord(ev[2 * q], c->stream);
             if (e == hipSuccess)
                 e = launch_eval_batch(b.runs, b.items + off[q], n_items, wtp[q], b.counters + q, std::min(n_items, 2048),
-                                      tile_cfg(cls[q].cand[p]), false, c->stream);
+                                      tile_cfg(cls[q].cand[p]), pl.bps > 0 && tile_has_split(cls[q].cand[p], false), c->stream);
             if (e == hipSuccess) e = hipEventRecord(ev[2 * q + 1], c->stream);
         }
         // the host item list is reused by the next pass
@@ -3404,31 +3424,35 @@ ft_status ft_eval_batch(ft_ctx c, const ft_batch *bt, int32_t use_graph)
         e = hipMemcpyAsync(b.power, bt->power, (size_t)bt->power_len * sizeof(float), hipMemcpyDefault, c->stream);
         if (e != hipSuccess) return hip_fail(c, e, "upload batch tables");
     }
+    // the kernels of the runs without a tile, and the split
+    const auto plan_split = [&] {
+        for (int r = 0; r < n_runs; ++r)
+            pl.local[r] = pl.tile[r] < 0 && local_bank(pl, r, runs[r], f0h.data(), f1h.data(), skyh.data(), bt->t_sft);
+        pl.small_chunk = choose_small_chunk(pl, false);
+        pl.local_chunk = choose_small_chunk(pl, true);
+        plan_batch_split(pl);
+        if (pl.bps > 0 && ensure(&b.bsum, &b.c_bsum, (size_t)pl.bsum_len) != hipSuccess) {
+            (void)hipGetLastError();  // no room: not split
+            pl.bps = 0;
+        }
+        int64_t at = 0;
+        for (int r = 0; r < n_runs; ++r) {
+            EvalRun &E = pl.runs[r];
+            E.seg_blocks = can_split(pl, r) ? pl.bps : 0;
+            E.bsum = E.seg_blocks > 0 ? b.bsum + at : nullptr;
+            E.bsum_n = E.seg_blocks > 0 ? (int64_t)E.n_f0 * E.n_f1 * E.n_sky : 0;
+            at += (E.n_sft + SUM_BLOCK - 1) / SUM_BLOCK * E.bsum_n;
+        }
+    };
+    plan_split();
     if (!to_tune.empty()) {
         ft_status st = tune_batch(c, pl, runs, f0h.data(), f1h.data(), bt->t_sft, gen, to_tune);
         if (st != FT_OK) return st;
         to_tune.clear();
         plan_tiles();
+        plan_split();
     }
     // work items grouped by tile (the direct kernel's last)
-    for (int r = 0; r < n_runs; ++r)
-        if (pl.tile[r] < 0) pl.local[r] = local_bank(pl, r, runs[r], f0h.data(), f1h.data(), skyh.data(), bt->t_sft);
-    pl.small_chunk = choose_small_chunk(pl, false);
-    pl.local_chunk = choose_small_chunk(pl, true);
-    plan_batch_split(pl);
-    if (pl.bps > 0 && ensure(&b.bsum, &b.c_bsum, (size_t)pl.bsum_len) != hipSuccess) {
-        (void)hipGetLastError();  // no room: not split
-        pl.bps = 0;
-    }
-    if (pl.bps > 0) {
-        int64_t at = 0;
-        for (EvalRun &E : pl.runs) {
-            E.seg_blocks = pl.bps;
-            E.bsum = b.bsum + at;
-            E.bsum_n = (int64_t)E.n_f0 * E.n_f1 * E.n_sky;
-            at += (E.n_sft + SUM_BLOCK - 1) / SUM_BLOCK * E.bsum_n;
-        }
-    }
     const auto group_of = [&](int r) { return pl.tile[r] >= 0 ? pl.tile[r] : tile_count() + (pl.local[r] ? 1 : 0); };
     int64_t total_items = 0;
     pl.group_wtp.assign(tile_count() + 1, 64);
