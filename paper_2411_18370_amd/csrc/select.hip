@@ -1113,17 +1113,17 @@ hipError_t launch_select(const EvalRun &r, bool grid, int n_seg, int k, double r
     return hipGetLastError();
 }
 
-// Re-summation of the candidates, about `expect` of them: a workgroup each up
-// to 4096 (50 candidates of a binary bank over 10^4 SFTs: 245 us with a wave
-// each, 62 us with a workgroup), a wave each beyond (the 10^4 of a box
-// search: 0.88 against 1.2 ms).
+// Re-summation of the candidates, about `expect` of them: a workgroup each up to
+// 1024, a wave each beyond.  Over 10^4 SFTs with a workgroup each and a wave each:
+// 250 candidates 33 and 67 us, 1000 65 and 62 (binary banks 70 and 81), 3000 181
+// and 163, 10^4 730 and 547; over 30 SFTs, 4000: 22 and 10.
 static void launch_rescore(const EvalRun &r, bool grid, const int64_t *cand, const uint32_t *off, int n_seg, int64_t cap,
                            int64_t expect, double *s64, double *mom, hipStream_t s)
 {
     if (mom)
         hipLaunchKernelGGL(rescore_kernel<true>, dim3(2048), dim3(64 * RS_WAVES), 0, s, r, grid, cand, off, n_seg, cap,
                            s64, mom);
-    else if (expect <= 4096)
+    else if (expect <= 1024)
         hipLaunchKernelGGL(rescore_kernel<false>, dim3(2048), dim3(64 * RS_WAVES), 0, s, r, grid, cand, off, n_seg, cap,
                            s64, mom);
     else

@@ -56,6 +56,17 @@ def test_rescore_long_toplists(ft, k):
         _check(c, w, s64, f0, k)
 
 
+@pytest.mark.parametrize("k,n_per_det", [(1024, 10), (1025, 10), (1024, 400), (1025, 400)])
+def test_rescore_either_way(ft, k, n_per_det):
+    """The longest toplist re-summed by a workgroup each and the shortest by a wave each."""
+    w = synth.tiny_bank(40, 1, 1, n_per_det)
+    f0, f1, sky = _list_bank(w, 3000)
+    s64, _ = oracle.eval_list(w.t_mid, w.t_ref, w.t_sft, w.first_bin, w.power, None, w.v, f0, f1, sky)
+    with _load(ft, w) as c:
+        c.eval_templates(f0, f1, sky, w.t_ref, k, w.sub_edges, kind=ft.FT_BANK_LIST)
+        _check(c, w, s64, f0, k)
+
+
 def test_rescore_batch_groups(ft):
     """Runs of 5, 768 and 1537 SFTs, toplists of 1, 4 and 11 (groups of four candidates)."""
     import torch
