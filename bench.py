@@ -522,7 +522,7 @@ def bench_surrogate(ft, synth, tau, n_train, n_test, log):
     flops = rows * 2 * 3 * 2 * 256 * 256
     mfma = {"flops": flops, "steps": epochs * -(-n_train // batch), "TFLOPs": flops / t_train / 1e12,
             "frac_of_bf16_dense_peak": flops / t_train / 2.5e15,
-            "note": "whole training call (host validation, two launches per step) over the "
+            "note": "whole training call (the inputs' check on the device, two launches per step) over the "
                     "bf16 dense peak of 2.5 PFLOP/s; batch 2048 leaves each product at 0.27 "
                     "GFLOP, so a step is bound by launch and reduction latency"}
     per_query = t_pred / n_test

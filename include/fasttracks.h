@@ -606,8 +606,9 @@ const char *ft_tile_name(int32_t tile);
  * untuned call would take, where their LDS window fits.  Each is launched as
  * the call would launch it, split over SFT blocks where the tile can be and the
  * bank or batch leaves the GPU idle.  The fastest is cached per context and used
- * by later calls of that class with tile = 0 or FT_TILE_TUNE.  Tuning synchronises the stream and
- * overwrites the statistic buffer (the call then evaluates as usual).
+ * by later calls of that class with tile = 0 or FT_TILE_TUNE.  Tuning synchronises
+ * the stream and overwrites the statistic buffer (the call then evaluates as
+ * usual).
  */
 #define FT_TILE_TUNE (-1)
 

@@ -397,8 +397,9 @@ double model_cost(int id, double n_f0, double n_f1)
     const double f0w = std::ceil(n_f0 / (64.0 * t.L)) * 64.0 * t.L / n_f0;
     const double f1w = std::ceil(n_f1 / t.JT) * t.JT / n_f1;
     const double ops = t.L > 1 ? (7.0 + t.L) / t.L : 7.0;
-    // a run tile's staging and parameters are shared by its f1 values: one
-    // takes 2.4 times, two 1.4 times the time a slot of three (5 f0 values)
+    // a run tile's staging and parameters are shared by its f1 values: with one a
+    // slot takes 2.2 (runs of 5 f0 values) to 2.4 (of 3) times as long as with
+    // three, with two 1.3 times (kTileTime, full CUs); taken as 2.2 and 1.4
     const double few = t.L > 1 && t.JT < 3 ? (t.JT == 1 ? 2.2 : 1.4) : 1.0;
     return f0w * f1w * ops * few;
 }
@@ -1870,8 +1871,6 @@ ft_status ft_eval_templates(ft_ctx c, const ft_bank *bank, double t_ref, const f
                                               gp.tail.tile >= 0 ? &gp.tail : nullptr));
 }
 
-// Launch sequence of an evaluation: clear flags, map sub-bands, evaluate,
-// select, re-sum, rank (run fully prepared; n_seg_map = f0 values to map).
 // Time segments of the summation blocks for the bank kernel: bit j of a
 // block's mask is set where its SFT j starts a segment.  Times ascend in a
 // segment and span at most 1.2 times the median block's span (blocks across a
@@ -2139,6 +2138,9 @@ static hipError_t deliver(ft_ctx c, int n_seg, int k, const SelectBufs &sb)
     return e;
 }
 
+// Launch sequence of an evaluation: clear flags, map sub-bands, evaluate,
+// select, re-sum, rank, deliver (run fully prepared; n_seg_map = f0 values to
+// map).
 static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile, int64_t n_t, int64_t n_seg_map,
                                     const ft_eval_opts *opts, const std::vector<double> &edges, float *stats,
                                     const WindowPlan *tail)

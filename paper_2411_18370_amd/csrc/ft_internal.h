@@ -616,11 +616,11 @@ hipError_t launch_select_prep(const double *f0, int64_t n, const double *edges, 
                               const SelectBufs &b, uint32_t *err, hipStream_t s);
 hipError_t launch_select(const EvalRun &run, bool grid, int n_seg, int k, double rel_err,
                          const SelectBufs &b, hipStream_t s);
-// Writes the error flags, the candidate count, the toplists' lengths and their
-// entries to host memory mapped into the device: DeliverHead | n_out[n_seg]
-// (padded to 16 bytes) | out[n_seg][k].
+// Writes the error flags, the toplists' lengths and their entries to host memory
+// mapped into the device: DeliverHead | n_out[n_seg] (padded to 16 bytes) |
+// out[n_seg][k].
 struct DeliverHead {
-    uint32_t flags, total;
+    uint32_t flags;
 };
 inline size_t deliver_entries_at(int n_seg) { return (sizeof(DeliverHead) + (size_t)n_seg * 4 + 15) / 16 * 16; }
 hipError_t launch_deliver(const uint32_t *err, int n_seg, int k, const SelectBufs &b, char *host, hipStream_t s);

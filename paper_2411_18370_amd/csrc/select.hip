@@ -838,10 +838,7 @@ __global__ __launch_bounds__(256) void deliver_kernel(const uint32_t *err, int n
     constexpr int W = sizeof(ft_candidate) / 8;
     static_assert(sizeof(ft_candidate) % 8 == 0, "entries are copied in words of 8 bytes");
     const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
-    if (i0 == 0) {
-        head->flags = *err;
-        head->total = b.off[n_seg];
-    }
+    if (i0 == 0) head->flags = *err;
     for (int64_t sg = i0; sg < n_seg; sg += step) n_out[sg] = b.n_out[sg];
     const uint64_t *src = (const uint64_t *)b.out;
     const int64_t row = (int64_t)k * W;
