@@ -104,10 +104,11 @@ constexpr int row_threads(int r) { return 64 * r; }
 //
 // Without TRAIN a workgroup keeps both matrices and walks over tiles: nothing
 // but features is read, and the bound is the VALU's erf (two branches each, so a
-// lane's run one after the other and take waves to overlap; 200,000 rows: 233 us,
-// 1200 us as four launches per 8192 rows).  A training step's workgroups are bound by the
-// latency of five layers in turn, the first behind the weights' way from L2
-// (2048 rows: 17 us, 59 us as seven launches).
+// lane's run one after the other and take waves to overlap; 200,000 rows: 233 us
+// with the VALU 81% busy, 1200 us as four launches per 8192 rows).  A training
+// step's workgroups are bound by the latency of five layers in turn, the first
+// behind the weights' way from L2 (2048 rows: 17 us, VALU 27% busy; 59 us as
+// seven launches).
 template <int R, bool TRAIN>
 __global__ __launch_bounds__(row_threads(R)) void mlp_rows_kernel(const float *raw, const float *labels, MlpBufs m, MlpConst c,
                                                        int bsz, int n_tiles, float inv_n, float *prob)
