@@ -378,7 +378,9 @@ ft_status ft_toplist(ft_ctx ctx, int32_t sub, ft_candidate *out, int32_t *n_out)
  * the POWER statistic this is the persistence check of Sec. VI.B: the loudest
  * template whose number count reaches a minimum is the first entry that
  * reaches it (when none of the k does, it lies deeper than the toplist).
- * Synchronises the context's stream.  Errors as ft_toplist.
+ * Synchronises the context's stream.  Errors as ft_toplist, and FT_E_STATE when
+ * the evaluation's bank is no longer on the device (an evaluation that was
+ * refused after its upload may have taken its place).
  */
 ft_status ft_toplist_number_count(ft_ctx ctx, int32_t sub, double *nc_out, double *z_out, int32_t *n_out);
 

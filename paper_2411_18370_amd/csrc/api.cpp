@@ -205,6 +205,9 @@ struct ft_ctx_s {
     size_t cap_h_top = 0;
     bool delivered = false;
     EvalRun last_run{};
+    struct {
+        size_t f0, f1, sky, bin, norm, ms, stats;
+    } last_caps{};  // capacities of its bank's buffers
     bool last_grid = true;
     int last_k = 0, last_nsub = 0;
     int64_t last_cap = 0;
@@ -365,6 +368,22 @@ hipError_t with_room(ft_ctx c, F alloc)
 {
     const hipError_t e = alloc();
     return e == hipErrorOutOfMemory && give_back(c) ? alloc() : e;
+}
+
+// Whether the buffers that the last evaluation's re-summation reads are still
+// the context's: a later bank may have freed them before its evaluation was
+// refused.  (The SFT set's buffers end the evaluation with them.)  A buffer
+// allocated again has another capacity, should it lie in the same place.
+bool bank_alive(ft_ctx c)
+{
+    const EvalRun &r = c->last_run;
+    const auto &l = c->last_caps;
+    const auto is = [](const void *p, size_t cap, const void *q, size_t qcap) { return !p || (p == q && cap == qcap); };
+    return (is(r.f0, l.f0, c->d_f0, c->cap_f0) || is(r.f0, l.f0, c->d_f0_new, c->cap_f0_new)) &&
+           (is(r.f1, l.f1, c->d_f1, c->cap_f1) || is(r.f1, l.f1, c->d_f1_new, c->cap_f1_new)) &&
+           (is(r.sky, l.sky, c->d_sky, c->cap_sky) || is(r.sky, l.sky, c->d_sky_new, c->cap_sky_new)) &&
+           is(r.ap, l.bin, c->d_bin, c->cap_bin) && is(r.sky_norm, l.norm, c->d_sky_norm, c->cap_sky_norm) &&
+           is(r.sky_ms, l.ms, c->d_sky_ms, c->cap_sky_ms);
 }
 
 // Doppler-coherent visiting order of the sky points: bands of equal height in
@@ -2202,6 +2221,7 @@ static ft_status launch_eval_select(ft_ctx c, EvalRun &run, bool grid, int tile,
     if (e != hipSuccess) return hip_fail(c, e, "launch evaluation");
     c->have_eval = true;
     c->last_run = run;
+    c->last_caps = {c->cap_f0, c->cap_f1, c->cap_sky, c->cap_bin, c->cap_sky_norm, c->cap_sky_ms, c->cap_stats};
     c->last_grid = grid;
     c->last_k = k;
     c->last_nsub = n_seg;
@@ -2422,6 +2442,8 @@ ft_status ft_sync(ft_ctx c)
     if (st != FT_OK || !c->have_eval) return st;
     // Grow the candidate buffer and redo the compaction if it overflowed.
     if (flags & ERR_CAND_OVERFLOW) {
+        if (!bank_alive(c) || c->last_run.stats != c->d_stats || c->last_caps.stats != c->cap_stats)
+            return fail(c, FT_E_STATE, "the bank of the last evaluation has been replaced before its toplists were complete");
         uint32_t total = 0;
         hipMemcpy(&total, c->d_off + c->last_nsub, sizeof total, hipMemcpyDeviceToHost);
         // the per-sub-band offsets are 32-bit and saturate at 2^32 - 1
@@ -2499,6 +2521,7 @@ ft_status ft_toplist_number_count(ft_ctx c, int32_t sub, double *nc_out, double 
     if (sub < 0 || sub >= c->last_nsub) return fail(c, FT_E_INVALID, "sub-band %d out of range", sub);
     if (!nc_out || !n_out) return fail(c, FT_E_INVALID, "nc_out and n_out must be non-null");
     ft_status st = ft_sync(c);
+    if (st == FT_OK && !bank_alive(c)) st = fail(c, FT_E_STATE, "the bank of the last evaluation has been replaced");
     if (st == FT_OK) st = ensure_nc(c);
     if (st != FT_OK) return st;
     hipError_t e = ensure(&c->d_top_nc, &c->cap_top_nc, (size_t)c->last_k * 3);

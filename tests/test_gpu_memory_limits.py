@@ -148,3 +148,33 @@ with ft.Context(0) as c:
     c.eval_campaign(cp)
     c.batch_toplist(0, 3)
 """)
+
+
+def test_number_counts_of_a_bank_that_is_gone(ft):
+    """Evaluations refused after their bank was uploaded (lists have no sky-dependent weights)
+    free the last one's buffers where theirs need more: its toplists stay, its number counts
+    can be read as long as its bank is there."""
+    _run(ft, 1 << 40, LIST + """
+def counts(c):
+    return c.toplist_number_count(0, 4)[0].tolist()
+def fail(c, seed, n):
+    refused(ft.FT_E_UNSUPPORTED, lambda: c.eval_templates(*bank(seed, n), w.t_ref, 4, edges, kind=ft.FT_BANK_LIST,
+                                                          weights=ft.FT_WEIGHTS_SKY))
+with ft.Context(0) as c:
+    load(c)
+    want = top(c, bank(1, 2000))
+    nc = counts(c)
+    fail(c, 2, 3000)  # beside the evaluated bank, which stays
+    assert counts(c) == nc
+    fail(c, 3, 9000)  # into the evaluated bank's buffers, which are too small
+    refused(ft.FT_E_STATE, lambda: counts(c))
+    assert [(t.index, t.s64) for t in c.toplist(0, 4)] == want
+    assert top(c, bank(1, 2000)) == want and counts(c) == nc
+    c.eval_templates(w.f0, w.f1, w.sky, w.t_ref, 4, edges)
+    nc = counts(c)
+    assert len(nc) == 4
+    fail(c, 4, 20000)
+    fail(c, 5, 50000)
+    refused(ft.FT_E_STATE, lambda: counts(c))
+    assert len(c.toplist(0, 4)) == 4
+""")
